@@ -197,7 +197,7 @@ struct pack_handle {
   // tile sets of the forward, data- and weight-gradient GEMMs: -1 chooses per
   // launch (launch_tiles), else a fixed TileSet
   int tiles_fwd = -1, tiles_dx = -1, tiles_dw = -1;
-  TileSet ns_tiles = TILES_SMALL;  // tile set of the Newton-Schulz GEMMs
+  int ns_tiles = -1;  // tile set of the Newton-Schulz GEMMs: -1 chooses per launch, else a fixed TileSet
   TileSet emb_tiles = TILES_SMALL;  // tile set of the embedded first layer's forward (training and evaluation)
   bool muon_fused = true;  // the Muon update in the last Newton-Schulz GEMM's epilogue
   // side stream for ALU-bound work that overlaps memory-bound kernels of the
@@ -491,7 +491,8 @@ struct Plan {
 // a remainder of at most 128 rows or columns is covered by a strip of small
 // 128 x 128 tiles (a larger remainder takes one more, partly filled, big
 // tile).  Tall set: 256 x 128 tiles, rows as in the big set, the last column
-// tile partly filled.  Small set: 128 x 128 tiles only.
+// tile partly filled.  Small set: 128 x 128 tiles only.  Mini set: 64 x 64
+// tiles only.
 void add_tiles(Plan& p, Launch& ln, int d, int M, int N, int kdepth) {
   const size_t first = p.tiles.size();
   ln.ts = p.tile_set;
@@ -516,13 +517,16 @@ void add_tiles(Plan& p, Launch& ln, int d, int M, int N, int kdepth) {
     return;
   }
   const bool big = p.tile_set == TILES_BIG, tall = p.tile_set == TILES_TALL;
+  const bool mini = p.tile_set == TILES_MINI;
+  const int edge = mini ? kMiniTile : kSmallTile;  // the square tiles (all of them, or the edge strips)
   const int Mb = big || tall ? big_end(M) : 0;
   const int Nb = big ? big_end(N) : (tall ? (int)round_up(N, kSmallTile) : 0);
   const int tn = big ? kBigTile : kSmallTile;  // columns of the large tile
   const int large = big ? kShapeBig : kShapeTall;
   auto push = [&](int m0, int n0, int shape) {
-    const int tm = shape == kShapeSmall ? kSmallTile : kBigTile;
-    const int tw = shape == kShapeBig ? kBigTile : kSmallTile;
+    const int tm = shape == kShapeBig || shape == kShapeTall ? kBigTile : edge;
+    const int tw = shape == kShapeBig ? kBigTile : edge;
+    if (mini) shape = kShapeMini;
     const int mb = std::min(tm, M - m0), nb = std::min(tw, N - n0);
     p.tiles.push_back(Tile{d, m0, n0, shape});
     p.cost.push_back((int64_t)kdepth * std::max(mb, 0) * std::max(nb, 0));
@@ -531,8 +535,8 @@ void add_tiles(Plan& p, Launch& ln, int d, int M, int N, int kdepth) {
     for (int n0 = 0; n0 < Nb; n0 += tn) push(m0, n0, large);
   for (int m0 = 0; m0 < Mb; m0 += kSmallTile)
     for (int n0 = Nb; n0 < N; n0 += kSmallTile) push(m0, n0, kShapeSmall);
-  for (int m0 = Mb; m0 < M; m0 += kSmallTile)
-    for (int n0 = 0; n0 < N; n0 += kSmallTile) push(m0, n0, kShapeSmall);
+  for (int m0 = Mb; m0 < M; m0 += edge)
+    for (int n0 = 0; n0 < N; n0 += edge) push(m0, n0, kShapeSmall);
   // Wider than tall (the embedded first layer's dE = dZ_1 W_1 and dW_1 =
   // dZ_1^T E, thousands of columns): tiles in column-strip order, so the row
   // tiles sharing a strip of the wide operand run together and read it once
@@ -685,6 +689,13 @@ void add_tiles_sym(Plan& p, Launch& ln, int d, int S, int kdepth) {
   if (p.tile_set == TILES_SMALL) {
     for (int m0 = 0; m0 < S; m0 += kSmallTile)
       for (int n0 = m0; n0 < S; n0 += kSmallTile) push(m0, n0, kShapeSmall);
+  } else if (p.tile_set == TILES_MINI) {
+    for (int m0 = 0; m0 < S; m0 += kMiniTile)
+      for (int n0 = m0; n0 < S; n0 += kMiniTile) {
+        p.tiles.push_back(Tile{d, m0, n0, kShapeMini});
+        p.cost.push_back((int64_t)kdepth * std::min(kMiniTile, S - m0) * std::min(kMiniTile, S - n0) *
+                         (m0 < n0 ? 2 : 1));
+      }
   } else {
     const bool big = p.tile_set == TILES_BIG;
     const int large = big ? kShapeBig : kShapeTall, tn = big ? kBigTile : kSmallTile;
@@ -706,10 +717,42 @@ void add_tiles_sym(Plan& p, Launch& ln, int d, int S, int kdepth) {
   ln.ntiles = (int)p.tiles.size() - ln.tile0;
 }
 
-void plan_muon(const pack_handle* h, const Bufs& bf, const std::vector<int> (&group)[kGroups], Plan& p) {
+// Tile set of one forward / data-gradient / weight-gradient launch whose
+// 128 x 128 tiles number n_small: fixed by `forced` (>= 0), else 256 x 128 tiles
+// when there are at least kTallMinTiles small ones (two full rounds of tall
+// tiles at two workgroups per CU), small tiles otherwise.  Measured (ms per
+// step, all small / all tall / chosen): 64 members of widths 64..2048 at batch
+// 2048 (launches of 700..2800 small tiles) 6.29 / 5.76; 64 of widths
+// 256..1024 at batch 1024 (500..840) 1.45 / 1.53 (tall dW alone 1.53);
+// 32 of 256..1024 (~440) 0.63 / 0.67.
+// Weight-gradient launches also need a depth (padded batch) of at least
+// kTallMinDepthDw: their small tiles stream the fused optimizer over the whole
+// staged gradient tile, which the tall tiles do not, and at a 1024-row batch
+// that epilogue outweighs the tall tiles' faster main loop (the embedded first
+// layer's dW: 7.05 ms small, 7.99 ms tall), at 2048 rows it does not
+// (widths 64..2048: 6.29 -> 6.09 ms per step with tall dW tiles alone).
+constexpr int kTallMinTiles = 1024, kTallMinDepthDw = 2048;
+// Mini tiles below kMiniMaxTiles small ones (one for each CU): such a launch
+// leaves CUs idle, and four times the workgroups share its depth chains (fp32
+// ones above all, whose MFMAs run at 1/16 of the bf16 rate).  Measured, small /
+// mini: a prediction of 37 rows by 16 members of widths 128..512 (48 small
+// tiles a layer) 56 / 46 us; an fp32 step of 9 members of widths 33..301 at
+// batch 300 (at most 45) 464 / 265 us; a bf16 step of 32 members of widths
+// 256..1024 at batch 1024 (~220 a launch) 636 / 634 us; with mini tiles up to
+// 640 small ones 668 us.
+constexpr int kMiniMaxTiles = 256;
+TileSet launch_tiles(const pack_handle* h, int forced, int64_t n_small, int min_depth = 0) {
+  if (forced >= 0) return (TileSet)forced;
+  if (n_small < kMiniMaxTiles) return TILES_MINI;
+  if (h->prec != Prec::BF16 || h->Bp < min_depth) return TILES_SMALL;
+  return n_small >= kTallMinTiles ? TILES_TALL : TILES_SMALL;
+}
+int64_t small_tiles(int M, int N) { return (int64_t)((M + kSmallTile - 1) / kSmallTile) * ((N + kSmallTile - 1) / kSmallTile); }
+
+void plan_muon(const pack_handle* h, const Bufs& bf, const std::vector<int> (&group)[kGroups], Plan& p,
+               bool sizing) {
   const size_t es = h->elt();
   const TileSet saved = p.tile_set;
-  p.tile_set = h->ns_tiles;
   int64_t xo = 0, ao = 0;
   struct Item {
     MuonShape q;
@@ -747,6 +790,17 @@ void plan_muon(const pack_handle* h, const Bufs& bf, const std::vector<int> (&gr
         ao += round_up((int64_t)q.S * q.S, kChunk);
       }
     }
+    // the launches' small tiles: symmetric products (A, B') and X'
+    int64_t n_sym = 0, n_x = 0;
+    for (const Item& it : items) {
+      const int64_t n = (it.q.S + kSmallTile - 1) / kSmallTile;
+      n_sym += n * (n + 1) / 2;
+      n_x += small_tiles(it.q.S, it.q.L);
+    }
+    auto ns_set = [&](int64_t n_small) {
+      return h->ns_tiles >= 0 ? (TileSet)h->ns_tiles : n_small < kMiniMaxTiles && !sizing ? TILES_MINI : TILES_SMALL;
+    };
+    p.tile_set = ns_set(n_sym);
     // A = X X^T, one launch per parity of the X buffer it reads
     for (int par = 0; par < 2; ++par) {
       Launch& ln = p.nsA[par][hf];
@@ -791,6 +845,7 @@ void plan_muon(const pack_handle* h, const Bufs& bf, const std::vector<int> (&gr
       }
       sort_launch(p, ln);
     }
+    p.tile_set = ns_set(n_x);
     // X' = a X + B' X, reading X from buffer par and writing buffer 1 - par
     for (int par = 0; par < 2; ++par) {
       Launch& ln = p.nsX[par][hf];
@@ -828,28 +883,6 @@ void plan_muon(const pack_handle* h, const Bufs& bf, const std::vector<int> (&gr
   p.mtileg[kGroups] = (int)p.mtiles.size();
   p.tile_set = saved;
 }
-
-// Tile set of one forward / data-gradient / weight-gradient launch whose
-// 128 x 128 tiles number n_small: fixed by `forced` (>= 0), else 256 x 128 tiles
-// when there are at least kTallMinTiles small ones (two full rounds of tall
-// tiles at two workgroups per CU), small tiles otherwise.  Measured (ms per
-// step, all small / all tall / chosen): 64 members of widths 64..2048 at batch
-// 2048 (launches of 700..2800 small tiles) 6.29 / 5.76; 64 of widths
-// 256..1024 at batch 1024 (500..840) 1.45 / 1.53 (tall dW alone 1.53);
-// 32 of 256..1024 (~440) 0.63 / 0.67.
-// Weight-gradient launches also need a depth (padded batch) of at least
-// kTallMinDepthDw: their small tiles stream the fused optimizer over the whole
-// staged gradient tile, which the tall tiles do not, and at a 1024-row batch
-// that epilogue outweighs the tall tiles' faster main loop (the embedded first
-// layer's dW: 7.05 ms small, 7.99 ms tall), at 2048 rows it does not
-// (widths 64..2048: 6.29 -> 6.09 ms per step with tall dW tiles alone).
-constexpr int kTallMinTiles = 1024, kTallMinDepthDw = 2048;
-TileSet launch_tiles(const pack_handle* h, int forced, int64_t n_small, int min_depth = 0) {
-  if (forced >= 0) return (TileSet)forced;
-  if (h->prec != Prec::BF16 || h->Bp < min_depth) return TILES_SMALL;
-  return n_small >= kTallMinTiles ? TILES_TALL : TILES_SMALL;
-}
-int64_t small_tiles(int M, int N) { return (int64_t)((M + kSmallTile - 1) / kSmallTile) * ((N + kSmallTile - 1) / kSmallTile); }
 
 // Launch tables over the members of `group` (the active members split into
 // streams; carve() sizes the workspace with every member in one group).
@@ -1101,7 +1134,7 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
   }
   p.headtile0[kGroups] = (int)p.headtiles.size();
   p.member0[kGroups] = (int)p.members.size();
-  if (h->muon) plan_muon(h, bf, group, p);
+  if (h->muon) plan_muon(h, bf, group, p, sizing);
   return p;
 }
 
@@ -1158,8 +1191,13 @@ size_t carve(const pack_handle* h, char* base, Bufs& bf) {
   // The tables are sized by a plan with every member in one launch per layer
   // and small tiles for the main GEMMs: any tile set, and any split of the
   // members, takes at most as many tiles.
+  // Mini tiles are chosen only below kMiniMaxTiles small ones (or forced):
+  // at most 4 times as many, in every launch of every group.
   Plan plan = build_plan(h, bf, all, true);
-  bf.tile_cap = plan.tiles.size();
+  const bool mini_forced = h->tiles_fwd == TILES_MINI || h->tiles_dx == TILES_MINI || h->tiles_dw == TILES_MINI ||
+                           h->ns_tiles == TILES_MINI;
+  bf.tile_cap = mini_forced ? 4 * plan.tiles.size()
+                            : plan.tiles.size() + (size_t)4 * kMiniMaxTiles * kGroups * (4 * (size_t)c.L + 6);
   if (h->muon) {
     bf.mpart = cv.take<double>(plan.mtiles.size());
     bf.minv = cv.take<float>(plan.mmats.size());
@@ -1168,7 +1206,7 @@ size_t carve(const pack_handle* h, char* base, Bufs& bf) {
     bf.d_mtile0 = cv.take<int32_t>(plan.mtile0.size());
   }
   bf.d_descs = cv.take<GemmDesc>(plan.descs.size());
-  bf.d_tiles = cv.take<Tile>(plan.tiles.size());
+  bf.d_tiles = cv.take<Tile>(bf.tile_cap);
   bf.d_coltiles = cv.take<ColTile>(plan.coltiles.size());
   bf.d_headtiles = cv.take<HeadTile>(plan.headtiles.size());
   bf.d_members = cv.take<int32_t>(plan.members.size());
@@ -1365,10 +1403,7 @@ hipError_t muon_step(pack_handle* h, const GemmArgs& base, int g, hipStream_t st
   if (e != hipSuccess) return e;
   static const float kA = 3.4445f, kB = -4.7750f, kC = 2.0315f;
   auto ns_args = [&](const GemmArgs& b0, const Launch& ln, OpKind bk, float alpha, float beta, bool sym) {
-    GemmArgs ga = b0;
-    ga.tiles += ln.tile0;
-    ga.ntiles = ln.ntiles;
-    ga.tile_set = h->ns_tiles;
+    GemmArgs ga = for_launch(b0, ln);
     ga.ns_alpha = alpha;
     ga.ns_beta = beta;
     ga.ns_sym = sym ? 1 : 0;
@@ -1436,12 +1471,13 @@ int pack_init(const pack_config* cfg, pack_handle** out) {
     h->tiles = v == "big" ? TILES_BIG : (v == "tall" ? TILES_TALL : TILES_SMALL);
   }
   if (h->prec == Prec::FP32) h->tiles = TILES_SMALL;
-  auto tile_env = [&](const char* name) {
+  auto tile_env = [&](const char* name, bool main = true) {
     const char* e = getenv(name);
-    if (h->prec == Prec::FP32) return (int)TILES_SMALL;
-    if (!e) e = getenv("TABPACK_GEMM_TILES");
+    if (!e && main) e = getenv("TABPACK_GEMM_TILES");
     if (!e) return -1;
     const std::string v(e);
+    if (v == "mini") return (int)TILES_MINI;
+    if (h->prec == Prec::FP32) return (int)TILES_SMALL;
     return (int)(v == "big" ? TILES_BIG : (v == "tall" ? TILES_TALL : TILES_SMALL));
   };
   h->tiles_fwd = tile_env("TABPACK_TILES_FWD");
@@ -1449,12 +1485,7 @@ int pack_init(const pack_config* cfg, pack_handle** out) {
   h->tiles_dw = tile_env("TABPACK_TILES_DW");
   // Newton-Schulz GEMMs: small tiles measured 3.79 ms per Muon step on the
   // 64-member regression workload, tall 4.03, big 5.53; TABPACK_NS_TILES overrides
-  h->ns_tiles = TILES_SMALL;
-  if (const char* e = getenv("TABPACK_NS_TILES")) {
-    const std::string v(e);
-    h->ns_tiles = v == "big" ? TILES_BIG : (v == "tall" ? TILES_TALL : TILES_SMALL);
-  }
-  if (h->prec == Prec::FP32) h->ns_tiles = TILES_SMALL;
+  h->ns_tiles = tile_env("TABPACK_NS_TILES", false);
   // the embedded first layer's forward: wide tiles in bf16 (each produced E
   // element feeds 256 output columns); TABPACK_EMB_TILES=small overrides
   h->emb_tiles = h->prec == Prec::BF16 ? TILES_WIDE : TILES_SMALL;

@@ -145,6 +145,11 @@ struct Shape<kShapeSmall> {
   static constexpr int STAGE = 32 * (NB * 128 + 32);
 };
 template <>
+struct Shape<kShapeMini> {
+  static constexpr int MB = 1, NB = 1, TM = 64, TN = 64;
+  static constexpr int STAGE = 32 * (NB * 128 + 32);
+};
+template <>
 struct Shape<kShapeTall> {
   static constexpr int MB = 4, NB = 2, TM = 256, TN = 128;
   static constexpr int STAGE = 32 * (NB * 128 + 32);
@@ -194,10 +199,19 @@ __device__ __forceinline__ int kmaj16_off(int row, int c) {
   return row * (32 * KS) + ((c ^ kmaj_f<KS>(row)) << 4);
 }
 
-// rows-contiguous bf16 layout (R rows): byte offset of element `col` of depth row k
+// rows-contiguous bf16 layout (R rows): the 32-byte chunk c of depth row k at
+// chunk position c ^ rmaj_x(k).  The four depth rows a transposing read covers
+// then fall on disjoint banks: rows of 256 bytes or more share their banks and
+// take four positions, the 128-byte rows of 64-row tiles alternate between the
+// two halves of the banks and take two.
+template <int R>
+__device__ __forceinline__ int rmaj_x(int k) {
+  return R >= 128 ? (k & 3) << 1 : ((k >> 1) & 1) << 1;
+}
+// byte offset of element `col` of depth row k
 template <int R>
 __device__ __forceinline__ int rmaj_off(int k, int col) {
-  return k * (R * 2) + ((((col >> 4) ^ ((k & 3) << 1))) << 5) + ((col & 15) << 1);
+  return k * (R * 2) + (((col >> 4) ^ rmaj_x<R>(k)) << 5) + ((col & 15) << 1);
 }
 
 __device__ __forceinline__ float to_float(__bf16 x) { return (float)x; }
@@ -304,7 +318,7 @@ template <int R>
 struct LoadRmajF32 {
   static constexpr int RB = R / 4;              // row blocks
   static constexpr int NBLK = RB * KV;          // blocks per tile
-  static constexpr int PER = NBLK / NT;
+  static constexpr int PER = NBLK < NT ? 1 : NBLK / NT;  // fewer blocks than threads: the others load nothing
   u32x4 reg[PER][4];
   __amdgpu_buffer_rsrc_t rsrc;
   uint32_t off[PER];
@@ -316,7 +330,7 @@ struct LoadRmajF32 {
     for (int p = 0; p < PER; ++p) {
       const int b = tid + p * NT;
       const int rb = b % RB, kb = b / RB;
-      off[p] = row0 + rb * 4 < rbound ? (uint32_t)(kb * 4 * ldb + (int64_t)(row0 + rb * 4) * 4) : kOob;
+      off[p] = b < NBLK && row0 + rb * 4 < rbound ? (uint32_t)(kb * 4 * ldb + (int64_t)(row0 + rb * 4) * 4) : kOob;
     }
   }
   __device__ void load(int k0, int kd, int tid) {
@@ -334,6 +348,7 @@ struct LoadRmajF32 {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
       const int b = tid + p * NT;
+      if (b >= NBLK) break;
       const int rb = b % RB, kb = b / RB;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -435,7 +450,7 @@ struct DmaRmaj {
     for (int p = 0; p < PER; ++p) {
       const int pos = (wave * PER + p) * 1024 + lane * 16;
       const int k = pos / RBYTES, b = pos % RBYTES;
-      const int chunk = (b >> 5) ^ ((k & 3) << 1);
+      const int chunk = (b >> 5) ^ rmaj_x<R>(k);
       const int col = chunk * 16 + ((b >> 4) & 1) * 8;
       krow[p] = k;
       const int64_t dep = map_ ? 0 : k * (int64_t)ldb;
@@ -1123,58 +1138,66 @@ __device__ __forceinline__ void stage_flush_adamw(const GemmArgs& a, const GemmD
   }
 }
 
-// Weight-gradient tile of the small shape with the optimizer fused, done by
-// the whole workgroup: the 128 x 128 fp32 gradient tile is staged in LDS (it
-// fills the 64 KB the operand stages used), then the 256 threads stream the
-// optimizer over it in row-contiguous 16-byte vectors, 16 per thread, with the
-// optimizer state of kAdamAhead vectors in flight ahead of the one being
-// updated, so the update of one vector never waits for the stores of the one
-// before.  LDS layout: element (r, c) at r * 512 + 16 ((c / 4) ^ 8 ((r / 4) & 1))
-// + 4 (c % 4): the two half-waves of an accumulator write (rows 4 apart) fall
-// on disjoint banks, and each 16-byte vector stays contiguous.
+// Weight-gradient tile of the small or mini shape with the optimizer fused,
+// done by the whole workgroup: the TM x TN fp32 gradient tile is staged in LDS
+// (128 x 128 fills the 64 KB the operand stages used), then the 256 threads
+// stream the optimizer over it in row-contiguous 16-byte vectors, 16 per thread
+// (mini: 4), with the optimizer state of AHEAD vectors in flight ahead of the
+// one being updated, so the update of one vector never waits for the stores of
+// the one before.  LDS layout: element (r, c) at r * 4 TN + 16 ((c / 4) ^
+// 8 ((r / 4) & 1)) + 4 (c % 4): the two half-waves of an accumulator write
+// (rows 4 apart) fall on disjoint banks, and each 16-byte vector stays
+// contiguous.
 // Vectors in flight: 8 (210 VGPRs) measured 0.8% faster per training step than
 // 4; 16 exceeds the register budget of two workgroups per CU and spills.
 #ifndef TABPACK_ADAM_AHEAD
 #define TABPACK_ADAM_AHEAD 8
 #endif
 constexpr int kAdamAhead = TABPACK_ADAM_AHEAD;
+template <int TN>
 __device__ __forceinline__ int dwt_off(int r, int c) {
-  return r * 512 + ((((c >> 2) ^ (((r >> 2) & 1) << 3))) << 4) + ((c & 3) << 2);
+  return r * (4 * TN) + ((((c >> 2) ^ (((r >> 2) & 1) << 3))) << 4) + ((c & 3) << 2);
 }
 
 // rows of the gradient tile staged per pass: the whole tile when the small
 // kernel's LDS holds it, else halves (every kernel has at least that much LDS)
 constexpr int kDwPassRows = kLdsSmallBf16 >= 128 * 512 ? 128 : 64;
 
-__device__ __forceinline__ void dw_adamw_small(const GemmArgs& a, const GemmDesc& d, const Tile& t,
-                                               f32x16 (&acc)[2][2], int wm, int wn, int lane, int tid, char* lds0) {
-  constexpr int NPASS = 128 / kDwPassRows;
-  constexpr int NV = kDwPassRows / 8;  // vectors per thread per pass
+template <int SH>
+__device__ __forceinline__ void dw_adamw_tile(const GemmArgs& a, const GemmDesc& d, const Tile& t,
+                                              f32x16 (&acc)[Shape<SH>::MB][Shape<SH>::NB], int wm, int wn, int lane,
+                                              int tid, char* lds0) {
+  constexpr int MB = Shape<SH>::MB, NB = Shape<SH>::NB, TM = Shape<SH>::TM, TN = Shape<SH>::TN;
+  constexpr int PROWS = TM < kDwPassRows ? TM : kDwPassRows;
+  constexpr int NPASS = TM / PROWS;
+  constexpr int VPR = TN / 4, RPV = NT / VPR;  // vectors per row, rows per vector of all threads
+  constexpr int NV = PROWS / RPV;              // vectors per thread per pass
+  constexpr int AHEAD = NV < kAdamAhead ? NV : kAdamAhead;
   const int hv = lane >> 5;
   const AdamConst ac = a.adam;
   const float decay = 1.0f - d.lr * d.wd;
   const float step = d.lr / ac.bc1;
   // the rows that hold weights (the padding rows stay zero: not loaded, not written)
-  const int mrows = min(d.opt_rows - t.m0, 128), ncols = min(d.N - t.n0, 128);
-  // vector u of this thread in a pass: row 8 u + tid / 32 of the pass, columns 4 (tid % 32) .. +3
-  const int r0 = tid >> 5, c = (tid & 31) * 4;
+  const int mrows = min(d.opt_rows - t.m0, TM), ncols = min(d.N - t.n0, TN);
+  // vector u of this thread in a pass: row RPV u + tid / VPR of the pass, columns 4 (tid % VPR) .. +3
+  const int r0 = tid / VPR, c = (tid % VPR) * 4;
   const bool colok = c < ncols;
-  const int64_t estep = 8 * d.ldc;
+  const int64_t estep = RPV * d.ldc;
   float* th_p = a.theta + d.poff;
   float* m_p = a.am + d.poff;
   float* v_p = a.av + d.poff;
-  f32x4 th[kAdamAhead], m[kAdamAhead], vv[kAdamAhead];
+  f32x4 th[AHEAD], m[AHEAD], vv[AHEAD];
 #pragma unroll 1
   for (int pass = 0; pass < NPASS; ++pass) {
-    const int prow0 = pass * kDwPassRows;  // first tile row of this pass
+    const int prow0 = pass * PROWS;  // first tile row of this pass
     const int64_t e0 = (int64_t)(t.m0 + prow0 + r0) * d.ldc + t.n0 + c;  // element offset of vector 0
-    auto ok = [&](int u) { return colok && prow0 + 8 * u + r0 < mrows; };
+    auto ok = [&](int u) { return colok && prow0 + RPV * u + r0 < mrows; };
     auto load = [&](int u) {
       const int64_t e = e0 + u * estep;
       if (ok(u)) {
-        th[u % kAdamAhead] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(th_p + e));
-        m[u % kAdamAhead] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(m_p + e));
-        vv[u % kAdamAhead] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(v_p + e));
+        th[u % AHEAD] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(th_p + e));
+        m[u % AHEAD] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(m_p + e));
+        vv[u % AHEAD] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(v_p + e));
       }
     };
     if (pass > 0) {
@@ -1184,27 +1207,27 @@ __device__ __forceinline__ void dw_adamw_small(const GemmArgs& a, const GemmDesc
     // the first vectors' optimizer state is requested before the gradient
     // tile is staged, so its latency overlaps the staging and the barrier
 #pragma unroll
-    for (int u = 0; u < kAdamAhead; ++u) load(u);
+    for (int u = 0; u < AHEAD; ++u) load(u);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int row = wm * 64 + 32 * i + 8 * (r >> 2) + 4 * hv + (r & 3) - prow0;
-          const int col = wn * 64 + 32 * j + (lane & 31);
-          if (row >= 0 && row < kDwPassRows) *reinterpret_cast<float*>(lds0 + dwt_off(row, col)) = acc[i][j][r];
+          const int row = wm * MB * 32 + 32 * i + 8 * (r >> 2) + 4 * hv + (r & 3) - prow0;
+          const int col = wn * NB * 32 + 32 * j + (lane & 31);
+          if (row >= 0 && row < PROWS) *reinterpret_cast<float*>(lds0 + dwt_off<TN>(row, col)) = acc[i][j][r];
         }
     wait_vm<63, true>();  // this wave's LDS writes are done (the state loads may still be in flight)
     bar();
 #pragma unroll
     for (int u = 0; u < NV; ++u) {
-      const int b = u % kAdamAhead;
+      const int b = u % AHEAD;
       const int64_t e = e0 + u * estep;
       const bool in = ok(u);
-      f32x4 g = *reinterpret_cast<const f32x4*>(lds0 + dwt_off(8 * u + r0, c));
+      f32x4 g = *reinterpret_cast<const f32x4*>(lds0 + dwt_off<TN>(RPV * u + r0, c));
       f32x4 t_ = th[b], m_ = m[b], v_ = vv[b];
-      if (u + kAdamAhead < NV) load(u + kAdamAhead);
+      if (u + AHEAD < NV) load(u + AHEAD);
       if (in) {
         if (a.keep_grad) *glob(reinterpret_cast<f32x4*>(static_cast<float*>(d.C) + e)) = g;
         adamw_vec4(t_, g, m_, v_, decay, step, ac);
@@ -1262,7 +1285,8 @@ __device__ __forceinline__ void epi_prefetch(const GemmDesc& d, const Tile& t, i
 template <typename T, int EPI, int SH>
 __device__ __forceinline__ void epilogue(const GemmArgs& a, const GemmDesc& d, const Tile& t,
                                          f32x16 (&acc)[Shape<SH>::MB][Shape<SH>::NB], int wm, int wn, int lane,
-                                         int mv, int nv, char* stage, const EpiPre<SH>& pre) {
+                                         int mv, int nv, char* stage, const EpiPre<SH>& pre,
+                                         char* xlds = nullptr) {
   constexpr int MB = Shape<SH>::MB, NB = Shape<SH>::NB;
   const int hv = lane >> 5;
   const int col0 = t.n0 + wn * NB * 32;  // the wave's first column
@@ -1355,7 +1379,29 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const GemmDesc& d, c
         stage_flush<T, NB>(stage, C, d.ldc, rb + S::ROWS * p, col0, d.M, d.N, lane);
         wave_sync_lds();
       }
-      if (i & 1) {
+      if constexpr (MB == 1) {
+        // A 64-row block is held by two waves of 32 rows: the upper one goes on
+        // from the lower one's sums, so the order of the additions is that of a
+        // wave with all 64 rows.
+        float* xch = reinterpret_cast<float*>(xlds) + (wn * 64 + lane) * NB;
+        if (wm == 0) {
+#pragma unroll
+          for (int j = 0; j < NB; ++j) xch[j] = cs[j];
+        }
+        __syncthreads();
+        if (wm == 1) {
+#pragma unroll
+          for (int j = 0; j < NB; ++j) {
+            float c = xch[j];
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              c += ((mw[j] >> (8 * (r >> 2) + 4 * hv + (r & 3))) & 1) ? acc[i][j][r] * d.drop_s : 0.0f;
+            c += __shfl_xor(c, 32, 64);
+            const int64_t prow = (int64_t)((row0 - 32) / kPartRows) * d.N;
+            if (hv == 0 && colin[j] && row0 - 32 < d.M) *glob(d.colpart + prow + colL + 32 * j) = c;
+          }
+        }
+      } else if (i & 1) {
         const int hb = row0 + 32 * (i - 1);  // first row of this 64-row half
         const int64_t prow = (int64_t)(hb / kPartRows) * d.N;
 #pragma unroll
@@ -1640,16 +1686,17 @@ __device__ __forceinline__ void run_tile(const GemmArgs& a, const GemmDesc& d, c
       __syncthreads();
     }
   }
-  if constexpr (EPI == EPI_DW && SH == kShapeSmall && sizeof(T) == 2) {
+  if constexpr (EPI == EPI_DW && (SH == kShapeMini || (SH == kShapeSmall && sizeof(T) == 2))) {
     if (a.theta) {  // uniform: the whole workgroup takes the staged-tile path
-      dw_adamw_small(a, d, t, acc, wm, wn, lane, tid, lds0);
+      dw_adamw_tile<SH>(a, d, t, acc, wm, wn, lane, tid, lds0);
       return;
     }
   }
   if constexpr (EPI == EPI_DE)
     epilogue_de<T, SH>(a, d, t, acc, wm, wn, lane, tid, lds0);
   else
-    epilogue<T, EPI, SH>(a, d, t, acc, wm, wn, lane, mv, nv, lds0 + wave * Shape<SH>::STAGE, pre);
+    epilogue<T, EPI, SH>(a, d, t, acc, wm, wn, lane, mv, nv, lds0 + wave * Shape<SH>::STAGE, pre,
+                         lds0 + 4 * Shape<SH>::STAGE);
 }
 
 // Output tiles of the embedded first layer (small tiles): the forward, whose A
@@ -1831,7 +1878,7 @@ __device__ __forceinline__ void run_tile_emb(const GemmArgs& a, const GemmDesc& 
   }
   if constexpr (EPI == EPI_DW && sizeof(T) == 2) {
     if (a.theta) {  // uniform: the whole workgroup takes the staged-tile path
-      dw_adamw_small(a, d, t, acc, wm, wn, lane, tid, lds0);
+      dw_adamw_tile<SH>(a, d, t, acc, wm, wn, lane, tid, lds0);
       return;
     }
   }
@@ -1915,10 +1962,34 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   run_tile<__bf16, AK, BK_, EPI, kShapeSmall, kSmallKs, kSmallNs>(a, d, t, smem, tid, wave, smem + kLdsTall);
 }
 
+// Launches of mini tiles only (64 x 64, 4 waves of 32 x 32): four times the
+// workgroups of the small tiles, for launches that would leave CUs idle.  bf16:
+// four 16 KB stages of 64-deep steps, three of them in flight; fp32: two
+// register-staged 32-deep stages.
+constexpr int kMiniNs = 4;
+constexpr int kLdsMiniBf16 = kMiniNs * 2 * 64 * 128, kLdsMiniF32 = 2 * 2 * 64 * ROW;
+static_assert(4 * Shape<kShapeMini>::STAGE + 512 <= kLdsMiniF32, "epilogue staging and the bias-sum exchange");
+static_assert(64 * 64 * 4 <= kLdsMiniF32, "the staged weight-gradient tile");
+template <typename T, int AK, int BK_, int EPI>
+__global__ __launch_bounds__(NT, 2) void gemm_kernel_mini(GemmArgs a) {
+  constexpr int kOps = sizeof(T) == 2 ? kLdsMiniBf16 : kLdsMiniF32;
+  constexpr int kMap = sizeof(T) == 2 ? XMapBytes<T, EPI> : 0;
+  __shared__ __attribute__((aligned(16))) char smem[kOps + kMap];
+  const Tile t = a.tiles[blockIdx.x];
+  const GemmDesc d = a.descs[t.desc];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  run_tile<T, AK, BK_, EPI, kShapeMini, 4, sizeof(T) == 2 ? kMiniNs : 2>(a, d, t, smem, tid, wave, smem + kOps);
+}
+
 template <typename T, int AK, int BK_, int EPI>
 hipError_t launch_t(const GemmArgs& args, hipStream_t s) {
   if (args.ntiles <= 0) return hipSuccess;
-  if constexpr (sizeof(T) == 4) {  // fp32 operands: small tiles only
+  if (args.tile_set == TILES_MINI) {
+    hipLaunchKernelGGL((gemm_kernel_mini<T, AK, BK_, EPI>), dim3(args.ntiles), dim3(NT), 0, s, args);
+    return hipGetLastError();
+  }
+  if constexpr (sizeof(T) == 4) {  // fp32 operands: small (or mini) tiles only
     if (args.tile_set != TILES_SMALL) return hipErrorInvalidValue;
     hipLaunchKernelGGL((gemm_kernel_small<T, AK, BK_, EPI>), dim3(args.ntiles), dim3(NT), 0, s, args);
   } else {
