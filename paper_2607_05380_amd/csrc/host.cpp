@@ -41,6 +41,7 @@ constexpr uint32_t kTagHparam = 1, kTagInit = 2;
 constexpr int kGroups = 4;  // at most this many member groups run their GEMM chains concurrently
 
 int64_t round_up(int64_t x, int64_t q) { return (x + q - 1) / q * q; }
+int64_t small_tiles(int M, int N) { return (int64_t)((M + kSmallTile - 1) / kSmallTile) * ((N + kSmallTile - 1) / kSmallTile); }
 
 struct Key {
   uint32_t k0, k1;
@@ -106,15 +107,13 @@ struct Bufs {
   float4* etab = nullptr;  // embeddings: the members' column tables (MemberDev::e_tab), rebuilt every step
   float* dE = nullptr; // embeddings: at each member's E offset / 16, the dE GEMM's sums [Bp / 64][4][p_in] (fp32)
   char* H = nullptr;   // L activation buffers H_1..H_L
-  char* dz = nullptr;  // 2 ping-pong buffers for dZ_l
+  char* dz = nullptr;  // ndz() buffers for dZ_1..dZ_L
   float* colpart = nullptr;  // bias-gradient partials of the dX epilogues, (L - 1) x A / kPartRows floats
   uint32_t* mask = nullptr;  // ReLU/dropout keep bits of H_1..H_L, L * A / 32 words
   uint32_t* keepw = nullptr; // dropout keep words, 2 copies of L * A / 32 words
   char* zeros = nullptr;     // 256 zero bytes: GEMM loads of out-of-range elements read them
   float *dY = nullptr, *rowloss = nullptr;
   MemberDev* d_mem = nullptr;
-  uint32_t* d_chunks = nullptr;
-  uint32_t* d_aux = nullptr;
   int64_t* d_bias_off = nullptr;  // [L][K] offsets of b_l
   GemmDesc* d_descs = nullptr;
   Tile* d_tiles = nullptr;
@@ -134,7 +133,6 @@ struct Bufs {
   MuonTile* d_mtiles = nullptr;
   int32_t* d_mtile0 = nullptr;
   float* headpart = nullptr;  // head backward partials, (Bp / RB) * (d_out + 1) * A / Bp floats
-  int32_t* idx_ok = nullptr;  // the step's batch indices, entries outside [0, N) replaced by 0 [K * B]
   uint32_t* status = nullptr; // asynchronous error flags (pack_status)
 };
 
@@ -154,13 +152,10 @@ struct pack_handle {
   int64_t P = 0;     // packed parameter count (multiple of kChunk)
   int64_t A = 0;     // elements of one activation buffer (all members)
   std::vector<float> theta_host;  // host copy of the parameters, packed layout
-  std::vector<uint32_t> chunk_tab;
-  std::vector<uint32_t> aux_chunks;  // chunks the separate AdamW pass updates (biases, head)
   // Members in the pack's launches (Section 3.6: a base model that stops
   // improving is removed from the pack); inactive members keep their state.
   std::vector<uint8_t> active;
   std::vector<int32_t> active_ids;   // increasing
-  int64_t n_aux_active = 0;          // aux chunks of active members (uploaded first in d_aux)
   bool muon = false;                 // hidden weights on Muon (pack_config.optimizer)
   bool emb = false;                  // periodic feature embeddings (pack_config.emb_lo > 0)
   Launch de[kGroups]{};
@@ -181,6 +176,17 @@ struct pack_handle {
   // group's GEMM chain runs on its own stream (group 0 on the caller's), which
   // measured faster than one launch over all members.
   int ngroups = 1;
+  // Small packs (small_pack) run the whole step on the caller's stream, with
+  // if it can with one weight-gradient launch for all layers: such a step is
+  // bound by its launches and events, not by what runs side by side.
+  bool one_stream = false;
+  Launch dw_all{};                   // one_stream and small: the weight gradients of all layers (embedded packs: 2..L)
+  // a small pack with all its members active: the training head in one kernel,
+  // and a gradient buffer for every layer (decided once, whoever is active)
+  bool small = false;
+  // dZ_l buffers: one a layer, so that all weight gradients can follow the dX
+  // chain, or two in turn
+  int ndz() const { return small ? cfg.L : 2; }
   std::vector<int> group[kGroups];
   int sumtile0[kGroups + 1] = {};    // gradient-sum work items of group g: [sumtile0[g], sumtile0[g + 1])
   int headtile0[kGroups + 1] = {};   // head-backward tiles of group g
@@ -218,7 +224,6 @@ struct pack_handle {
   void* Hl(int l) const { return b.H + (size_t)(l - 1) * A * elt(); }  // H_l, l = 1..L
   int64_t H0e = 0;  // elements of the H_0 / E buffer (every member's first-layer input block)
   int64_t Etab = 0; // entries of the embedding column tables (p_in per embedded member)
-  void* dzb(int l) const { return b.dz + (size_t)(l & 1) * A * elt(); } // buffer holding dZ_l
 };
 
 namespace {
@@ -304,8 +309,7 @@ void sample_members(pack_handle* h) {
 
 // Packed layout: per member, tensors W_1 [dp, Pin], b_1 [dp], W_l [dp, dp],
 // b_l [dp], W_out [d_out, dp], b_out [d_out]; every tensor starts on a
-// kChunk-element boundary so an AdamW chunk never mixes members or
-// weights with biases.  Padding rows/columns hold exact zeros forever: their
+// kChunk-element boundary.  Padding rows/columns hold exact zeros forever: their
 // inputs or output gradients are zero, so their gradients and AdamW moments
 // stay zero.
 int emb_dp(int d_emb) { return (d_emb + 7) & ~7; }
@@ -313,8 +317,6 @@ int emb_dp(int d_emb) { return (d_emb + 7) & ~7; }
 void plan_layout(pack_handle* h) {
   const pack_config& c = h->cfg;
   int64_t off = 0, aoff = 0;
-  h->chunk_tab.clear();
-  h->aux_chunks.clear();
   int64_t h0 = 0, tab = 0;
   for (int k = 0; k < c.K; ++k) {
     Member& m = h->mem[k];
@@ -332,12 +334,7 @@ void plan_layout(pack_handle* h) {
                             (int64_t)c.d_in * m.d_emb, (int64_t)c.d_in * m.d_emb};
       for (int t = 0; t < 4; ++t) {
         m.eoff[t] = off;
-        const int64_t nc = round_up(n[t], kChunk) / kChunk;
-        for (int64_t i = 0; i < nc; ++i) {
-          h->aux_chunks.push_back((uint32_t)h->chunk_tab.size());
-          h->chunk_tab.push_back((uint32_t)k);
-        }
-        off += nc * kChunk;
+        off += round_up(n[t], kChunk);
       }
     }
     m.toff.assign(2 * m.depth + 2, 0);
@@ -347,15 +344,7 @@ void plan_layout(pack_handle* h) {
       for (int part = 0; part < 2; ++part) {
         const int64_t n = part == 0 ? rows * cols : rows;
         m.toff[2 * l + part] = off;
-        const int64_t nc = round_up(n, kChunk) / kChunk;
-        const uint32_t flag = (part == 1 && !c.decay_bias) ? 0x80000000u : 0u;
-        // hidden-layer weights are updated inside their weight-gradient GEMM
-        const bool fused = part == 0 && l < m.depth;
-        for (int64_t i = 0; i < nc; ++i) {
-          if (!fused) h->aux_chunks.push_back((uint32_t)h->chunk_tab.size());
-          h->chunk_tab.push_back((uint32_t)k | flag);
-        }
-        off += nc * kChunk;
+        off += round_up(n, kChunk);
       }
     }
     m.act_off = aoff;
@@ -469,7 +458,7 @@ struct Plan {
   std::vector<ColTile> coltiles;
   std::vector<HeadTile> headtiles;
   std::vector<Launch> fwd[2][kGroups], dx[kGroups], dw[kGroups];
-  Launch fwd1_eval{};
+  Launch fwd1_eval{}, dw_all{};
   int sumtile0[kGroups + 1] = {};  // see build_plan
   int headtile0[kGroups + 1] = {};
   std::vector<int32_t> members;  // member ids in group order
@@ -603,6 +592,22 @@ void sort_launch(Plan& p, const Launch& ln) {
   }
 }
 
+// Whether the given members make a small pack: their activations are at most
+// kOneStreamTiles 128 x 128 tiles a layer (two for each CU).  Its step is one
+// chain of 5 + 2 L launches or less (bound data: 2 + 2 L) instead of up to 30
+// launches and as many event operations in three streams, which took the host
+// about 150 us.  Measured, two groups / one stream: 4 fp32 members of widths
+// 64..256 at batch 256 (16 tiles) 200 / 52 us; 16 bf16 members of 128..512 at
+// batch 512 (~180) 200 / 107 us; 41 of 159..502 at batch 372 (490) 361 / 286
+// us; 32 of 256..1024 at batch 1024 (~1,300) 639 / 641 us, where side by side
+// the groups' weight-update traffic and matrix products overlap.
+constexpr int64_t kOneStreamTiles = 512;
+bool small_pack(const pack_handle* h, const std::vector<int>& ids) {
+  int64_t n = 0;
+  for (int k : ids) n += small_tiles(h->Bp, h->mem[k].dp);
+  return n <= kOneStreamTiles;
+}
+
 // Members into ngroups groups of about equal GEMM work (longest first, each
 // to the lightest group).  Default: 2 groups, 3 with Muon, whose per-group
 // Newton-Schulz chains overlap better in three (regression_large: 1.398
@@ -610,9 +615,11 @@ void sort_launch(Plan& p, const Launch& ln) {
 // 4 groups exceed the four hardware queues).  TABPACK_STREAMS (1 .. 4)
 // overrides it.
 void split_members(pack_handle* h) {
-  int ng = h->muon ? 3 : 2;
+  h->one_stream = small_pack(h, h->active_ids);
+  int ng = h->one_stream ? 1 : h->muon ? 3 : 2;
   if (const char* e = getenv("TABPACK_STREAMS")) ng = std::max(1, std::min(kGroups, atoi(e)));
   h->ngroups = std::max(1, std::min(ng, (int)h->active_ids.size()));
+  h->one_stream = h->one_stream && h->ngroups == 1;
   for (auto& v : h->group) v.clear();
   std::vector<std::pair<double, int>> cost;
   for (int k : h->active_ids) {
@@ -637,7 +644,7 @@ int max_pin(const pack_handle* h, const std::vector<int>& ids) {
 }
 
 // Rows per head-backward block: up to 256, dividing Bp.
-int head_rows(const pack_handle* h) { return h->Bp % 256 == 0 ? 256 : h->Bp; }
+int head_rows(const pack_handle* h) { return h->small ? kHeadRows : h->Bp % 256 == 0 ? 256 : h->Bp; }
 
 // Shape of the Newton-Schulz iterate of member m's hidden weight l (1-based):
 // padded [R x Cp] storage; X is [S x L], U or U^T (tall: true rows > true columns).
@@ -747,7 +754,6 @@ TileSet launch_tiles(const pack_handle* h, int forced, int64_t n_small, int min_
   if (h->prec != Prec::BF16 || h->Bp < min_depth) return TILES_SMALL;
   return n_small >= kTallMinTiles ? TILES_TALL : TILES_SMALL;
 }
-int64_t small_tiles(int M, int N) { return (int64_t)((M + kSmallTile - 1) / kSmallTile) * ((N + kSmallTile - 1) / kSmallTile); }
 
 void plan_muon(const pack_handle* h, const Bufs& bf, const std::vector<int> (&group)[kGroups], Plan& p,
                bool sizing) {
@@ -898,7 +904,7 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
   const size_t es = h->elt();
   const void* wsrc = h->prec == Prec::BF16 ? (const void*)bf.shadow : (const void*)bf.theta;
   auto Hl = [&](int l) -> void* { return bf.H + (size_t)(l - 1) * h->A * es; };
-  auto dzb = [&](int l) -> void* { return bf.dz + (size_t)(l & 1) * h->A * es; };
+  auto dzb = [&](int l) -> void* { return bf.dz + (size_t)((l - 1) % h->ndz()) * h->A * es; };
   auto wptr = [&](int k, int l) -> const void* {  // weight of hidden layer l (1-based) for GEMM reads
     return (const char*)wsrc + (size_t)h->mem[k].toff[2 * (l - 1)] * es;
   };
@@ -945,7 +951,6 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
       if (l == 1 && h->stream_rows && m.d_emb == 0 && !sizing) {  // rows straight from the data copy
         d.A = h->xb;
         d.lda = h->Pin;
-        d.xrows = bf.idx_ok + (size_t)k * c.B;
         d.xrows_n = c.B;
         d.xsrc_rows = h->data_N;
       }
@@ -977,7 +982,7 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
         const int k = group[hf][i];
         GemmDesc d = p.descs[p.fwd[0][hf][0].desc0 + i];
         if (h->mem[k].d_emb == 0) d.A = h0(0);  // embedded members read their own E block
-        d.xrows = nullptr;                      // evaluation reads the gathered validation rows
+        d.xrows_n = 0;                          // evaluation reads the gathered validation rows
         add_tiles(p, f, (int)p.descs.size(), h->Bp, h->mem[k].dp, d.Kd);
         p.descs.push_back(d);
       }
@@ -1018,12 +1023,10 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
       if (l == 1 && h->stream_rows && m.d_emb == 0 && !sizing) {  // rows straight from the data copy
         d.B = h->xb;
         d.ldb = h->Pin;
-        d.xrows = bf.idx_ok + (size_t)k * c.B;
         d.xrows_n = c.B;
         d.xsrc_rows = h->data_N;
       }
       if (l == 1 && m.d_emb) {  // E produced in the GEMM from the batch rows' data rows
-        d.xrows = bf.idx_ok + (size_t)k * c.B;
         d.xrows_n = c.B;
       }
       add_tiles(p, w, (int)p.descs.size(), d.M, d.N, d.Kd);
@@ -1077,20 +1080,45 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     }
     p.dx[hf].push_back(x);
   }
+  if (h->one_stream && h->small && !sizing) {
+    // one launch for the weight gradients of all layers, from the same descriptors
+    Launch& w = p.dw_all;
+    w = Launch{0, 0, (int)p.tiles.size(), 0, 0.0, 0.0};
+    int64_t nsm = 0;
+    for (int l = h->emb ? 2 : 1; l <= c.L; ++l)
+      for (int i = 0; i < p.dw[0][l - 1].ndesc; ++i) {
+        const GemmDesc& d = p.descs[p.dw[0][l - 1].desc0 + i];
+        nsm += small_tiles(d.M, d.N);
+      }
+    p.tile_set = choose(h->tiles_dw, nsm, kTallMinDepthDw);
+    for (int l = h->emb ? 2 : 1; l <= c.L; ++l) {
+      const Launch& ln = p.dw[0][l - 1];
+      for (int i = 0; i < ln.ndesc; ++i) {
+        const GemmDesc& d = p.descs[ln.desc0 + i];
+        add_tiles(p, w, ln.desc0 + i, d.M, d.N, d.Kd);
+      }
+      w.flops += ln.flops;
+      w.bytes += ln.bytes;
+    }
+    w.ts = p.tile_set;
+    sort_launch(p, w);
+  }
   // gradient-sum work items of group g (one launch after the group's last
   // backward launch): coltiles[sumtile0[g] .. sumtile0[g + 1]) -- the bias
   // columns of every dX launch (layer l >= 2: b_{l-1} of the members with at
-  // least l hidden blocks), then every member's head columns, then one loss
-  // item per member
+  // least l hidden blocks), then every member's head columns (per output), then
+  // its head biases and loss
   for (int hf = 0; hf < kGroups; ++hf) {
     p.sumtile0[hf] = (int)p.coltiles.size();
     for (int l = 2; l <= c.L; ++l)
       for (int k : group[hf])
         if (h->mem[k].depth >= l)
-          for (int c0 = 0; c0 < h->mem[k].dp; c0 += 64) p.coltiles.push_back(ColTile{k, c0, l - 2});
+          for (int c0 = 0; c0 < h->mem[k].dp; c0 += 64) p.coltiles.push_back(ColTile{k, c0, l - 2, 0});
     for (int k : group[hf])
-      for (int c0 = 0; c0 < h->mem[k].dp; c0 += 64) p.coltiles.push_back(ColTile{k, c0, kSumHead});
-    for (int k : group[hf]) p.coltiles.push_back(ColTile{k, 0, kSumLoss});
+      for (int o = 0; o <= c.d_out; ++o)
+        for (int c0 = 0; c0 < h->mem[k].dp; c0 += 64) p.coltiles.push_back(ColTile{k, c0, kSumHead, o});
+    for (int k : group[hf])
+      for (int o = 0; o <= c.d_out; ++o) p.coltiles.push_back(ColTile{k, 0, kSumLoss, o});
   }
   p.sumtile0[kGroups] = (int)p.coltiles.size();
   const TileSet saved_ts = p.tile_set;
@@ -1167,7 +1195,7 @@ size_t carve(const pack_handle* h, char* base, Bufs& bf) {
   bf.dE = h->emb ? cv.take<float>((size_t)h->H0e / 16) : nullptr;
   bf.etab = h->emb ? cv.take<float4>((size_t)h->Etab) : nullptr;
   bf.H = cv.take<char>((size_t)c.L * h->A * h->elt());
-  bf.dz = cv.take<char>((size_t)2 * h->A * h->elt());
+  bf.dz = cv.take<char>((size_t)h->ndz() * h->A * h->elt());
   bf.colpart = cv.take<float>((size_t)std::max(1, c.L - 1) * (h->A / kPartRows));
   bf.mask = cv.take<uint32_t>((size_t)c.L * (h->A / 32));
   bf.keepw = cv.take<uint32_t>((size_t)2 * c.L * (h->A / 32));
@@ -1175,8 +1203,6 @@ size_t carve(const pack_handle* h, char* base, Bufs& bf) {
   bf.dY = cv.take<float>((size_t)c.K * h->Bp * c.d_out);
   bf.rowloss = cv.take<float>((size_t)c.K * h->Bp);
   bf.d_mem = cv.take<MemberDev>(c.K);
-  bf.d_chunks = cv.take<uint32_t>(h->chunk_tab.size());
-  bf.d_aux = cv.take<uint32_t>(h->aux_chunks.size());
   bf.d_bias_off = cv.take<int64_t>((size_t)c.L * c.K);
   std::vector<int> all[kGroups];
   for (int k = 0; k < c.K; ++k) all[0].push_back(k);
@@ -1197,7 +1223,7 @@ size_t carve(const pack_handle* h, char* base, Bufs& bf) {
   const bool mini_forced = h->tiles_fwd == TILES_MINI || h->tiles_dx == TILES_MINI || h->tiles_dw == TILES_MINI ||
                            h->ns_tiles == TILES_MINI;
   bf.tile_cap = mini_forced ? 4 * plan.tiles.size()
-                            : plan.tiles.size() + (size_t)4 * kMiniMaxTiles * kGroups * (4 * (size_t)c.L + 6);
+                            : plan.tiles.size() + (size_t)4 * kMiniMaxTiles * kGroups * (4 * (size_t)c.L + 7);
   if (h->muon) {
     bf.mpart = cv.take<double>(plan.mtiles.size());
     bf.minv = cv.take<float>(plan.mmats.size());
@@ -1212,7 +1238,6 @@ size_t carve(const pack_handle* h, char* base, Bufs& bf) {
   bf.d_members = cv.take<int32_t>(plan.members.size());
   bf.d_active = cv.take<int32_t>(c.K);
   bf.headpart = cv.take<float>((size_t)(h->Bp / head_rows(h)) * (c.d_out + 1) * (h->A / h->Bp));
-  bf.idx_ok = cv.take<int32_t>((size_t)c.K * c.B);
   bf.status = cv.take<uint32_t>(64);
   return (size_t)round_up((int64_t)cv.off, 256);
 }
@@ -1309,9 +1334,8 @@ void set_active_ids(pack_handle* h) {
     if (h->active[k]) h->active_ids.push_back(k);
 }
 
-// Builds the launch tables of the active members, uploads them (and the AdamW
-// list of the active members' biases and heads) into the bound workspace, and
-// records the launches.  Synchronizes `stream`: the host tables are freed on
+// Builds the launch tables of the active members, uploads them into the bound
+// workspace, and records the launches.  Synchronizes `stream`: the host tables are freed on
 // return.  The caller's earlier work on `stream` is ordered before the copies.
 int upload_plan(pack_handle* h, hipStream_t stream) {
   const pack_config& c = h->cfg;
@@ -1319,14 +1343,9 @@ int upload_plan(pack_handle* h, hipStream_t stream) {
   if (plan.tiles.size() > h->b.tile_cap)
     return fail(PACK_EINVAL, "internal: the plan holds %zu GEMM tiles, the device table %zu", plan.tiles.size(),
                 h->b.tile_cap);
-  std::vector<uint32_t> aux;
-  for (uint32_t ch : h->aux_chunks)
-    if (h->active[h->chunk_tab[ch] & 0x7FFFFFFFu]) aux.push_back(ch);
-  h->n_aux_active = (int64_t)aux.size();
   auto up = [&](void* dst, const void* src, size_t bytes) {
     return bytes ? hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, stream) : hipSuccess;
   };
-  HIP_TRY(up(h->b.d_aux, aux.data(), aux.size() * 4));
   HIP_TRY(up(h->b.d_active, h->active_ids.data(), h->active_ids.size() * 4));
   HIP_TRY(up(h->b.d_descs, plan.descs.data(), plan.descs.size() * sizeof(GemmDesc)));
   HIP_TRY(up(h->b.d_tiles, plan.tiles.data(), plan.tiles.size() * sizeof(Tile)));
@@ -1360,6 +1379,7 @@ int upload_plan(pack_handle* h, hipStream_t stream) {
     h->dw[hf] = plan.dw[hf];
   }
   h->fwd1_eval = plan.fwd1_eval;
+  h->dw_all = plan.dw_all;
   for (int g = 0; g <= kGroups; ++g) h->sumtile0[g] = plan.sumtile0[g];
   for (int i = 0; i <= kGroups; ++i) {
     h->headtile0[i] = plan.headtile0[i];
@@ -1527,6 +1547,7 @@ int pack_init(const pack_config* cfg, pack_handle** out) {
   plan_layout(h);
   h->active.assign(cfg->K, 1);
   set_active_ids(h);
+  h->small = small_pack(h, h->active_ids);
   split_members(h);
   init_params(h);
   *out = h;
@@ -1602,12 +1623,11 @@ int pack_bind(pack_handle* h, void* workspace, size_t bytes, hipStream_t stream)
     const Member& m = h->mem[k];
     md[k] = MemberDev{m.width, m.dp, m.t, (float)m.scale, (float)m.lr, (float)m.wd, m.act_off,
                       m.toff[2 * m.depth], m.toff[2 * m.depth + 1], m.toff[2 * m.depth - 1],
-                      (int64_t)(m.depth - 1) * h->A + m.act_off, (int64_t)(m.depth & 1) * h->A + m.act_off,
+                      (int64_t)(m.depth - 1) * h->A + m.act_off, (int64_t)((m.depth - 1) % h->ndz()) * h->A + m.act_off,
                       m.depth, m.d_emb, m.eoff[0], m.eoff[1], m.eoff[2], m.eoff[3], m.h0_off, m.etab_off, m.p_in, 0};
     for (int l = 1; l <= m.depth; ++l) boff[(size_t)(l - 1) * h->cfg.K + k] = m.toff[2 * (l - 1) + 1];
   }
   HIP_TRY(hipMemcpyAsync(h->b.d_mem, md.data(), md.size() * sizeof(MemberDev), hipMemcpyHostToDevice, stream));
-  HIP_TRY(hipMemcpyAsync(h->b.d_chunks, h->chunk_tab.data(), h->chunk_tab.size() * 4, hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(h->b.d_bias_off, boff.data(), boff.size() * 8, hipMemcpyHostToDevice, stream));
   if (h->prec == Prec::BF16) HIP_TRY(launch_to_shadow(h->b.theta, h->b.shadow, h->P, stream));
   const int rc = upload_plan(h, stream);  // synchronizes the stream
@@ -1648,18 +1668,178 @@ int pack_train_step(pack_handle* h, const float* X, const void* y, int64_t N, co
   GemmArgs a = base_args(h);
   a.rows_valid = c.B;
   a.step = as_u32(step);
-  const double act_bytes = (double)c.B * h->elt() * [&] {
-    double s = 0;
-    for (int k : h->active_ids) s += h->mem[k].width;
-    return s;
-  }();
+  a.idx = idx;
+  int max_dp = 0;
+  double act_bytes = 0, nkeep = 0;
+  for (int k : h->active_ids) {
+    const Member& m = h->mem[k];
+    max_dp = std::max(max_dp, m.dp);
+    act_bytes += (double)c.B * h->elt() * m.width;
+    nkeep += (double)m.depth * h->Bp * m.dp / 8;
+  }
+  const double bc1 = 1.0 - std::pow(c.beta1, (double)step);
+  const double bc2 = 1.0 - std::pow(c.beta2, (double)step);
+  const AdamConst ac{(float)c.beta1, (float)c.beta2, (float)c.eps, (float)(1.0 - c.beta1), (float)(1.0 - c.beta2),
+                     (float)bc1, (float)std::sqrt(bc2)};
   auto gemm = [&](OpKind ak, OpKind bk, EpiKind e, const Launch& ln, int layer, hipStream_t s) {
     GemmArgs al = for_launch(a, ln);
     al.layer = layer;
     if (ak == OP_EMB || bk == OP_EMB) set_emb(h, al, X, N, idx, 0);
-    return timed(h, gemm_name(h->prec, ak, bk, e), 0, ln.flops, ln.bytes, s,
+    const bool adamw = e == EPI_DW && !h->muon;  // Muon: the gradient is stored, muon_step updates W_l
+    if (adamw) {
+      al.theta = h->b.theta;
+      al.am = h->b.m;
+      al.av = h->b.v;
+      al.shadow = h->b.shadow;
+      al.adam = ac;
+      al.keep_grad = c.keep_grads ? 1 : 0;
+    }
+    // AdamW fused: the weight update traffic dominates, so the HBM roofline applies
+    return timed(h, gemm_name(h->prec, ak, bk, e), adamw ? 1 : 0, ln.flops, ln.bytes, s,
                  [&] { return launch_gemm(h->prec, ak, bk, e, al, s); });
   };
+  // The dropout keep words alternate between two buffers by step parity.
+  const int par = (int)(step & 1);
+  auto words = [&](int p) { return h->b.keepw + (size_t)p * c.L * (h->A / 32); };
+  auto keep_words = [&](uint64_t s_step, int p, hipStream_t s) {
+    return timed(h, "dropout_words", 1, 0.0, nkeep, s, [&] {
+      return launch_dropout_words(a.key0, a.key1, as_u32(s_step), h->b.d_mem, nact, c.L, max_dp, h->Bp, c.B,
+                                  h->A / 32, words(p), h->b.d_active, s);
+    });
+  };
+  // The input of group hf's first layer: the embeddings' column tables from the
+  // current parameters (the first-layer GEMM produces E from them), or the
+  // gathered batch unless the data is bound.
+  auto input = [&](int hf, hipStream_t s) -> hipError_t {
+    const int32_t* gm = h->b.d_members + h->member0[hf];
+    const int gk = h->member0[hf + 1] - h->member0[hf];
+    if (h->emb) return emb_tables(h, gm, h->group[hf], s);
+    return timed(h, "gather", 1, 0.0, (double)gk * c.B * c.d_in * (4.0 + h->elt()), s, [&] {
+      return launch_gather(h->prec, X, N, c.d_in, h->Pin, idx, c.B, 0, c.B, gk, h->Bp, h->b.H0, gm, s);
+    });
+  };
+  auto forward = [&](int hf, int l, hipStream_t s) {
+    return gemm(l == 1 && h->emb ? OP_EMB : OP_KMAJ, OP_KMAJ, EPI_FWD, h->fwd[par][hf][l - 1], l, s);
+  };
+  // The head: loss and dY, then dZ_L and the head's partial sums.
+  auto head = [&](int hf, hipStream_t s) -> hipError_t {
+    const int32_t* gm = h->b.d_members + h->member0[hf];
+    const int gk = h->member0[hf + 1] - h->member0[hf];
+    const double nb = act_bytes / h->ngroups;
+    if (h->small)
+      return timed(h, "head_train", 1, 0.0, 2.0 * nb, s, [&] {
+        return launch_head_train(h->prec, h->task, h->b.H, h->b.theta, h->b.d_mem, gk, h->Bp, c.d_out, y, N, idx,
+                                 c.B, h->b.dY, h->b.rowloss, h->b.dz, h->b.headpart, h->b.status, gm, s);
+      });
+    const hipError_t e = timed(h, "head_fwd", 1, 0.0, nb, s, [&] {
+      return launch_head_fwd(h->prec, h->task, kHeadTrain, h->b.H, h->b.theta, h->b.d_mem, gk, h->Bp, c.d_out, y,
+                             idx, c.B, c.B, 0, N, h->b.dY, h->b.rowloss, nullptr, h->b.status, gm, s);
+    });
+    if (e != hipSuccess) return e;
+    return timed(h, "head_bwd", 1, 0.0, 2.0 * nb, s, [&] {
+      return launch_head_bwd(h->prec, h->b.H, h->b.theta, h->b.d_mem, h->b.d_headtiles + h->headtile0[hf],
+                             h->headtile0[hf + 1] - h->headtile0[hf], h->Bp, h->head_rb, c.d_out, h->b.dY,
+                             h->b.dz, h->b.headpart, s);
+    });
+  };
+  // The gradients of the embedding parameters: dE = dZ_1 W_1 (before W_1 is
+  // updated), reduced in the GEMM's epilogue into per-64-row-block gradient
+  // sums; then the sums over the blocks and the parameters' update.
+  auto emb_backward = [&](int hf, hipStream_t s) -> hipError_t {
+    GemmArgs ae = for_launch(a, h->de[hf]);
+    ae.tile_set = TILES_SMALL;
+    set_emb(h, ae, X, N, idx, 0);
+    const hipError_t e =
+        timed(h, gemm_name(h->prec, OP_KMAJ, OP_RMAJ, EPI_DE), 0, h->de[hf].flops, h->de[hf].bytes, s,
+              [&] { return launch_gemm(h->prec, OP_KMAJ, OP_RMAJ, EPI_DE, ae, s); });
+    if (e != hipSuccess) return e;
+    const int gk = h->member0[hf + 1] - h->member0[hf];
+    double gbytes = 0.0;
+    for (int k : h->group[hf]) gbytes += 4.0 * c.d_in * h->mem[k].d_emb * (4.0 * (h->Bp / 64) + 28.0);
+    return timed(h, "embed_grad", 1, 0.0, gbytes, s, [&] {
+      return launch_embed_grad(c.d_in, h->Bp, h->b.d_mem, h->b.d_members + h->member0[hf], gk,
+                               max_pin(h, h->group[hf]), h->b.dE, h->b.grad, h->b.theta, h->b.m, h->b.v, ac, s);
+    });
+  };
+  // The group's gradient sums (hidden biases from the dX partials, head
+  // weights and last hidden bias from the head partials, loss and head bias
+  // from the per-row values) and the update of those parameters, one launch;
+  // `ahead`: also the next step's keep words, into the other buffer (last read
+  // by the previous step's forward pass).
+  auto grad_sums = [&](int hf, bool ahead, hipStream_t s) -> hipError_t {
+    const int t0 = h->sumtile0[hf], t1 = h->sumtile0[hf + 1];
+    SumsArgs g{};
+    g.colpart = h->b.colpart;
+    g.part_stride = h->A / kPartRows;
+    g.headpart = h->b.headpart;
+    g.RB = h->head_rb;
+    g.rowloss = h->b.rowloss;
+    g.dY = h->b.dY;
+    g.mem = h->b.d_mem;
+    g.tiles = h->b.d_coltiles + t0;
+    g.ntiles = t1 - t0;
+    g.Bp = h->Bp;
+    g.B = c.B;
+    g.d_out = c.d_out;
+    g.K = c.K;
+    g.bias_off = h->b.d_bias_off;
+    g.grad = h->b.grad;
+    g.theta = h->b.theta;
+    g.m = h->b.m;
+    g.v = h->b.v;
+    g.loss_out = loss_out;
+    g.adam = ac;
+    g.decay_bias = c.decay_bias;
+    if (ahead) {
+      g.words = words(par ^ 1);
+      g.key0 = a.key0;
+      g.key1 = a.key1;
+      g.step = as_u32(step + 1);
+      g.L = c.L;
+      g.max_dp = max_dp;
+      g.nmembers = nact;
+      g.A32 = h->A / 32;
+      g.members = h->b.d_active;
+    }
+    return timed(h, "grad_sums", 1, 0.0, (4.0 * (h->Bp / kPartRows) + 28.0) * 64.0 * (t1 - t0) + (ahead ? nkeep : 0.0),
+                 s, [&] { return launch_grad_sums(g, s); });
+  };
+  // The kernels check the batch indices where they use them and the head flags
+  // one outside [0, N); those of members that are not in the launches are
+  // looked at here.
+  if (nact < c.K)
+    HIP_TRY(timed(h, "idx_check", 1, 0.0, 4.0 * c.K * c.B, stream,
+                  [&] { return launch_idx_check(idx, (int64_t)c.K * c.B, N, h->b.status, stream); }));
+
+  if (h->one_stream) {
+    // One chain of launches on the caller's stream.  The dX chain runs first
+    // (dX_l reads W_l, which the weight gradient updates), then the weight
+    // gradients of all layers in one launch; a large pack of which few members
+    // are left has two dZ buffers and runs them layer by layer.
+    if (h->keep_ready != step) HIP_TRY(keep_words(step, par, stream));
+    if (h->emb || !h->stream_rows) HIP_TRY(input(0, stream));
+    for (int l = 1; l <= c.L; ++l) HIP_TRY(forward(0, l, stream));
+    HIP_TRY(head(0, stream));
+    for (int l = c.L; l >= 2; --l) {
+      HIP_TRY(gemm(OP_KMAJ, OP_RMAJ, EPI_DX, h->dx[0][l - 1], l, stream));
+      // with two dZ buffers dW_l runs before dX_{l-1} overwrites dZ_l
+      if (!h->small) HIP_TRY(gemm(OP_RMAJ, OP_RMAJ, EPI_DW, h->dw[0][l - 1], l, stream));
+    }
+    if (h->emb) {
+      HIP_TRY(emb_backward(0, stream));
+      HIP_TRY(gemm(OP_RMAJ, OP_EMB, EPI_DW, h->dw[0][0], 1, stream));
+    }
+    if (h->small)
+      HIP_TRY(gemm(OP_RMAJ, OP_RMAJ, EPI_DW, h->dw_all, 0, stream));
+    else if (!h->emb)
+      HIP_TRY(gemm(OP_RMAJ, OP_RMAJ, EPI_DW, h->dw[0][0], 1, stream));
+    if (h->muon) HIP_TRY(muon_step(h, a, 0, stream));
+    HIP_TRY(grad_sums(0, true, stream));
+    h->keep_ready = step + 1;
+    h->t = step;
+    return PACK_OK;
+  }
+
   // member groups: group 0 on the caller's stream, group g on gstream[g]
   hipStream_t hs[kGroups] = {stream};
   for (int g = 1; g < kGroups; ++g) hs[g] = h->gstream[g];
@@ -1677,103 +1857,54 @@ int pack_train_step(pack_handle* h, const float* X, const void* y, int64_t N, co
     }
     return e;
   };
-  int max_dp = 0;
-  double nkeep = 0;
-  for (int k : h->active_ids) {
-    max_dp = std::max(max_dp, h->mem[k].dp);
-    nkeep += (double)h->mem[k].depth * h->Bp * h->mem[k].dp / 8;
-  }
   // Dropout keep words (Philox, ALU-bound) run on the side stream: normally
   // they were produced during the previous step's backward pass; otherwise
   // (first step, or after a break in the sequence) they are produced now,
   // beside the HBM-bound gather.  Either way the forward GEMMs wait for them.
-  const int par = (int)(step & 1);
-  auto keep_words = [&](uint64_t s_step, int p) {
-    return timed(h, "dropout_words", 1, 0.0, nkeep, h->side, [&] {
-      return launch_dropout_words(a.key0, a.key1, as_u32(s_step), h->b.d_mem, nact, c.L, max_dp, h->Bp, c.B,
-                                  h->A / 32, h->b.keepw + (size_t)p * c.L * (h->A / 32), h->b.d_active, h->side);
-    });
-  };
-  // indices outside [0, N) are replaced (and flagged) before any kernel reads X or y through them
-  HIP_TRY(timed(h, "idx_check", 1, 0.0, 8.0 * c.K * c.B, stream, [&] {
-    return launch_idx_check(idx, (int64_t)c.K * c.B, N, h->b.idx_ok, h->b.status, stream);
-  }));
-  idx = h->b.idx_ok;
   if (h->keep_ready != step) {
     HIP_TRY(hipEventRecord(h->ev_fork, stream));
     HIP_TRY(hipStreamWaitEvent(h->side, h->ev_fork, 0));
-    HIP_TRY(keep_words(step, par));
+    HIP_TRY(keep_words(step, par, h->side));
     HIP_TRY(hipEventRecord(h->ev_keep[par], h->side));
   }
-  const double bc1 = 1.0 - std::pow(c.beta1, (double)step);
-  const double bc2 = 1.0 - std::pow(c.beta2, (double)step);
-  const AdamConst ac{(float)c.beta1, (float)c.beta2, (float)c.eps, (float)(1.0 - c.beta1), (float)(1.0 - c.beta2),
-                     (float)bc1, (float)std::sqrt(bc2)};
   // Each member group runs its whole chain -- gather, forward GEMMs, head,
   // loss, backward GEMMs with the fused optimizer -- on its own stream; the
-  // groups join before the bias/head AdamW.
+  // groups join at the end.
   HIP_TRY(split());
   for (int hf = 0; hf < ng; ++hf) {
     const hipStream_t s = hs[hf];
-    const int gk = h->member0[hf + 1] - h->member0[hf];
     if (h->emb) {
-      // the column tables of the group's embeddings from the current parameters;
-      // the first-layer forward GEMM produces E from them
-      HIP_TRY(emb_tables(h, h->b.d_members + h->member0[hf], h->group[hf], s));
+      HIP_TRY(input(hf, s));
     } else if (!h->stream_rows) {
       // the groups' gathers (HBM-bound) run one after another, so a group's
       // forward GEMMs overlap the next group's gather instead of every group
       // waiting for all the groups' gathers at once
       if (hf > 0) HIP_TRY(hipStreamWaitEvent(s, h->ev_gather[hf - 1], 0));
-      HIP_TRY(timed(h, "gather", 1, 0.0, (double)gk * c.B * c.d_in * (4.0 + h->elt()), s, [&] {
-        return launch_gather(h->prec, X, c.d_in, h->Pin, idx, c.B, 0, c.B, gk, h->Bp, h->b.H0,
-                             h->b.d_members + h->member0[hf], s);
-      }));
+      HIP_TRY(input(hf, s));
       HIP_TRY(hipEventRecord(h->ev_gather[hf], s));
     }
     HIP_TRY(hipStreamWaitEvent(s, h->ev_keep[par], 0));
   }
-  // The group's gradient sums (hidden biases from the dX partials, head
-  // weights and last hidden bias from the head partials, loss and head bias
-  // from the per-row values) run as one launch on the side stream once the
-  // group's last producer (its last dX launch, or the head backward for
-  // one-block packs) is done: off the group's chain; the final bias and head
-  // AdamW waits for them.
-  auto grad_sums = [&](int hf) -> hipError_t {
+  // A group's gradient sums run on the side stream once its last producer (its
+  // last dX launch, or the head backward for one-block packs) is done: off the
+  // group's chain.  Nothing of the step reads the parameters they update after
+  // that point.
+  auto side_sums = [&](int hf) -> hipError_t {
     hipError_t e = hipEventRecord(h->ev_bias[hf], hs[hf]);
     if (e == hipSuccess) e = hipStreamWaitEvent(h->side, h->ev_bias[hf], 0);
-    if (e != hipSuccess) return e;
-    const int t0 = h->sumtile0[hf], t1 = h->sumtile0[hf + 1];
-    const double nb = 4.0 * (h->Bp / kPartRows) * 64.0 * (t1 - t0);
-    return timed(h, "grad_sums", 1, 0.0, nb, h->side, [&] {
-      return launch_grad_sums(h->b.colpart, h->A / kPartRows, h->b.headpart, h->head_rb, h->b.rowloss, h->b.dY,
-                              h->b.d_mem, h->b.d_coltiles + t0, t1 - t0, h->Bp, c.B, c.d_out, h->b.d_bias_off, c.K,
-                              h->b.grad, loss_out, h->side);
-    });
+    return e != hipSuccess ? e : grad_sums(hf, false, h->side);
   };
   for (int l = 1; l <= c.L; ++l)
-    for (int hf = 0; hf < ng; ++hf)
-      HIP_TRY(gemm(l == 1 && h->emb ? OP_EMB : OP_KMAJ, OP_KMAJ, EPI_FWD, h->fwd[par][hf][l - 1], l, hs[hf]));
+    for (int hf = 0; hf < ng; ++hf) HIP_TRY(forward(hf, l, hs[hf]));
   for (int hf = 0; hf < ng; ++hf) {
-    const hipStream_t s = hs[hf];
-    const int32_t* gm = h->b.d_members + h->member0[hf];
-    const int gk = h->member0[hf + 1] - h->member0[hf];
-    HIP_TRY(timed(h, "head_fwd", 1, 0.0, act_bytes / ng, s, [&] {
-      return launch_head_fwd(h->prec, h->task, kHeadTrain, h->b.H, h->b.theta, h->b.d_mem, gk, h->Bp, c.d_out, y,
-                             idx, c.B, c.B, 0, 0, h->b.dY, h->b.rowloss, nullptr, gm, s);
-    }));
-    HIP_TRY(timed(h, "head_bwd", 1, 0.0, 2.0 * act_bytes / ng, s, [&] {
-      return launch_head_bwd(h->prec, h->b.H, h->b.theta, h->b.d_mem, h->b.d_headtiles + h->headtile0[hf],
-                             h->headtile0[hf + 1] - h->headtile0[hf], h->Bp, h->head_rb, c.d_out, h->b.dY,
-                             h->b.dz, h->b.headpart, s);
-    }));
-    if (c.L == 1) HIP_TRY(grad_sums(hf));
+    HIP_TRY(head(hf, hs[hf]));
+    if (c.L == 1) HIP_TRY(side_sums(hf));
   }
   // the next step's keep words go to the other buffer (last read by the
   // previous step's forward pass) while this step's backward runs
   HIP_TRY(hipEventRecord(h->ev_fork, stream));
   HIP_TRY(hipStreamWaitEvent(h->side, h->ev_fork, 0));
-  HIP_TRY(keep_words(step + 1, par ^ 1));
+  HIP_TRY(keep_words(step + 1, par ^ 1, h->side));
   HIP_TRY(hipEventRecord(h->ev_keep[par ^ 1], h->side));
   h->keep_ready = step + 1;
   for (int l = c.L; l >= 1; --l)
@@ -1782,64 +1913,21 @@ int pack_train_step(pack_handle* h, const float* X, const void* y, int64_t N, co
       // dX_l reads W_l, so it runs before the weight-gradient GEMM updates W_l in place
       if (l > 1) {
         HIP_TRY(gemm(OP_KMAJ, OP_RMAJ, EPI_DX, h->dx[hf][l - 1], l, s));
-        if (l == 2) HIP_TRY(grad_sums(hf));
+        if (l == 2) HIP_TRY(side_sums(hf));
       }
-      if (l == 1 && h->emb) {
-        // dE = dZ_1 W_1, before W_1 is updated, reduced in the GEMM's epilogue
-        // into per-64-row-block gradient sums; then the sums over the blocks
-        GemmArgs ae = for_launch(a, h->de[hf]);
-        ae.tile_set = TILES_SMALL;
-        ae.emb_x = X;
-        ae.emb_idx = idx;
-        ae.emb_mem = h->b.d_mem;
-        ae.emb_d_in = c.d_in;
-        ae.emb_tab = h->b.etab;
-        HIP_TRY(timed(h, gemm_name(h->prec, OP_KMAJ, OP_RMAJ, EPI_DE), 0, h->de[hf].flops, h->de[hf].bytes, s,
-                      [&] { return launch_gemm(h->prec, OP_KMAJ, OP_RMAJ, EPI_DE, ae, s); }));
-        const int gk = h->member0[hf + 1] - h->member0[hf];
-        double gbytes = 0.0;
-        for (int k : h->group[hf]) gbytes += 4.0 * c.d_in * h->mem[k].d_emb * (4.0 * (h->Bp / 64) + 4.0);
-        HIP_TRY(timed(h, "embed_grad", 1, 0.0, gbytes, s, [&] {
-          return launch_embed_grad(c.d_in, h->Bp, h->b.d_mem, h->b.d_members + h->member0[hf], gk,
-                                   max_pin(h, h->group[hf]), h->b.dE, h->b.grad, s);
-        }));
-      }
-      GemmArgs al = for_launch(a, h->dw[hf][l - 1]);
-      al.layer = l;
-      const OpKind bk = l == 1 && h->emb ? OP_EMB : OP_RMAJ;  // the embedded E is produced in the GEMM
-      if (h->muon) {  // the gradient is stored; the Muon step below updates W_l
-        HIP_TRY(gemm(OP_RMAJ, bk, EPI_DW, h->dw[hf][l - 1], l, s));
-        continue;
-      }
-      if (bk == OP_EMB) set_emb(h, al, X, N, idx, 0);
-      al.theta = h->b.theta;
-      al.am = h->b.m;
-      al.av = h->b.v;
-      al.shadow = h->b.shadow;
-      al.adam = ac;
-      al.keep_grad = c.keep_grads ? 1 : 0;
-      // AdamW fused: the weight update traffic dominates, so the HBM roofline applies
-      HIP_TRY(timed(h, gemm_name(h->prec, OP_RMAJ, bk, EPI_DW), 1, h->dw[hf][l - 1].flops, h->dw[hf][l - 1].bytes, s,
-                    [&] { return launch_gemm(h->prec, OP_RMAJ, bk, EPI_DW, al, s); }));
+      if (l == 1 && h->emb) HIP_TRY(emb_backward(hf, s));
+      // the embedded E is produced in the GEMM
+      HIP_TRY(gemm(OP_RMAJ, l == 1 && h->emb ? OP_EMB : OP_RMAJ, EPI_DW, h->dw[hf][l - 1], l, s));
     }
   if (h->muon)
     for (int hf = 0; hf < ng; ++hf) HIP_TRY(muon_step(h, a, hf, hs[hf]));
   HIP_TRY(merge());
-  // the next step's keep words join the caller's stream too, so that a sync of
-  // that stream (or later work on it, such as a re-plan that rewrites the
-  // member table the keep-word kernel reads) orders after them
+  // the gradient sums and the next step's keep words join the caller's stream
+  // too, so that a sync of that stream (or later work on it, such as a re-plan
+  // that rewrites the member table the keep-word kernel reads) orders after
+  // them
   HIP_TRY(hipEventRecord(h->ev_join, h->side));
   HIP_TRY(hipStreamWaitEvent(stream, h->ev_join, 0));
-  double naux = 0;
-  for (int k : h->active_ids) {
-    const Member& m = h->mem[k];
-    naux += (double)m.depth * m.width + (double)c.d_out * m.width + c.d_out;
-  }
-  HIP_TRY(timed(h, "adamw", 1, 0.0, naux * (h->prec == Prec::BF16 ? 30.0 : 28.0), stream, [&] {
-    // biases and head weights: read in fp32 only, so no bf16 copy is written
-    return launch_adamw(h->prec, h->b.theta, h->b.grad, h->b.m, h->b.v, nullptr, h->b.d_chunks, h->b.d_aux,
-                        h->b.d_mem, h->n_aux_active, ac, stream);
-  }));
   h->t = step;
   return PACK_OK;
 }
@@ -1857,7 +1945,7 @@ hipError_t eval_forward(pack_handle* h, GemmArgs a, const float* X, int64_t N, i
   const pack_config& c = h->cfg;
   hipError_t e = hipSuccess;
   if (!h->emb)
-    e = launch_gather(h->prec, X, c.d_in, h->Pin, nullptr, c.B, r0, a.rows_valid, 1, h->Bp, h->b.H0, nullptr,
+    e = launch_gather(h->prec, X, N, c.d_in, h->Pin, nullptr, c.B, r0, a.rows_valid, 1, h->Bp, h->b.H0, nullptr,
                       stream);
   if (e != hipSuccess) return e;
   for (int l = 1; l <= c.L; ++l) {
@@ -1890,8 +1978,8 @@ int pack_eval_members(pack_handle* h, const float* Xv, const void* yv, int64_t N
     a.rows_valid = (int)std::min<int64_t>(h->Bp, Nv - r0);
     HIP_TRY(eval_forward(h, a, Xv, Nv, r0, stream));
     HIP_TRY(launch_head_fwd(h->prec, h->task, kHeadEval, h->b.H, h->b.theta, h->b.d_mem, nact, h->Bp, c.d_out,
-                            yv, nullptr, c.B, a.rows_valid, r0, Nv, nullptr, nullptr, pred_out, h->b.d_active,
-                            stream));
+                            yv, nullptr, c.B, a.rows_valid, r0, Nv, nullptr, nullptr, pred_out, nullptr,
+                            h->b.d_active, stream));
   }
   HIP_TRY(launch_eval_score(h->task, pred_out, yv, nact, Nv, score_out, h->b.d_active, stream));
   return PACK_OK;
@@ -1915,12 +2003,12 @@ int pack_predict(pack_handle* h, const float* X, int64_t N, int32_t mode, float*
       // member i (i-th active id) writes rows r0.. of out[i, :, :]
       HIP_TRY(launch_head_fwd(h->prec, h->task, kHeadPredict, h->b.H, h->b.theta, h->b.d_mem, nact, h->Bp,
                               c.d_out, nullptr, nullptr, c.B, a.rows_valid, r0, N, nullptr, nullptr, out,
-                              h->b.d_active, stream));
+                              nullptr, h->b.d_active, stream));
     } else {
       // the chunk's member predictions go to the dY buffer ([K, Bp, d_out]), then their mean to out
       HIP_TRY(launch_head_fwd(h->prec, h->task, kHeadPredict, h->b.H, h->b.theta, h->b.d_mem, nact, h->Bp,
                               c.d_out, nullptr, nullptr, c.B, a.rows_valid, 0, h->Bp, nullptr, nullptr, h->b.dY,
-                              h->b.d_active, stream));
+                              nullptr, h->b.d_active, stream));
       HIP_TRY(launch_ensemble_mean(h->b.dY, nact, h->Bp, a.rows_valid, c.d_out, r0, out, stream));
     }
   }

@@ -105,127 +105,6 @@ struct Vec8<float> {
   }
 };
 
-// Y = H_L[row] . W_out^T + b_out for 8 rows per wave (8 lanes per row, each
-// lane a 16-byte column vector per step), then, by MODE: the training loss and
-// dLoss/dY of the row (kHeadTrain); the score-ready eval value (kHeadEval:
-// output, P(class 1) or P(true class)) at pred[k * Nv + row_base + row]; or
-// all d_out prediction values (kHeadPredict: outputs, P(class 1) or the softmax
-// probabilities) at pred[((blockIdx.y * Nv) + row_base + row) * d_out + o].
-// D >= d_out is the output count rounded up to a power of two.  H is the start
-// of the activation buffers; member k reads its last hidden layer at H + h_last.
-template <typename T, int MODE, int D>
-__global__ __launch_bounds__(256) void head_fwd_kernel(Task task, const T* H, const float* theta,
-                                                       const MemberDev* mem, int Bp, int d_out,
-                                                       const void* y, const int32_t* idx, int B,
-                                                       int rows_valid, int64_t row_base, int64_t Nv,
-                                                       float* dY, float* rowloss, float* pred,
-                                                       const int32_t* members) {
-  const int k = members ? members[blockIdx.y] : (int)blockIdx.y;
-  const int lane = threadIdx.x & 63, sub = lane & 7;
-  const int row = blockIdx.x * 32 + (threadIdx.x >> 3);
-  if (row >= Bp) return;  // Bp is a multiple of 32: whole 8-lane groups leave together
-  const MemberDev md = mem[k];
-  const T* h = H + md.h_last + (int64_t)row * md.dp;
-  const float* Wo = theta + md.w_out_off;
-  float acc[D];
-#pragma unroll
-  for (int o = 0; o < D; ++o) acc[o] = 0.0f;
-  // unrolled so that several rows' loads are in flight at once (the loop is
-  // latency-bound otherwise: one 16-byte load per lane per iteration)
-#pragma unroll 4
-  for (int c = sub * 8; c < md.dp; c += 64) {
-    float x[8];
-    Vec8<T>::load(h + c, x);
-#pragma unroll
-    for (int o = 0; o < D; ++o) {
-      if (o >= d_out) break;
-      const float4 w0 = *reinterpret_cast<const float4*>(Wo + (int64_t)o * md.dp + c);
-      const float4 w1 = *reinterpret_cast<const float4*>(Wo + (int64_t)o * md.dp + c + 4);
-      acc[o] += ((x[0] * w0.x + x[1] * w0.y) + (x[2] * w0.z + x[3] * w0.w)) +
-                ((x[4] * w1.x + x[5] * w1.y) + (x[6] * w1.z + x[7] * w1.w));
-    }
-  }
-  float z[kMaxOut];
-#pragma unroll
-  for (int o = 0; o < kMaxOut; ++o) z[o] = 0.0f;
-#pragma unroll
-  for (int o = 0; o < D; ++o) {
-    float v = acc[o];
-    v += __shfl_xor(v, 1, 64);
-    v += __shfl_xor(v, 2, 64);
-    v += __shfl_xor(v, 4, 64);
-    if (o < d_out) z[o] = v + theta[md.b_out_off + o];
-  }
-  if (sub != 0) return;
-
-  constexpr bool EVAL = MODE != kHeadTrain;
-  const bool valid = EVAL ? row < rows_valid : row < B;
-  int64_t src = 0;
-  if (valid) src = EVAL ? row_base + row : (int64_t)idx[(int64_t)k * B + row];
-  if constexpr (MODE == kHeadPredict) {
-    if (!valid) return;
-    float* out = pred + ((int64_t)blockIdx.y * Nv + row_base + row) * d_out;
-    if (task == Task::REG) {
-      for (int o = 0; o < d_out; ++o) out[o] = z[o];
-    } else if (task == Task::BIN) {
-      out[0] = 1.0f / (1.0f + expf(-z[0]));
-    } else {
-      float mx = z[0];
-      for (int o = 1; o < d_out; ++o) mx = fmaxf(mx, z[o]);
-      float se = 0.0f;
-      for (int o = 0; o < d_out; ++o) se += expf(z[o] - mx);
-      for (int o = 0; o < d_out; ++o) out[o] = expf(z[o] - mx) / se;
-    }
-    return;
-  }
-  if (EVAL) {
-    if (!valid) return;
-    float p;
-    if (task == Task::REG) {
-      p = z[0];
-    } else if (task == Task::BIN) {
-      p = 1.0f / (1.0f + expf(-z[0]));
-    } else {
-      const int lab = min(max(static_cast<const int32_t*>(y)[src], 0), d_out - 1);
-      float mx = z[0];
-      for (int o = 1; o < d_out; ++o) mx = fmaxf(mx, z[o]);
-      float se = 0.0f;
-      for (int o = 0; o < d_out; ++o) se += expf(z[o] - mx);
-      p = expf(z[lab] - mx) / se;
-    }
-    pred[(int64_t)k * Nv + row_base + row] = p;
-    return;
-  }
-  float* dy = dY + ((int64_t)k * Bp + row) * d_out;
-  if (!valid) {
-    for (int o = 0; o < d_out; ++o) dy[o] = 0.0f;
-    rowloss[(int64_t)k * Bp + row] = 0.0f;
-    return;
-  }
-  const float invB = 1.0f / (float)B;
-  float loss;
-  if (task == Task::REG) {
-    const float d = z[0] - static_cast<const float*>(y)[src];
-    loss = d * d;
-    dy[0] = 2.0f * d * invB;
-  } else if (task == Task::BIN) {
-    const float t = static_cast<const float*>(y)[src];
-    const float x = z[0];
-    loss = fmaxf(x, 0.0f) - x * t + log1pf(expf(-fabsf(x)));
-    dy[0] = (1.0f / (1.0f + expf(-x)) - t) * invB;
-  } else {
-    const int lab = min(max(static_cast<const int32_t*>(y)[src], 0), d_out - 1);
-    float mx = z[0];
-    for (int o = 1; o < d_out; ++o) mx = fmaxf(mx, z[o]);
-    float se = 0.0f;
-    for (int o = 0; o < d_out; ++o) se += expf(z[o] - mx);
-    const float lse = mx + logf(se);
-    loss = lse - z[lab];
-    for (int o = 0; o < d_out; ++o) dy[o] = (expf(z[o] - lse) - (o == lab ? 1.0f : 0.0f)) * invB;
-  }
-  rowloss[(int64_t)k * Bp + row] = loss;
-}
-
 // CPT consecutive activations of one row.
 template <typename T, int CPT>
 struct VecN;
@@ -261,6 +140,272 @@ struct VecN<float, 4> {
     *reinterpret_cast<float4*>(p) = float4{x[0], x[1], x[2], x[3]};
   }
 };
+template <>
+struct VecN<__bf16, 2> {
+  __device__ static void load(const __bf16* p, float (&x)[2]) {
+    const uint32_t u = *reinterpret_cast<const uint32_t*>(p);
+    x[0] = __uint_as_float(u << 16);
+    x[1] = __uint_as_float(u & 0xFFFF0000u);
+  }
+  __device__ static void store(__bf16* p, const float (&x)[2]) {
+    *reinterpret_cast<uint32_t*>(p) = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)x[0]) |
+                                      ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)x[1]) << 16);
+  }
+};
+template <>
+struct VecN<float, 2> {
+  __device__ static void load(const float* p, float (&x)[2]) {
+    const float2 a = *reinterpret_cast<const float2*>(p);
+    x[0] = a.x; x[1] = a.y;
+  }
+  __device__ static void store(float* p, const float (&x)[2]) { *reinterpret_cast<float2*>(p) = float2{x[0], x[1]}; }
+};
+
+// Partial products of one row with the head: lane sub of the row's 8 lanes sums
+// the columns c = 8 sub, 8 sub + 64, ... (16-byte vectors).  Unrolled so that
+// several vectors' loads are in flight at once (the loop is latency-bound
+// otherwise: one 16-byte load per lane per iteration).
+template <typename T, int D>
+__device__ __forceinline__ void head_row(const T* h, const float* Wo, int dp, int d_out, int sub, float (&acc)[D]) {
+#pragma unroll
+  for (int o = 0; o < D; ++o) acc[o] = 0.0f;
+#pragma unroll 4
+  for (int c = sub * 8; c < dp; c += 64) {
+    float x[8];
+    Vec8<T>::load(h + c, x);
+#pragma unroll
+    for (int o = 0; o < D; ++o) {
+      if (o >= d_out) break;
+      const float4 w0 = *reinterpret_cast<const float4*>(Wo + (int64_t)o * dp + c);
+      const float4 w1 = *reinterpret_cast<const float4*>(Wo + (int64_t)o * dp + c + 4);
+      acc[o] += ((x[0] * w0.x + x[1] * w0.y) + (x[2] * w0.z + x[3] * w0.w)) +
+                ((x[4] * w1.x + x[5] * w1.y) + (x[6] * w1.z + x[7] * w1.w));
+    }
+  }
+}
+
+// The row's outputs from its 8 lanes' partial products (every lane gets them).
+template <int D>
+__device__ __forceinline__ void head_outputs(const float (&acc)[D], const float* b_out, int d_out,
+                                             float (&z)[kMaxOut]) {
+#pragma unroll
+  for (int o = 0; o < kMaxOut; ++o) z[o] = 0.0f;
+#pragma unroll
+  for (int o = 0; o < D; ++o) {
+    float v = acc[o];
+    v += __shfl_xor(v, 1, 64);
+    v += __shfl_xor(v, 2, 64);
+    v += __shfl_xor(v, 4, 64);
+    if (o < d_out) z[o] = v + b_out[o];
+  }
+}
+
+// The training loss of a row with outputs z and target y[src], and dLoss/dz
+// (times 1 / B) by put(o, value).
+template <typename Put>
+__device__ __forceinline__ float head_loss(Task task, const float (&z)[kMaxOut], int d_out, const void* y,
+                                           int64_t src, int B, Put put) {
+  const float invB = 1.0f / (float)B;
+  float loss;
+  if (task == Task::REG) {
+    const float d = z[0] - static_cast<const float*>(y)[src];
+    loss = d * d;
+    put(0, 2.0f * d * invB);
+  } else if (task == Task::BIN) {
+    const float t = static_cast<const float*>(y)[src];
+    const float x = z[0];
+    loss = fmaxf(x, 0.0f) - x * t + log1pf(expf(-fabsf(x)));
+    put(0, (1.0f / (1.0f + expf(-x)) - t) * invB);
+  } else {
+    const int lab = min(max(static_cast<const int32_t*>(y)[src], 0), d_out - 1);
+    float mx = z[0];
+    for (int o = 1; o < d_out; ++o) mx = fmaxf(mx, z[o]);
+    float se = 0.0f;
+    for (int o = 0; o < d_out; ++o) se += expf(z[o] - mx);
+    const float lse = mx + logf(se);
+    loss = lse - z[lab];
+    for (int o = 0; o < d_out; ++o) put(o, (expf(z[o] - lse) - (o == lab ? 1.0f : 0.0f)) * invB);
+  }
+  return loss;
+}
+
+// The data row of batch row `row` of member k; an index outside [0, N) takes
+// row 0 and raises the status flag (a plain vector store under a per-lane
+// condition; every writer stores the same value).
+__device__ __forceinline__ int64_t batch_row(const int32_t* idx, int64_t i, int64_t N, uint32_t* status) {
+  const int32_t v = idx[i], r = checked_row(v, N);
+  if (r != v) status[0] = 1u;
+  return r;
+}
+
+// Y = H_L[row] . W_out^T + b_out for 8 rows per wave (8 lanes per row, each
+// lane a 16-byte column vector per step), then, by MODE: the training loss and
+// dLoss/dY of the row (kHeadTrain); the score-ready eval value (kHeadEval:
+// output, P(class 1) or P(true class)) at pred[k * Nv + row_base + row]; or
+// all d_out prediction values (kHeadPredict: outputs, P(class 1) or the softmax
+// probabilities) at pred[((blockIdx.y * Nv) + row_base + row) * d_out + o].
+// D >= d_out is the output count rounded up to a power of two.  H is the start
+// of the activation buffers; member k reads its last hidden layer at H + h_last.
+template <typename T, int MODE, int D>
+__global__ __launch_bounds__(256) void head_fwd_kernel(Task task, const T* H, const float* theta,
+                                                       const MemberDev* mem, int Bp, int d_out,
+                                                       const void* y, const int32_t* idx, int B,
+                                                       int rows_valid, int64_t row_base, int64_t Nv,
+                                                       float* dY, float* rowloss, float* pred, uint32_t* status,
+                                                       const int32_t* members) {
+  const int k = members ? members[blockIdx.y] : (int)blockIdx.y;
+  const int lane = threadIdx.x & 63, sub = lane & 7;
+  const int row = blockIdx.x * 32 + (threadIdx.x >> 3);
+  if (row >= Bp) return;  // Bp is a multiple of 32: whole 8-lane groups leave together
+  const MemberDev md = mem[k];
+  float acc[D], z[kMaxOut];
+  head_row<T, D>(H + md.h_last + (int64_t)row * md.dp, theta + md.w_out_off, md.dp, d_out, sub, acc);
+  head_outputs<D>(acc, theta + md.b_out_off, d_out, z);
+  if (sub != 0) return;
+
+  constexpr bool EVAL = MODE != kHeadTrain;
+  const bool valid = EVAL ? row < rows_valid : row < B;
+  if constexpr (MODE == kHeadPredict) {
+    if (!valid) return;
+    float* out = pred + ((int64_t)blockIdx.y * Nv + row_base + row) * d_out;
+    if (task == Task::REG) {
+      for (int o = 0; o < d_out; ++o) out[o] = z[o];
+    } else if (task == Task::BIN) {
+      out[0] = 1.0f / (1.0f + expf(-z[0]));
+    } else {
+      float mx = z[0];
+      for (int o = 1; o < d_out; ++o) mx = fmaxf(mx, z[o]);
+      float se = 0.0f;
+      for (int o = 0; o < d_out; ++o) se += expf(z[o] - mx);
+      for (int o = 0; o < d_out; ++o) out[o] = expf(z[o] - mx) / se;
+    }
+    return;
+  }
+  if (EVAL) {
+    if (!valid) return;
+    float p;
+    if (task == Task::REG) {
+      p = z[0];
+    } else if (task == Task::BIN) {
+      p = 1.0f / (1.0f + expf(-z[0]));
+    } else {
+      const int lab = min(max(static_cast<const int32_t*>(y)[row_base + row], 0), d_out - 1);
+      float mx = z[0];
+      for (int o = 1; o < d_out; ++o) mx = fmaxf(mx, z[o]);
+      float se = 0.0f;
+      for (int o = 0; o < d_out; ++o) se += expf(z[o] - mx);
+      p = expf(z[lab] - mx) / se;
+    }
+    pred[(int64_t)k * Nv + row_base + row] = p;
+    return;
+  }
+  float* dy = dY + ((int64_t)k * Bp + row) * d_out;
+  float loss = 0.0f;
+  if (valid) {
+    const int64_t src = batch_row(idx, (int64_t)k * B + row, Nv, status);
+    loss = head_loss(task, z, d_out, y, src, B, [&](int o, float v) { dy[o] = v; });
+  } else {
+    for (int o = 0; o < d_out; ++o) dy[o] = 0.0f;
+  }
+  rowloss[(int64_t)k * Bp + row] = loss;
+}
+
+// The training head of small packs: one workgroup takes 32 rows of one member
+// through the head forward, the loss, dZ_L and the partial sums of dW_out and
+// db_L (one row block of kHeadRows rows).  Small launches are bound by the
+// chain of launches and loads, not by the second read of H_L (which hits the
+// caches here).  Column pairs: thread t takes columns 2 (t % 128), + 256, ... of
+// rows 16 (t / 128) .. + 15; the two halves' sums are added in that order.
+template <typename T, int D>
+__global__ __launch_bounds__(256) void head_train_kernel(Task task, const T* H, const float* theta,
+                                                         const MemberDev* mem, int Bp, int d_out, const void* y,
+                                                         int64_t N, const int32_t* idx, int B, float* dY,
+                                                         float* rowloss, T* dZ, float* part, uint32_t* status,
+                                                         const int32_t* members) {
+  __shared__ float sdy[kHeadRows][D];
+  __shared__ float red[D + 1][256];
+  const int k = members[blockIdx.y];
+  const int tid = threadIdx.x, sub = tid & 7, rl = tid >> 3;
+  const int r0 = blockIdx.x * kHeadRows, row = r0 + rl;
+  const MemberDev md = mem[k];
+  const T* h = H + md.h_last;
+  const float* Wo = theta + md.w_out_off;
+  {
+    float acc[D], z[kMaxOut];
+    head_row<T, D>(h + (int64_t)row * md.dp, Wo, md.dp, d_out, sub, acc);
+    head_outputs<D>(acc, theta + md.b_out_off, d_out, z);
+    if (sub == 0) {
+      float* dy = dY + ((int64_t)k * Bp + row) * d_out;
+#pragma unroll
+      for (int o = 0; o < D; ++o) sdy[rl][o] = 0.0f;
+      float loss = 0.0f;
+      if (row < B) {
+        const int64_t src = batch_row(idx, (int64_t)k * B + row, N, status);
+        loss = head_loss(task, z, d_out, y, src, B, [&](int o, float v) { sdy[rl][o] = v; });
+      }
+      for (int o = 0; o < d_out; ++o) dy[o] = sdy[rl][o];
+      rowloss[(int64_t)k * Bp + row] = loss;
+    }
+  }
+  __syncthreads();
+  T* dz = dZ + md.dz_last;
+  float* pk = part + (int64_t)(Bp / kHeadRows) * (d_out + 1) * (md.act_off / Bp) +
+              (int64_t)blockIdx.x * (d_out + 1) * md.dp;
+  const int half = tid >> 7;
+  for (int c0 = 0; c0 < md.dp; c0 += 256) {  // uniform
+    const int cl = 2 * (tid & 127), c = c0 + cl;
+    const bool valid = c < md.dp;  // dp is even
+    float wo[D][2], accw[D][2], accb[2] = {0.0f, 0.0f};
+#pragma unroll
+    for (int o = 0; o < D; ++o)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        wo[o][j] = valid && o < d_out ? Wo[(int64_t)o * md.dp + c + j] : 0.0f;
+        accw[o][j] = 0.0f;
+      }
+    if (valid) {
+#pragma unroll 8
+      for (int i = 0; i < kHeadRows / 2; ++i) {
+        const int r = half * (kHeadRows / 2) + i;
+        const int64_t e = (int64_t)(r0 + r) * md.dp + c;
+        float hv[2], g[2];
+        VecN<T, 2>::load(h + e, hv);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          float dh = 0.0f;
+#pragma unroll
+          for (int o = 0; o < D; ++o) {
+            const float dy = sdy[r][o];
+            dh += dy * wo[o][j];
+            accw[o][j] += dy * hv[j];
+          }
+          g[j] = hv[j] > 0.0f ? dh * md.drop_s : 0.0f;
+          accb[j] += g[j];
+        }
+        VecN<T, 2>::store(dz + e, g);
+      }
+    }
+    __syncthreads();  // the previous columns' sums have been read
+    if (half == 1) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+#pragma unroll
+        for (int o = 0; o < D; ++o) red[o][cl + j] = accw[o][j];
+        red[D][cl + j] = accb[j];
+      }
+    }
+    __syncthreads();
+    if (half == 0 && valid) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+#pragma unroll
+        for (int o = 0; o < D; ++o)
+          if (o < d_out) pk[(int64_t)o * md.dp + c + j] = accw[o][j] + red[o][cl + j];
+        pk[(int64_t)d_out * md.dp + c + j] = accb[j] + red[D][cl + j];
+      }
+    }
+  }
+}
 
 // Head backward over one (member, 32*CPT columns, RB rows) block:
 //   dH_L = dY W_out, dZ_L = dH_L * [H_L > 0] * s_k (written out),
@@ -344,73 +489,94 @@ template <typename V, typename F>
 __device__ __forceinline__ V sum_in_order(int n, int step, F term) {
   const int m = n <= 0 ? 0 : (n + step - 1) / step;
   V s = 0;
-  int i = 0;
-  for (; i + 8 <= m; i += 8) {
+  for (int i = 0; i < m; i += 8) {
     V v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = term(i + u);
+    for (int u = 0; u < 8; ++u) v[u] = i + u < m ? term(i + u) : V(0);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) s += v[u];
+    for (int u = 0; u < 8; ++u)
+      if (i + u < m) s += v[u];
   }
-  for (; i < m; ++i) s += term(i);
   return s;
 }
 
-// The gradient sums of a member group, one wave per ColTile (fixed orders):
+__device__ __forceinline__ void write_keep_word(uint32_t key0, uint32_t key1, uint32_t step, const MemberDev* mem,
+                                                int k, int l, int64_t w, int Bp, int rows_valid, int64_t A32,
+                                                uint32_t* out);
+
+// The gradient sums of a member group, one wave per ColTile (fixed orders), and
+// the AdamW update of the parameters they belong to:
 //   part >= 0: db_{part+1}[c] = sum over the 64-row blocks of the dX
 //     epilogue's column partials (bias layer part at colpart + part * part_stride);
-//   kSumHead:  dW_out[o][c] and db_L[c] = sums over the head backward's row blocks;
-//   kSumLoss:  the batch-mean loss of the member (fp64 over its B rows) and
-//     db_out[o] = sum of dY over the rows (fp64).
-__global__ __launch_bounds__(256) void grad_sums_kernel(const float* colpart, int64_t part_stride,
-                                                        const float* headpart, int RB, const float* rowloss,
-                                                        const float* dY, const MemberDev* mem, const ColTile* tiles,
-                                                        int ntiles, int Bp, int B, int d_out,
-                                                        const int64_t* bias_off, int K, float* grad,
-                                                        float* loss_out) {
+//   kSumHead:  dW_out[o][c], or db_L[c] (o = d_out) = sum over the head
+//     backward's row blocks;
+//   kSumLoss:  db_out[o] = sum of dY over the rows (fp64), or the batch-mean
+//     loss of the member (o = d_out; fp64 over its B rows).
+// Each wave sums one quantity: the kernel is a short chain of loads, and the
+// items of ten outputs run side by side instead of one after another (57 -> 13
+// us for 16 members with ten outputs).  The update right after the sum saves
+// the separate pass over the same parameters at the end of the step.
+// Workgroups from nsum on write the keep words of args.step.
+__global__ __launch_bounds__(256) void grad_sums_kernel(SumsArgs a, int nsum, int words_x) {
+  if ((int)blockIdx.x >= nsum) {  // uniform
+    const int b = blockIdx.x - nsum, x = b % words_x, kl = b / words_x;
+    const int k = a.members[kl % a.nmembers], l = kl / a.nmembers + 1;
+    write_keep_word(a.key0, a.key1, a.step, a.mem, k, l, (int64_t)x * 256 + threadIdx.x, a.Bp, a.B, a.A32, a.words);
+    return;
+  }
   const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (w >= ntiles) return;
-  const ColTile ct = tiles[w];
-  const MemberDev md = mem[ct.member];
+  if (w >= a.ntiles) return;
+  const ColTile ct = a.tiles[w];
+  const MemberDev md = a.mem[ct.member];
   const int lane = threadIdx.x & 63;
+  int64_t e;  // the parameter
+  float g;    // its gradient
+  bool bias = true;
   if (ct.part == kSumLoss) {
-    const int64_t r0 = (int64_t)ct.member * Bp;
-    const double s =
-        wave_sum_d(sum_in_order<double>(B - lane, 64, [&](int i) { return (double)rowloss[r0 + lane + 64 * i]; }));
-    if (lane == 0) loss_out[ct.member] = (float)(s / (double)B);
-    for (int o = 0; o < d_out; ++o) {
-      const double g = wave_sum_d(
-          sum_in_order<double>(B - lane, 64, [&](int i) { return (double)dY[(r0 + lane + 64 * i) * d_out + o]; }));
-      if (lane == 0) grad[md.b_out_off + o] = (float)g;
+    const int64_t r0 = (int64_t)ct.member * a.Bp;
+    const bool loss = ct.o == a.d_out;
+    const double s = wave_sum_d(sum_in_order<double>(a.B - lane, 64, [&](int i) {
+      const int64_t r = r0 + lane + 64 * i;
+      return loss ? (double)a.rowloss[r] : (double)a.dY[r * a.d_out + ct.o];
+    }));
+    if (lane != 0) return;
+    if (loss) {
+      a.loss_out[ct.member] = (float)(s / (double)a.B);
+      return;
     }
-    return;
-  }
-  const int c = ct.c0 + lane;
-  if (c >= md.dp) return;
-  if (ct.part == kSumHead) {
-    const int nrb = Bp / RB;
-    const float* pk = headpart + (int64_t)nrb * (d_out + 1) * (md.act_off / Bp);
-    for (int o = 0; o <= d_out; ++o) {
-      const float v =
-          sum_in_order<float>(nrb, 1, [&](int rb) { return pk[((int64_t)rb * (d_out + 1) + o) * md.dp + c]; });
-      if (o < d_out)
-        grad[md.w_out_off + (int64_t)o * md.dp + c] = v;
-      else
-        grad[md.b_last_off + c] = v;
+    e = md.b_out_off + ct.o;
+    g = (float)s;
+  } else {
+    const int c = ct.c0 + lane;
+    if (c >= md.dp) return;
+    if (ct.part == kSumHead) {
+      const int nrb = a.Bp / a.RB;
+      const float* pk = a.headpart + (int64_t)nrb * (a.d_out + 1) * (md.act_off / a.Bp);
+      g = sum_in_order<float>(nrb, 1, [&](int rb) { return pk[((int64_t)rb * (a.d_out + 1) + ct.o) * md.dp + c]; });
+      bias = ct.o == a.d_out;
+      e = (bias ? md.b_last_off : md.w_out_off + (int64_t)ct.o * md.dp) + c;
+    } else {
+      const float* p = a.colpart + ct.part * a.part_stride + md.act_off / kPartRows;
+      g = sum_in_order<float>(a.Bp / kPartRows, 1, [&](int r) { return p[(int64_t)r * md.dp + c]; });
+      e = a.bias_off[(int64_t)ct.part * a.K + ct.member] + c;
     }
-    return;
   }
-  const float* p = colpart + ct.part * part_stride + md.act_off / kPartRows;
-  grad[bias_off[(int64_t)ct.part * K + ct.member] + c] =
-      sum_in_order<float>(Bp / kPartRows, 1, [&](int r) { return p[(int64_t)r * md.dp + c]; });
+  a.grad[e] = g;
+  const float decay = bias && !a.decay_bias ? 1.0f : 1.0f - md.lr * md.wd;
+  float th = a.theta[e], m = a.m[e], v = a.v[e];
+  adamw_elem(th, g, m, v, decay, md.lr / a.adam.bc1, a.adam);
+  a.theta[e] = th;
+  a.m[e] = m;
+  a.v[e] = v;
 }
 
 // ----------------------------------------------------------------- gather --
 // H_0 of member k, row r: the feature row X[idx[k * B + r]] (or X[row_base + r]
 // for contiguous rows) in the GEMM precision, zero-padded to Pin columns; rows
-// r >= rows_valid are zero.  One wave per row, float4 reads.
+// r >= rows_valid are zero; an index outside [0, N) reads row 0.  One wave per
+// row, float4 reads.
 template <typename T>
-__global__ __launch_bounds__(256) void gather_kernel(const float* X, int d_in, int Pin, const int32_t* idx,
+__global__ __launch_bounds__(256) void gather_kernel(const float* X, int64_t N, int d_in, int Pin, const int32_t* idx,
                                                      int B, int64_t row_base, int rows_valid, int Bp, T* H0,
                                                      const int32_t* members) {
   const int k = members ? members[blockIdx.y] : (int)blockIdx.y;
@@ -419,7 +585,7 @@ __global__ __launch_bounds__(256) void gather_kernel(const float* X, int d_in, i
   if (r >= Bp) return;
   T* dst = H0 + ((int64_t)k * Bp + r) * Pin;
   const bool valid = r < rows_valid;
-  const int64_t src = valid ? (idx ? (int64_t)idx[(int64_t)k * B + r] : row_base + r) : 0;
+  const int64_t src = !valid ? 0 : idx ? (int64_t)checked_row(idx[(int64_t)k * B + r], N) : row_base + r;
   const float* x = X + src * d_in;
   const bool vec = (d_in % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0);
   // 1024 columns per round: the lane's four 16-byte loads are all issued
@@ -455,19 +621,13 @@ __global__ __launch_bounds__(256) void gather_kernel(const float* X, int d_in, i
 }
 
 // -------------------------------------------------------------- idx check --
-// The batch indices come from the caller: every entry outside [0, N) is
-// replaced by row 0 in the copy the step's kernels read, and flags bit 0 of
-// the status word, so that no kernel ever reads outside X or y.  The flag
-// store is predicated on a per-lane condition (a plain vector store; every
-// writer stores the same value).
+// The batch indices come from the caller: the kernels read row 0 in place of an
+// entry outside [0, N), and the head raises bit 0 of the status word.  The
+// entries of members that are not in the launches are looked at here.
 __global__ __launch_bounds__(256) void idx_check_kernel(const int32_t* __restrict__ idx, int64_t n, int64_t N,
-                                                        int32_t* __restrict__ out, uint32_t* status) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const int32_t v = idx[i];
-  const bool bad = v < 0 || (int64_t)v >= N;
-  out[i] = bad ? 0 : v;
-  if (bad) status[0] = 1u;
+                                                        uint32_t* status) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+    if (checked_row(idx[i], N) != idx[i]) status[0] = 1u;
 }
 
 // ----------------------------------------------------------- stream copy --
@@ -487,44 +647,6 @@ __global__ __launch_bounds__(256) void stream_copy_kernel(const f32x4* __restric
     for (int u = 0; u < 4; ++u) __builtin_nontemporal_store(v[u], dst + i + u * stride);
   }
   for (; i < n; i += stride) __builtin_nontemporal_store(__builtin_nontemporal_load(src + i), dst + i);
-}
-
-// ------------------------------------------------------------------ AdamW --
-// One wave per 256-element chunk of the packed parameter buffer; every chunk
-// belongs to one member and is all-weight or all-bias, so (lr_k, wd_k) and the
-// decay switch are wave-uniform.  float4 loads/stores, 30 bytes per element
-// with the bf16 shadow.
-template <bool SHADOW>
-__global__ __launch_bounds__(256) void adamw_kernel(float* theta, const float* grad, float* m,
-                                                    float* v, uint16_t* shadow,
-                                                    const uint32_t* chunk_tab, const uint32_t* list,
-                                                    const MemberDev* mem, int64_t nchunks, AdamConst ac) {
-  const int lane = threadIdx.x & 63;
-  const int64_t nw = (int64_t)gridDim.x * 4;
-  const int64_t w0 = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int64_t w = w0; w < nchunks; w += nw) {
-    const int64_t c = list ? (int64_t)list[w] : w;
-    const uint32_t e = chunk_tab[c];
-    const MemberDev md = mem[e & 0x7FFFFFFFu];
-    const float decay = (e >> 31) ? 1.0f : 1.0f - md.lr * md.wd;
-    const float step = md.lr / ac.bc1;
-    const int64_t i = c * kChunk + lane * 4;
-    f32x4 th = *reinterpret_cast<const f32x4*>(theta + i);
-    const f32x4 g = *reinterpret_cast<const f32x4*>(grad + i);
-    f32x4 mm = *reinterpret_cast<const f32x4*>(m + i);
-    f32x4 vv = *reinterpret_cast<const f32x4*>(v + i);
-    adamw_vec4(th, g, mm, vv, decay, step, ac);
-    *reinterpret_cast<f32x4*>(theta + i) = th;
-    *reinterpret_cast<f32x4*>(m + i) = mm;
-    *reinterpret_cast<f32x4*>(v + i) = vv;
-    if (SHADOW) {
-      uint32_t lo = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)th[0]) |
-                    ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)th[1]) << 16);
-      uint32_t hi = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)th[2]) |
-                    ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)th[3]) << 16);
-      *reinterpret_cast<u32x2*>(shadow + i) = u32x2{lo, hi};
-    }
-  }
 }
 
 // xb row r = X row r in bf16, zero-padded from d_in to Pin columns: one
@@ -584,23 +706,30 @@ __device__ __forceinline__ uint32_t keep_word(uint32_t key0, uint32_t key1, uint
   return w;
 }
 
-// Keep words of every hidden layer of every member for one training step:
+// Keep word w of layer l of member k for one training step:
 // word (rb, c) of layer l, member k at out[(l-1)*A32 + act_off/32 + rb*dp + c].
 // Rows >= rows_valid and columns >= width get 0 (the epilogue zeroes them).
-__global__ __launch_bounds__(256) void dropout_words_kernel(uint32_t key0, uint32_t key1, uint32_t step,
-                                                            const MemberDev* mem, int Bp, int rows_valid,
-                                                            int64_t A32, uint32_t* out, const int32_t* members) {
-  const int k = members ? members[blockIdx.y] : (int)blockIdx.y, l = blockIdx.z + 1;
+__device__ __forceinline__ void write_keep_word(uint32_t key0, uint32_t key1, uint32_t step, const MemberDev* mem,
+                                                int k, int l, int64_t w, int Bp, int rows_valid, int64_t A32,
+                                                uint32_t* out) {
   const MemberDev md = mem[k];
   if (l > md.depth) return;  // the member has no layer l
   const int64_t nw = (int64_t)(Bp / 32) * md.dp;
-  const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (w >= nw) return;
   const int rb = (int)(w / md.dp), c = (int)(w % md.dp);
   uint32_t word = 0;
   if (rb * 32 < rows_valid && c < md.width)
     word = md.drop_t == 0u ? ~0u : keep_word(key0, key1, step, ((uint32_t)k << 8) | (uint32_t)l, rb, c, md.drop_t);
   out[(int64_t)(l - 1) * A32 + md.act_off / 32 + w] = word;
+}
+
+// Keep words of every hidden layer of every member.
+__global__ __launch_bounds__(256) void dropout_words_kernel(uint32_t key0, uint32_t key1, uint32_t step,
+                                                            const MemberDev* mem, int Bp, int rows_valid,
+                                                            int64_t A32, uint32_t* out, const int32_t* members) {
+  const int k = members ? members[blockIdx.y] : (int)blockIdx.y;
+  write_keep_word(key0, key1, step, mem, k, blockIdx.z + 1, (int64_t)blockIdx.x * 256 + threadIdx.x, Bp, rows_valid,
+                  A32, out);
 }
 
 // Test hook: the keep mask of one (layer, member) as bytes [B, width].
@@ -773,18 +902,20 @@ namespace {
 template <typename T, int MODE, int D>
 void head_fwd_t(dim3 grid, hipStream_t s, Task task, const void* H, const float* theta, const MemberDev* mem,
                 int Bp, int d_out, const void* y, const int32_t* idx, int B, int rows_valid, int64_t row_base,
-                int64_t Nv, float* dY, float* rowloss, float* pred, const int32_t* members) {
+                int64_t Nv, float* dY, float* rowloss, float* pred, uint32_t* status, const int32_t* members) {
   hipLaunchKernelGGL((head_fwd_kernel<T, MODE, D>), grid, dim3(256), 0, s, task, static_cast<const T*>(H), theta,
-                     mem, Bp, d_out, y, idx, B, rows_valid, row_base, Nv, dY, rowloss, pred, members);
+                     mem, Bp, d_out, y, idx, B, rows_valid, row_base, Nv, dY, rowloss, pred, status,
+                     members);
 }
 
 template <typename T, int MODE>
 void head_fwd_d(int d_out, dim3 grid, hipStream_t s, Task task, const void* H, const float* theta,
                 const MemberDev* mem, int Bp, const void* y, const int32_t* idx, int B, int rows_valid,
-                int64_t row_base, int64_t Nv, float* dY, float* rowloss, float* pred, const int32_t* members) {
+                int64_t row_base, int64_t Nv, float* dY, float* rowloss, float* pred, uint32_t* status,
+                const int32_t* members) {
 #define TABPACK_HEAD_FWD(DD)                                                                                   \
   head_fwd_t<T, MODE, DD>(grid, s, task, H, theta, mem, Bp, d_out, y, idx, B, rows_valid, row_base, Nv, dY, \
-                          rowloss, pred, members)
+                          rowloss, pred, status, members)
   if (d_out <= 1) TABPACK_HEAD_FWD(1);
   else if (d_out <= 2) TABPACK_HEAD_FWD(2);
   else if (d_out <= 4) TABPACK_HEAD_FWD(4);
@@ -798,14 +929,16 @@ void head_fwd_d(int d_out, dim3 grid, hipStream_t s, Task task, const void* H, c
 hipError_t launch_head_fwd(Prec prec, Task task, int mode, const void* H, const float* theta,
                            const MemberDev* mem, int K, int Bp, int d_out, const void* y,
                            const int32_t* idx, int B, int rows_valid, int64_t row_base, int64_t Nv,
-                           float* dY, float* rowloss, float* pred, const int32_t* members, hipStream_t s) {
+                           float* dY, float* rowloss, float* pred, uint32_t* status, const int32_t* members,
+                           hipStream_t s) {
   if (Bp % 32 != 0 || d_out < 1 || d_out > kMaxOut || mode < kHeadTrain || mode > kHeadPredict)
     return hipErrorInvalidValue;
+  if (mode == kHeadTrain && !status) return hipErrorInvalidValue;
   if (K <= 0) return hipSuccess;
   const dim3 grid(Bp / 32, K);
 #define TABPACK_HEAD_FWD_MODE(TT, MM)                                                                         \
   head_fwd_d<TT, MM>(d_out, grid, s, task, H, theta, mem, Bp, y, idx, B, rows_valid, row_base, Nv, dY, rowloss, \
-                     pred, members)
+                     pred, status, members)
   if (prec == Prec::BF16) {
     if (mode == kHeadTrain) TABPACK_HEAD_FWD_MODE(__bf16, kHeadTrain);
     else if (mode == kHeadEval) TABPACK_HEAD_FWD_MODE(__bf16, kHeadEval);
@@ -851,34 +984,66 @@ hipError_t launch_head_bwd(Prec prec, const void* H, const float* theta, const M
 }
 
 
-hipError_t launch_grad_sums(const float* colpart, int64_t part_stride, const float* headpart, int RB,
-                            const float* rowloss, const float* dY, const MemberDev* mem, const ColTile* tiles,
-                            int ntiles, int Bp, int B, int d_out, const int64_t* bias_off, int K, float* grad,
-                            float* loss_out, hipStream_t s) {
-  if (RB <= 0 || Bp % RB != 0 || Bp % kPartRows != 0) return hipErrorInvalidValue;
-  if (ntiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(grad_sums_kernel, dim3((ntiles + 3) / 4), dim3(256), 0, s, colpart, part_stride, headpart, RB,
-                     rowloss, dY, mem, tiles, ntiles, Bp, B, d_out, bias_off, K, grad, loss_out);
+namespace {
+template <typename T>
+void head_train_d(int d_out, dim3 grid, hipStream_t s, Task task, const void* H, const float* theta,
+                  const MemberDev* mem, int Bp, const void* y, int64_t N, const int32_t* idx, int B, float* dY,
+                  float* rowloss, void* dZ, float* part, uint32_t* status, const int32_t* members) {
+#define TABPACK_HEAD_TRAIN(DD)                                                                                 \
+  hipLaunchKernelGGL((head_train_kernel<T, DD>), grid, dim3(256), 0, s, task, static_cast<const T*>(H), theta, \
+                     mem, Bp, d_out, y, N, idx, B, dY, rowloss, static_cast<T*>(dZ), part, status, members)
+  if (d_out <= 1) TABPACK_HEAD_TRAIN(1);
+  else if (d_out <= 2) TABPACK_HEAD_TRAIN(2);
+  else if (d_out <= 4) TABPACK_HEAD_TRAIN(4);
+  else if (d_out <= 8) TABPACK_HEAD_TRAIN(8);
+  else TABPACK_HEAD_TRAIN(16);
+#undef TABPACK_HEAD_TRAIN
+}
+}  // namespace
+
+hipError_t launch_head_train(Prec prec, Task task, const void* H, const float* theta, const MemberDev* mem, int K,
+                             int Bp, int d_out, const void* y, int64_t N, const int32_t* idx, int B, float* dY,
+                             float* rowloss, void* dZ, float* part, uint32_t* status, const int32_t* members,
+                             hipStream_t s) {
+  if (Bp % kHeadRows != 0 || d_out < 1 || d_out > kMaxOut || !status) return hipErrorInvalidValue;
+  if (K <= 0) return hipSuccess;
+  const dim3 grid(Bp / kHeadRows, K);
+  if (prec == Prec::BF16)
+    head_train_d<__bf16>(d_out, grid, s, task, H, theta, mem, Bp, y, N, idx, B, dY, rowloss, dZ, part, status,
+                         members);
+  else
+    head_train_d<float>(d_out, grid, s, task, H, theta, mem, Bp, y, N, idx, B, dY, rowloss, dZ, part, status,
+                        members);
   return hipGetLastError();
 }
 
-hipError_t launch_gather(Prec prec, const float* X, int d_in, int Pin, const int32_t* idx, int B,
+hipError_t launch_grad_sums(const SumsArgs& a, hipStream_t s) {
+  if (a.RB <= 0 || a.Bp % a.RB != 0 || a.Bp % kPartRows != 0) return hipErrorInvalidValue;
+  const int nsum = (a.ntiles + 3) / 4;
+  const int64_t words_x = a.words ? ((int64_t)(a.Bp / 32) * a.max_dp + 255) / 256 : 0;
+  const int64_t grid = nsum + words_x * a.nmembers * a.L;
+  if (grid <= 0) return hipSuccess;
+  if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(grad_sums_kernel, dim3((unsigned)grid), dim3(256), 0, s, a, nsum, (int)words_x);
+  return hipGetLastError();
+}
+
+hipError_t launch_gather(Prec prec, const float* X, int64_t N, int d_in, int Pin, const int32_t* idx, int B,
                          int64_t row_base, int rows_valid, int members, int Bp, void* H0,
                          const int32_t* member_ids, hipStream_t s) {
   if (members <= 0) return hipSuccess;
   const dim3 grid((Bp + 3) / 4, members);
   if (prec == Prec::BF16)
-    hipLaunchKernelGGL((gather_kernel<__bf16>), grid, dim3(256), 0, s, X, d_in, Pin, idx, B, row_base,
+    hipLaunchKernelGGL((gather_kernel<__bf16>), grid, dim3(256), 0, s, X, N, d_in, Pin, idx, B, row_base,
                        rows_valid, Bp, static_cast<__bf16*>(H0), member_ids);
   else
-    hipLaunchKernelGGL((gather_kernel<float>), grid, dim3(256), 0, s, X, d_in, Pin, idx, B, row_base,
+    hipLaunchKernelGGL((gather_kernel<float>), grid, dim3(256), 0, s, X, N, d_in, Pin, idx, B, row_base,
                        rows_valid, Bp, static_cast<float*>(H0), member_ids);
   return hipGetLastError();
 }
 
-hipError_t launch_idx_check(const int32_t* idx, int64_t n, int64_t N, int32_t* out, uint32_t* status,
-                            hipStream_t s) {
-  hipLaunchKernelGGL(idx_check_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, idx, n, N, out, status);
+hipError_t launch_idx_check(const int32_t* idx, int64_t n, int64_t N, uint32_t* status, hipStream_t s) {
+  hipLaunchKernelGGL(idx_check_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, idx, n, N, status);
   return hipGetLastError();
 }
 
@@ -887,21 +1052,6 @@ hipError_t launch_stream_copy(const void* src, void* dst, int64_t n16, hipStream
   const int64_t blocks = std::min<int64_t>(grid_for(n16, 256), 256 * 8);
   hipLaunchKernelGGL(stream_copy_kernel, dim3(blocks), dim3(256), 0, s, static_cast<const f32x4*>(src),
                      static_cast<f32x4*>(dst), n16);
-  return hipGetLastError();
-}
-
-hipError_t launch_adamw(Prec prec, float* theta, const float* grad, float* m, float* v,
-                        uint16_t* shadow, const uint32_t* chunk_tab, const uint32_t* list,
-                        const MemberDev* mem, int64_t nchunks, const AdamConst& ac, hipStream_t s) {
-  if (nchunks <= 0) return hipSuccess;
-  const int grid = grid_for(nchunks, 4);
-  (void)prec;
-  if (shadow)
-    hipLaunchKernelGGL((adamw_kernel<true>), dim3(grid), dim3(256), 0, s, theta, grad, m, v, shadow,
-                       chunk_tab, list, mem, nchunks, ac);
-  else
-    hipLaunchKernelGGL((adamw_kernel<false>), dim3(grid), dim3(256), 0, s, theta, grad, m, v, shadow,
-                       chunk_tab, list, mem, nchunks, ac);
   return hipGetLastError();
 }
 

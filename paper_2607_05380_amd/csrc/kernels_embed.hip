@@ -12,6 +12,7 @@
 // reduces dE = dZ_1 W_1 in its epilogue (fp32 accumulators) into
 // per-64-row-block sums of the four gradient terms; embed_grad_kernel adds the
 // blocks.
+#include "adamw.h"
 #include "pack_internal.h"
 
 namespace tabpack {
@@ -68,9 +69,11 @@ __global__ __launch_bounds__(256) void embed_table_kernel(int d_in, const Member
 // GEMM: its epilogue leaves, per member, real column and 64-row block pb, the
 // four sums over the block's rows (alpha, beta, w, b terms) at
 // part[e_act / 16 + (pb * 4 + q) * p_in + col]; here they are added over the
-// blocks in block order.  One thread per (column, member).
+// blocks in block order (4 blocks' terms fetched before they are added), and
+// the parameters take their AdamW step.  One thread per (column, member).
 __global__ __launch_bounds__(256) void embed_grad_kernel(int d_in, int nblk, const MemberDev* mem,
-                                                         const int32_t* members, const float* part, float* grad) {
+                                                         const int32_t* members, const float* part, float* grad,
+                                                         float* theta, float* m, float* v, AdamConst adam) {
   const int k = members[blockIdx.y];
   const MemberDev md = mem[k];
   const int col = blockIdx.x * 256 + threadIdx.x;
@@ -79,16 +82,34 @@ __global__ __launch_bounds__(256) void embed_grad_kernel(int d_in, int nblk, con
   if (i >= d_in || j >= md.d_emb) return;  // padding column
   const float* p = part + md.e_act / 16 + col;
   float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int pb = 0; pb < nblk; ++pb)
+  for (int pb = 0; pb < nblk; pb += 4) {
+    float t[4][4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) s[q] += p[(int64_t)(pb * 4 + q) * md.p_in];
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) t[u][q] = pb + u < nblk ? p[(int64_t)((pb + u) * 4 + q) * md.p_in] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (pb + u < nblk) s[q] += t[u][q];
+  }
+  const float decay = 1.0f - md.lr * md.wd, step = md.lr / adam.bc1;
+  auto update = [&](int64_t e, float g) {
+    grad[e] = g;
+    float th = theta[e], mm = m[e], vv = v[e];
+    adamw_elem(th, g, mm, vv, decay, step, adam);
+    theta[e] = th;
+    m[e] = mm;
+    v[e] = vv;
+  };
   const int64_t ai = (int64_t)i * md.d_emb + j;
-  grad[md.e_a + ai] = s[0];
-  grad[md.e_be + ai] = s[1];
+  update(md.e_a + ai, s[0]);
+  update(md.e_be + ai, s[1]);
   if (j > 0) {
     const int64_t wi = (int64_t)i * (md.d_emb - 1) + j - 1;
-    grad[md.e_w + wi] = s[2];
-    grad[md.e_b + wi] = s[3];
+    update(md.e_w + wi, s[2]);
+    update(md.e_b + wi, s[3]);
   }
 }
 
@@ -106,11 +127,12 @@ hipError_t launch_embed_table(Prec prec, int d_in, const MemberDev* mem, const i
 }
 
 hipError_t launch_embed_grad(int d_in, int Bp, const MemberDev* mem, const int32_t* members, int nmembers,
-                             int max_pin, const float* part, float* grad, hipStream_t s) {
+                             int max_pin, const float* part, float* grad, float* theta, float* m, float* v,
+                             const AdamConst& adam, hipStream_t s) {
   if (nmembers <= 0 || max_pin <= 0) return hipSuccess;
   if (Bp % 64) return hipErrorInvalidValue;
   hipLaunchKernelGGL(embed_grad_kernel, dim3((max_pin + 255) / 256, nmembers), dim3(256), 0, s, d_in, Bp / 64, mem,
-                     members, part, grad);
+                     members, part, grad, theta, m, v, adam);
   return hipGetLastError();
 }
 

@@ -391,7 +391,7 @@ struct DmaKmaj {
   int kofs[2];         // depth offset (elements) of this lane's vector per block parity
   int wave;
   // rows != nullptr: row r < nrows of the operand is row rows[r] of P (src_rows
-  // rows), rows >= nrows read as zero
+  // rows; checked), rows >= nrows read as zero
   __device__ void init(const __bf16* P, int64_t ld, int row0, int rbound, int, int wave_, int lane,
                        const int32_t* rows = nullptr, int nrows = 0, int64_t src_rows = 0) {
     rsrc = make_rsrc(P, (rows ? src_rows : (int64_t)rbound) * ld * 2);
@@ -406,7 +406,7 @@ struct DmaKmaj {
     for (int p = 0; p < PER; ++p) {
       const int row = row0 + (wave * PER + p) * BR + r;
       if (rows)
-        voff[p] = row < nrows ? (uint32_t)(((int64_t)rows[row] * ld + kofs[p & 1]) * 2) : kOob;
+        voff[p] = row < nrows ? (uint32_t)(((int64_t)checked_row(rows[row], src_rows) * ld + kofs[p & 1]) * 2) : kOob;
       else
         voff[p] = row < rbound ? (uint32_t)(((int64_t)row * ld + kofs[p & 1]) * 2) : kOob;
     }
@@ -569,8 +569,9 @@ struct EmbRowsProducer {
     for (int i = 0; i < NR; ++i) {
       const int r = t.m0 + rl0 + RS * i;
       const int64_t row =
-          r < a.rows_valid ? (a.emb_idx ? (int64_t)a.emb_idx[(int64_t)d.member * a.rows_valid + r] : a.emb_row_base + r)
-                           : 0;
+          r >= a.rows_valid ? 0
+          : a.emb_idx       ? (int64_t)checked_row(a.emb_idx[(int64_t)d.member * a.rows_valid + r], a.emb_x_rows)
+                            : a.emb_row_base + r;
       xrow[i] = a.emb_x + row * a.emb_d_in;
     }
   }
@@ -1518,7 +1519,10 @@ __device__ __forceinline__ void epilogue_de(const GemmArgs& a, const GemmDesc& d
   const int nf = min(d_in - 1, (min(t.n0 + TM, ncol) - 1) / dp) - i0 + 1;
   if (tid < TM) {
     const int r = t.m0 + tid;
-    rowoff[tid] = r < a.rows_valid ? (int64_t)a.emb_idx[(int64_t)d.member * a.rows_valid + r] * d_in : -1;
+    rowoff[tid] =
+        r < a.rows_valid
+            ? (int64_t)checked_row(a.emb_idx[(int64_t)d.member * a.rows_valid + r], a.emb_x_rows) * d_in
+            : -1;
   }
   __syncthreads();
   for (int e = tid; e < TM * nf; e += NT) {
@@ -1621,13 +1625,15 @@ __device__ __forceinline__ void run_tile(const GemmArgs& a, const GemmDesc& d, c
     constexpr int PS = LA::type::PER + LB::type::PER;  // direct loads per wave per K step
     const int nk = (d.Kd + BKE - 1) / BKE;
     if constexpr (AK == OP_KMAJ && (EPI == EPI_FWD || EPI == EPI_FWD_EVAL))
-      la.init(static_cast<const T*>(d.A), d.lda, t.m0, d.M, d.Kd, wave, lane, d.xrows, d.xrows_n, d.xsrc_rows);
+      la.init(static_cast<const T*>(d.A), d.lda, t.m0, d.M, d.Kd, wave, lane,
+              d.xrows_n > 0 ? a.idx + (int64_t)d.member * d.xrows_n : nullptr, d.xrows_n, d.xsrc_rows);
     else
       la.init(static_cast<const T*>(d.A), d.lda, t.m0, d.M, d.Kd, wave, lane);
     if constexpr (BK_ == OP_RMAJ && EPI == EPI_DW) {
-      if (d.xrows) {  // the batch rows' row numbers, for every K step's loads (one table per tile)
+      if (d.xrows_n > 0) {  // the batch rows' row numbers, for every K step's loads (one table per tile)
         lds_i32* m = (lds_i32*)xmap;
-        for (int i = tid; i < d.xrows_n; i += NT) m[i] = d.xrows[i];
+        const int32_t* rows = a.idx + (int64_t)d.member * d.xrows_n;
+        for (int i = tid; i < d.xrows_n; i += NT) m[i] = checked_row(rows[i], d.xsrc_rows);
         __syncthreads();
         lb.init(static_cast<const T*>(d.B), d.ldb, t.n0, d.N, d.Kd, wave, lane, m, d.xrows_n, d.xsrc_rows);
       } else {
@@ -1747,7 +1753,8 @@ __device__ __forceinline__ void run_tile_emb(const GemmArgs& a, const GemmDesc& 
     ep.init(a, d, t, tid);
   } else {  // the batch rows' data rows, for every K step's x loads (one table per tile)
     lds_i32* m = (lds_i32*)xmap;
-    for (int i = tid; i < d.xrows_n; i += NT) m[i] = d.xrows[i];
+    const int32_t* rows = a.emb_idx + (int64_t)d.member * d.xrows_n;
+    for (int i = tid; i < d.xrows_n; i += NT) m[i] = checked_row(rows[i], a.emb_x_rows);
     __syncthreads();
     ep.init(a, d, t, tid, m, d.xrows_n);
   }

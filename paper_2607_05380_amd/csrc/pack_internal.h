@@ -10,7 +10,7 @@ struct pack_handle;  // the library handle (include/tabpack.h)
 
 namespace tabpack {
 
-constexpr int kChunk = 256;        // AdamW chunk: elements of one member, one kind (weight / bias)
+constexpr int kChunk = 256;        // every tensor of the packed buffers starts on a multiple of this
 constexpr int kMaxOut = 16;        // largest head width d_out supported by the head kernels
 constexpr int kRowAlign = 256;     // base-batch rows are padded to a multiple of this (largest GEMM row tile)
 constexpr uint32_t kTagDropout = 3;
@@ -72,14 +72,14 @@ struct GemmDesc {
   int64_t poff;        // EPI_DW with fused AdamW, EPI_NS with the Muon update: element offset of the weight tensor
   const void* Y;       // EPI_NS: the matrix added to the product (GEMM precision), or nullptr
   int64_t ldy;
-  // bf16 only: the batch rows of the operand that holds the data, taken
-  // straight from a bf16 copy of X (xsrc_rows rows): when xrows is set, batch
-  // row r < xrows_n is row xrows[r] of that copy, rows >= xrows_n read as
-  // zero.  EPI_FWD: the rows of A (depth-contiguous, lda); EPI_DW: the depth
-  // rows of B (rows-contiguous, ldb), at most kMapRows of them.  The embedded
-  // first layer's weight gradient (B = OP_EMB, bf16 or fp32) takes its batch
-  // rows' data rows from xrows the same way.
-  const int32_t* xrows;
+  // The batch rows of the operand that holds the data, taken straight from a
+  // copy of X (xsrc_rows rows): when xrows_n > 0, batch row r < xrows_n is row
+  // idx[member * xrows_n + r] of that copy (GemmArgs::idx; row 0 in place of an
+  // index outside it), rows >= xrows_n read as zero.  EPI_FWD (bf16): the rows
+  // of A (depth-contiguous, lda); EPI_DW (bf16): the depth rows of B
+  // (rows-contiguous, ldb), at most kMapRows of them.  The embedded first
+  // layer's weight gradient (B = OP_EMB, bf16 or fp32) takes its batch rows'
+  // data rows the same way.
   int32_t xrows_n;
   int64_t xsrc_rows;
   // EPI_DW with fused AdamW: the rows r >= opt_rows (past the member's true
@@ -109,12 +109,16 @@ struct AdamConst {
   float bc2_sqrt;    // sqrt(1 - beta2^t)
 };
 
+// A batch index as the kernels use it: row 0 in place of one outside [0, n).
+__device__ __forceinline__ int32_t checked_row(int32_t v, int64_t n) { return v >= 0 && v < n ? v : 0; }
+
 struct GemmArgs {
   const GemmDesc* descs;
   const Tile* tiles;
   int32_t ntiles;
   int32_t layer;        // 1-based hidden layer (dropout counter)
   int32_t rows_valid;   // batch rows that exist (B in training, chunk rows in eval)
+  const int32_t* idx;   // the step's batch indices [K, B] as the caller gave them (checked where they are used)
   uint32_t key0, key1;  // dropout stream key
   uint32_t step;        // dropout counter word
   const void* zeros;    // >= 16 bytes of zeros in device memory (source for out-of-range elements)
@@ -156,14 +160,12 @@ struct GemmArgs {
   // batch row r is emb_x[row * emb_d_in + feature].  Forward: row =
   // emb_idx[member * rows_valid + r] (training) or emb_row_base + r
   // (emb_idx == nullptr: evaluation and prediction), for r < rows_valid.
-  // Weight gradient: row = desc.xrows[r] for r < desc.xrows_n.  emb_x has
-  // emb_x_rows rows.
+  // Weight gradient: row = emb_idx[member * xrows_n + r] for r < desc.xrows_n.
+  // emb_x has emb_x_rows rows; an index outside them reads row 0.
   const float4* emb_tab;
   int64_t emb_row_base;
   int64_t emb_x_rows;
 };
-
-// AdamW constants of one step.
 
 // Per-member table used by the small kernels.
 struct MemberDev {
@@ -174,7 +176,7 @@ struct MemberDev {
   int64_t act_off;          // member offset inside one activation buffer (elements)
   int64_t w_out_off, b_out_off, b_last_off;  // head weight, head bias, last hidden bias (elements of theta)
   int64_t h_last;           // the member's last hidden activation H_depth: offset from the start of H_1 (elements)
-  int64_t dz_last;          // its gradient dZ_depth: offset from the start of the dZ ping-pong pair (elements)
+  int64_t dz_last;          // its gradient dZ_depth: offset from the start of the dZ buffers (elements)
   int32_t depth;            // hidden blocks of the member
   int32_t d_emb;            // periodic embedding size per feature (0: no embedding)
   // periodic embeddings: offsets (elements of theta / grad) of w, b [d_in, d_emb-1]
@@ -217,8 +219,9 @@ struct ColTile {            // (member, first column, kind) work item of the gra
   int32_t member;
   int32_t c0;
   int32_t part;             // >= 0: b_{part + 1} from the partials of the dX launch of layer part + 2;
-                            // kSumHead: W_out and b_L from the head backward's partials;
-                            // kSumLoss: the member's batch-mean loss and b_out (c0 = 0)
+                            // kSumHead: output o of W_out, or b_L (o = d_out), from the head's partials;
+                            // kSumLoss: b_out[o], or the member's batch-mean loss (o = d_out) (c0 = 0)
+  int32_t o;
 };
 constexpr int32_t kSumHead = -1, kSumLoss = -2;
 
@@ -228,11 +231,13 @@ hipError_t launch_gemm(Prec prec, OpKind a, OpKind b, EpiKind e, const GemmArgs&
 // Head forward modes: training loss and dY / score-ready eval value / all prediction values.
 constexpr int kHeadTrain = 0, kHeadEval = 1, kHeadPredict = 2;
 
-// Launchers (kernels_aux.hip).
+// Launchers (kernels_aux.hip).  Training: Nv is the number of data rows N; an
+// index outside [0, N) takes the target of row 0 and sets status[0] = 1.
 hipError_t launch_head_fwd(Prec prec, Task task, int mode, const void* H, const float* theta,
                            const MemberDev* mem, int K, int Bp, int d_out, const void* y,
                            const int32_t* idx, int B, int rows_valid, int64_t row_base, int64_t Nv,
-                           float* dY, float* rowloss, float* pred, const int32_t* members, hipStream_t s);
+                           float* dY, float* rowloss, float* pred, uint32_t* status, const int32_t* members,
+                           hipStream_t s);
 hipError_t launch_head_bwd(Prec prec, const void* H, const float* theta, const MemberDev* mem,
                            const HeadTile* tiles, int ntiles, int Bp, int RB, int d_out, const float* dY,
                            void* dZ, float* part, hipStream_t s);
@@ -245,28 +250,50 @@ int select_with_scratch(pack_handle* h, const float* cand, const void* yv, int32
                         hipStream_t stream);
 // Sets the library's last error message; returns code.
 int set_error(int code, const char* msg);
+// The training head of small packs in one kernel (32 rows a workgroup): the
+// rows' loss and dY, then dZ_L and the row block's partial sums (kHeadRows rows
+// per block), as launch_head_fwd and launch_head_bwd leave them.
+constexpr int kHeadRows = 32;
+hipError_t launch_head_train(Prec prec, Task task, const void* H, const float* theta, const MemberDev* mem, int K,
+                             int Bp, int d_out, const void* y, int64_t N, const int32_t* idx, int B, float* dY,
+                             float* rowloss, void* dZ, float* part, uint32_t* status, const int32_t* members,
+                             hipStream_t s);
 // The gradient sums of one member group after its last backward launch (one
-// wave per ColTile): hidden-layer bias gradients from the dX epilogues'
-// partials (bias layer j at colpart + j * part_stride), the head weight and
-// last hidden bias gradients from the head backward's partials (RB rows per
-// block), and each member's loss (loss_out) and head-bias gradient from the
-// per-row losses and dY.  Fixed summation orders.
-hipError_t launch_grad_sums(const float* colpart, int64_t part_stride, const float* headpart, int RB,
-                            const float* rowloss, const float* dY, const MemberDev* mem, const ColTile* tiles,
-                            int ntiles, int Bp, int B, int d_out, const int64_t* bias_off, int K, float* grad,
-                            float* loss_out, hipStream_t s);
-hipError_t launch_gather(Prec prec, const float* X, int d_in, int Pin, const int32_t* idx, int B,
+// wave per ColTile), each followed by the AdamW update of the parameters whose
+// gradient it is: hidden-layer bias gradients from the dX epilogues' partials
+// (bias layer j at colpart + j * part_stride), the head weight and last hidden
+// bias gradients from the head backward's partials (RB rows per block), and
+// each member's loss (loss_out) and head-bias gradient from the per-row losses
+// and dY.  Fixed summation orders.  With words set, further workgroups of the
+// launch write the dropout keep words of `step` (as launch_dropout_words does).
+struct SumsArgs {
+  const float* colpart;
+  int64_t part_stride;
+  const float* headpart;
+  int32_t RB;
+  const float *rowloss, *dY;
+  const MemberDev* mem;
+  const ColTile* tiles;
+  int32_t ntiles, Bp, B, d_out, K;
+  const int64_t* bias_off;
+  float *grad, *theta, *m, *v, *loss_out;
+  AdamConst adam;
+  int32_t decay_bias;
+  uint32_t* words;
+  uint32_t key0, key1, step;
+  int32_t L, max_dp, nmembers;
+  int64_t A32;
+  const int32_t* members;
+};
+hipError_t launch_grad_sums(const SumsArgs& a, hipStream_t s);
+// (an index outside [0, N) gathers row 0)
+hipError_t launch_gather(Prec prec, const float* X, int64_t N, int d_in, int Pin, const int32_t* idx, int B,
                          int64_t row_base, int rows_valid, int members, int Bp, void* H0,
                          const int32_t* member_ids, hipStream_t s);
-// out[i] = idx[i], or 0 with status[0] = 1 where idx[i] lies outside [0, N)
-hipError_t launch_idx_check(const int32_t* idx, int64_t n, int64_t N, int32_t* out, uint32_t* status,
-                            hipStream_t s);
+// status[0] = 1 where idx[i] lies outside [0, N), i < n
+hipError_t launch_idx_check(const int32_t* idx, int64_t n, int64_t N, uint32_t* status, hipStream_t s);
 // dst <- src, n16 16-byte vectors, non-temporal loads and stores
 hipError_t launch_stream_copy(const void* src, void* dst, int64_t n16, hipStream_t s);
-// shadow: where the bf16 copy of the updated parameters goes, or nullptr for none
-hipError_t launch_adamw(Prec prec, float* theta, const float* grad, float* m, float* v,
-                        uint16_t* shadow, const uint32_t* chunk_tab, const uint32_t* list,
-                        const MemberDev* mem, int64_t nchunks, const AdamConst& ac, hipStream_t s);
 hipError_t launch_to_shadow(const float* theta, uint16_t* shadow, int64_t n, hipStream_t s);
 // xb[r][c] = bf16(X[r][c]) for c < d_in, 0 for d_in <= c < Pin; N rows
 hipError_t launch_rows_to_bf16(const float* X, int64_t N, int d_in, int Pin, void* xb, hipStream_t s);
@@ -277,9 +304,10 @@ hipError_t launch_rows_to_bf16(const float* X, int64_t N, int d_in, int Pin, voi
 hipError_t launch_embed_table(Prec prec, int d_in, const MemberDev* mem, const int32_t* members, int nmembers,
                               int max_pin, const float* theta, float4* tab, hipStream_t s);
 // grad of w, b, alpha, beta from the EPI_DE partial sums (in the dE buffer at
-// each member's e_act / 16: [Bp / 64][4][p_in])
+// each member's e_act / 16: [Bp / 64][4][p_in]), and their AdamW update
 hipError_t launch_embed_grad(int d_in, int Bp, const MemberDev* mem, const int32_t* members, int nmembers,
-                             int max_pin, const float* part, float* grad, hipStream_t s);
+                             int max_pin, const float* part, float* grad, float* theta, float* m, float* v,
+                             const AdamConst& adam, hipStream_t s);
 // members: the K member ids whose rows of pred are scored (nullptr: 0 .. K-1)
 hipError_t launch_eval_score(Task task, const float* pred, const void* yv, int K, int64_t Nv,
                              double* score_out, const int32_t* members, hipStream_t s);

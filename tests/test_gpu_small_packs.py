@@ -1,9 +1,11 @@
-"""Small launches: the 64 x 64 GEMM tiles give the results of the 128 x 128 ones."""
+"""Small packs: the 64 x 64 GEMM tiles give the results of the 128 x 128 ones, the one-stream step those of the step on
+several streams, and the fused training head those of the oracle."""
 import numpy as np
 import pytest
 
-from paper_2607_05380_amd import configs, tabpack
-from parity import make_inputs, to_dev
+from oracle.pack import OraclePack
+from paper_2607_05380_amd import configs, synth, tabpack
+from parity import TOL, check_tensor, compare_member, make_inputs, oracle_cfg, oracle_hparams, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -47,5 +49,85 @@ def test_mini_tiles_bit_identical(monkeypatch, name, over):
         got += [t.cpu().numpy() for t in pk.eval_members(Xv, yv)] + [pk.predict(Xv).cpu().numpy()]
         runs.append(got + state(pk, cfg.get("keep_grads", 1)))
     assert len(runs[0]) == len(runs[1])
+    for a, b in zip(*runs):
+        np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("name,over", [
+    ("regression_onehot", dict(B=300)),
+    ("multiclass_lognormal", dict(B=200, d_in=24, L=1)),
+    ("binary_small", dict(optimizer="muon", L=3)),
+    ("binary_small", dict(emb_lo=8, emb_hi=16, emb_step=4))])
+def test_one_stream_step_bit_identical(monkeypatch, name, over):
+    # three steps (the second and third with keep words produced by the step
+    # before) of a small pack on the caller's stream and split over two
+    cfg = configs.workload(name, K=len(WIDTHS), **over)
+    mem = [dict(m, d_emb=8 + 4 * (i % 3), sigma=1.0) for i, m in enumerate(members((cfg["L"], 1)))]
+    Xtr, ytr, _, _, orders, _ = make_inputs(cfg, 1200, 10)
+    X, y = to_dev(Xtr, ytr)
+    runs = []
+    for streams in ("1", "2"):
+        monkeypatch.setenv("TABPACK_STREAMS", streams)
+        monkeypatch.setenv("TABPACK_GEMM_TILES", "small")
+        pk = tabpack.Pack(cfg, members=mem).bind()
+        got = []
+        for s in range(3):
+            (idx,) = to_dev(synth.batch_indices(orders, s, cfg["B"]))
+            got.append(pk.train_step(X, y, idx, s + 1).cpu().numpy())
+        runs.append(got + [x for k in range(pk.K) for p in (pk.get_params(k), *pk.get_moments(k), pk.get_grads(k))
+                           for part in p for x in (part.values() if isinstance(part, dict) else part)])
+    for a, b in zip(*runs):
+        np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("d_out", [2, 3, 8, 16])
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+def test_fused_head_outputs(precision, d_out):
+    # every output count's kernel, a batch that ends inside a 32-row block, and
+    # widths of one to several column passes, against the oracle
+    cfg = configs.workload("multiclass_lognormal", K=3, L=1, B=45, d_in=12, d_out=d_out, precision=precision)
+    mem = [dict(width=w, dropout=0.0, lr=1e-3, wd=1e-3) for w in (7, 256, 530)]
+    Xtr, ytr, _, _, _, idx = make_inputs(cfg, 400, 10)
+    X, y, idx_d = to_dev(Xtr, ytr, idx)
+    pk = tabpack.Pack(cfg, members=mem).bind()
+    op = OraclePack(oracle_cfg(cfg), hparams=oracle_hparams(cfg, mem),
+                    precision="bf16" if precision == "bf16" else "fp64")
+    p0 = [[(W.copy(), b.copy()) for W, b in p] for p in op.params]
+    loss = pk.train_step(X, y, idx_d, 1).cpu().numpy()
+    check_tensor("loss", loss, op.train_step(Xtr, ytr, idx, 1), TOL[precision])
+    for k in range(3):
+        compare_member(pk, op, k, p0[k], TOL[precision])
+
+
+def test_bad_index_of_removed_member_is_flagged():
+    cfg = configs.workload("binary_small", K=3)
+    Xtr, ytr, _, _, _, idx = make_inputs(cfg, 600, 10)
+    idx = idx.copy()
+    idx[1, 5] = 600
+    X, y, idx_d = to_dev(Xtr, ytr, idx)
+    pk = tabpack.Pack(cfg).bind()
+    pk.set_active([1, 0, 1])
+    pk.train_step(X, y, idx_d, 1)
+    assert pk.status() == tabpack.STATUS_IDX_RANGE
+
+
+def test_few_members_left_of_a_large_pack(monkeypatch):
+    # a pack too large for the one-stream step, of which two members stay: one
+    # stream with two gradient buffers against two streams
+    cfg = configs.workload("regression_onehot", K=40, B=512, L=4, width_lo=300, width_hi=512)
+    Xtr, ytr, _, _, orders, _ = make_inputs(cfg, 2000, 10)
+    X, y = to_dev(Xtr, ytr)
+    runs = []
+    for streams in ("1", "2"):
+        monkeypatch.setenv("TABPACK_STREAMS", streams)
+        pk = tabpack.Pack(cfg).bind()
+        (idx,) = to_dev(synth.batch_indices(orders, 0, cfg["B"]))
+        got = [pk.train_step(X, y, idx, 1).cpu().numpy()]
+        pk.set_active([k in (3, 17) for k in range(40)])
+        for s in (1, 2):
+            (idx,) = to_dev(synth.batch_indices(orders, s, cfg["B"]))
+            got.append(pk.train_step(X, y, idx, s + 1).cpu().numpy()[[3, 17]])
+        runs.append(got + [x for k in (0, 3, 17) for p in (pk.get_params(k), *pk.get_moments(k)) for part in p
+                           for x in part])
     for a, b in zip(*runs):
         np.testing.assert_array_equal(a, b)
