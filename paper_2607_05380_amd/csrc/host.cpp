@@ -38,6 +38,9 @@ int fail(int code, const char* fmt, ...) {
   } while (0)
 
 constexpr uint32_t kTagHparam = 1, kTagInit = 2;
+// Evaluation and prediction take their rows in chunks of eval_rows() of the
+// levels 0 .. eval_levels - 1 (each a quarter of the one before).
+constexpr int kEvalLevels = 8;
 constexpr int kGroups = 4;  // at most this many member groups run their GEMM chains concurrently
 
 int64_t round_up(int64_t x, int64_t q) { return (x + q - 1) / q * q; }
@@ -171,7 +174,11 @@ struct pack_handle {
   // buffer: the dropout keep words alternate between two copies by step
   // parity, so the next step's are produced while this step's backward runs
   std::vector<Launch> fwd[2][kGroups], dx[kGroups], dw[kGroups];  // [keep-word parity][group] / [group]
-  Launch fwd1_eval{};                // layer 1 over the shared validation rows in H_0 block 0
+  // evaluation and prediction: one launch a layer over all active members, per
+  // chunk level; chunks of level i hold Bp << eval_shift >> 2 i rows
+  std::vector<Launch> ev[kEvalLevels];
+  int eval_shift = 0, eval_levels = 1;
+  int last_rows = 0;  // rows of the last forward pass's activation blocks (Bp, or an evaluation chunk's)
   // The members are split into ngroups groups of about equal GEMM work; each
   // group's GEMM chain runs on its own stream (group 0 on the caller's), which
   // measured faster than one launch over all members.
@@ -221,7 +228,7 @@ struct pack_handle {
   std::vector<ProfGroup> groups;
 
   size_t elt() const { return prec == Prec::BF16 ? 2 : 4; }
-  void* Hl(int l) const { return b.H + (size_t)(l - 1) * A * elt(); }  // H_l, l = 1..L
+  int eval_rows(int level) const { return (int)(((int64_t)Bp << eval_shift) >> (2 * level)); }
   int64_t H0e = 0;  // elements of the H_0 / E buffer (every member's first-layer input block)
   int64_t Etab = 0; // entries of the embedding column tables (p_in per embedded member)
 };
@@ -458,7 +465,8 @@ struct Plan {
   std::vector<ColTile> coltiles;
   std::vector<HeadTile> headtiles;
   std::vector<Launch> fwd[2][kGroups], dx[kGroups], dw[kGroups];
-  Launch fwd1_eval{}, dw_all{};
+  Launch dw_all{};
+  std::vector<Launch> ev[kEvalLevels];  // evaluation, per chunk level and layer
   int sumtile0[kGroups + 1] = {};  // see build_plan
   int headtile0[kGroups + 1] = {};
   std::vector<int32_t> members;  // member ids in group order
@@ -755,6 +763,27 @@ TileSet launch_tiles(const pack_handle* h, int forced, int64_t n_small, int min_
   return n_small >= kTallMinTiles ? TILES_TALL : TILES_SMALL;
 }
 
+// Rows of an evaluation chunk: the training batch's padded rows times a power
+// of two, up to kEvalTiles 128 x 128 activation tiles a layer and kEvalRows
+// rows (the activation buffers grow with it), and quarters of that down to 64
+// rows for short inputs and last chunks.  A chunk of Bp rows leaves the CUs
+// idle at the ends of a layer's launch, and a call waits for launches in
+// proportion to its chunks.  Measured, chunks of Bp rows with a launch per
+// member group / these chunks: 64 members of widths 256..1024 on 70,000 rows
+// 26.1 / 21.6 ms, 32 of them on 20,000 rows 4.56 / 3.38 ms, 16 members of
+// 128..512 on 37 rows 39.9 / 28.6 us (chunks of 512 rows, of 128).
+constexpr int64_t kEvalTiles = 8192, kEvalRows = 8192;
+void plan_eval(pack_handle* h) {
+  int64_t n = 0;
+  for (const Member& m : h->mem) n += small_tiles(h->Bp, m.dp);
+  h->eval_shift = 0;
+  while ((n << (h->eval_shift + 1)) <= kEvalTiles && ((int64_t)h->Bp << (h->eval_shift + 1)) <= kEvalRows)
+    ++h->eval_shift;
+  h->eval_levels = 1;
+  while (h->eval_levels < kEvalLevels && h->eval_rows(h->eval_levels) >= 64 && h->eval_rows(h->eval_levels) % 32 == 0)
+    ++h->eval_levels;
+}
+
 void plan_muon(const pack_handle* h, const Bufs& bf, const std::vector<int> (&group)[kGroups], Plan& p,
                bool sizing) {
   const size_t es = h->elt();
@@ -968,26 +997,44 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     sort_launch(p, f);
     p.fwd[par][hf].push_back(f);
   }
-  {
-    // evaluation, layer 1: every member reads the same validation rows (H_0 block 0)
-    Launch f{(int)p.descs.size(), 0, (int)p.tiles.size(), 0, 0.0};
-    int64_t nsm = 0;
-    for (int hf = 0; hf < kGroups; ++hf) {
-      f.ndesc += (int)group[hf].size();
-      for (int k : group[hf]) nsm += small_tiles(h->Bp, h->mem[k].dp);
+  // evaluation: all members in one launch a layer (no second stream runs beside
+  // it), over chunks of R rows whose activation blocks are R / Bp times the
+  // training ones; the first layer reads the chunk's rows from H_0 block 0
+  for (int lv = 0; lv < h->eval_levels; ++lv) {
+    const int R = h->eval_rows(lv);
+    auto ract = [&](int l, int k) -> void* {
+      return bf.H + ((size_t)(l - 1) * (h->A / h->Bp) + (size_t)(h->mem[k].act_off / h->Bp)) * R * es;
+    };
+    for (int l = 1; l <= c.L; ++l) {
+      Launch f{(int)p.descs.size(), 0, (int)p.tiles.size(), 0, 0.0, 0.0};
+      int64_t nsm = 0;
+      for (int hf = 0; hf < kGroups; ++hf)
+        for (int k : group[hf])
+          if (h->mem[k].depth >= l) nsm += small_tiles(R, h->mem[k].dp);
+      p.tile_set = l == 1 && h->emb ? (sizing ? TILES_SMALL : h->emb_tiles) : choose(h->tiles_fwd, nsm);
+      for (int hf = 0; hf < kGroups; ++hf)
+        for (int k : group[hf]) {
+          const Member& m = h->mem[k];
+          if (m.depth < l) continue;
+          GemmDesc d{};
+          d.A = l > 1 ? ract(l - 1, k) : m.d_emb ? nullptr : (void*)bf.H0;
+          d.lda = d.ldb = l == 1 ? m.p_in : m.dp;
+          d.B = wptr(k, l);
+          d.C = ract(l, k);
+          d.ldc = m.dp;
+          d.bias = bf.theta + m.toff[2 * (l - 1) + 1];
+          d.M = R;
+          d.N = m.dp;
+          d.Kd = l == 1 ? m.p_in : m.dp;
+          d.width = m.width;
+          d.member = k;
+          add_tiles(p, f, (int)p.descs.size(), R, m.dp, d.Kd);
+          p.descs.push_back(d);
+          ++f.ndesc;
+        }
+      sort_launch(p, f);
+      p.ev[lv].push_back(f);
     }
-    p.tile_set = h->emb ? (sizing ? TILES_SMALL : h->emb_tiles) : choose(h->tiles_fwd, nsm);
-    for (int hf = 0; hf < kGroups; ++hf)
-      for (int i = 0; i < (int)group[hf].size(); ++i) {
-        const int k = group[hf][i];
-        GemmDesc d = p.descs[p.fwd[0][hf][0].desc0 + i];
-        if (h->mem[k].d_emb == 0) d.A = h0(0);  // embedded members read their own E block
-        d.xrows_n = 0;                          // evaluation reads the gathered validation rows
-        add_tiles(p, f, (int)p.descs.size(), h->Bp, h->mem[k].dp, d.Kd);
-        p.descs.push_back(d);
-      }
-    sort_launch(p, f);
-    p.fwd1_eval = f;
   }
   for (int hf = 0; hf < kGroups; ++hf)
   for (int l = 1; l <= c.L; ++l) {
@@ -1189,18 +1236,19 @@ size_t carve(const pack_handle* h, char* base, Bufs& bf) {
   bf.v = cv.take<float>(h->P);
   bf.shadow = h->prec == Prec::BF16 ? cv.take<uint16_t>(h->P) : nullptr;
   // embedded packs never store E (the first layer's GEMMs produce it)
-  bf.H0 = h->emb ? nullptr : cv.take<char>((size_t)h->H0e * h->elt());
+  const int64_t emax = h->eval_rows(0);  // rows of the largest evaluation chunk
+  bf.H0 = h->emb ? nullptr : cv.take<char>((size_t)std::max(h->H0e, emax * h->Pin) * h->elt());
   // each member's sums at its E offset / 16 (Bp is a multiple of 256, so the
   // offsets divide; a member's [Bp / 64][4][p_in] sums fill Bp p_in / 16)
   bf.dE = h->emb ? cv.take<float>((size_t)h->H0e / 16) : nullptr;
   bf.etab = h->emb ? cv.take<float4>((size_t)h->Etab) : nullptr;
-  bf.H = cv.take<char>((size_t)c.L * h->A * h->elt());
+  bf.H = cv.take<char>((size_t)c.L * (h->A / h->Bp) * emax * h->elt());
   bf.dz = cv.take<char>((size_t)h->ndz() * h->A * h->elt());
   bf.colpart = cv.take<float>((size_t)std::max(1, c.L - 1) * (h->A / kPartRows));
   bf.mask = cv.take<uint32_t>((size_t)c.L * (h->A / 32));
   bf.keepw = cv.take<uint32_t>((size_t)2 * c.L * (h->A / 32));
   bf.zeros = cv.take<char>(256);
-  bf.dY = cv.take<float>((size_t)c.K * h->Bp * c.d_out);
+  bf.dY = cv.take<float>((size_t)c.K * emax * c.d_out);
   bf.rowloss = cv.take<float>((size_t)c.K * h->Bp);
   bf.d_mem = cv.take<MemberDev>(c.K);
   bf.d_bias_off = cv.take<int64_t>((size_t)c.L * c.K);
@@ -1223,7 +1271,7 @@ size_t carve(const pack_handle* h, char* base, Bufs& bf) {
   const bool mini_forced = h->tiles_fwd == TILES_MINI || h->tiles_dx == TILES_MINI || h->tiles_dw == TILES_MINI ||
                            h->ns_tiles == TILES_MINI;
   bf.tile_cap = mini_forced ? 4 * plan.tiles.size()
-                            : plan.tiles.size() + (size_t)4 * kMiniMaxTiles * kGroups * (4 * (size_t)c.L + 7);
+                            : plan.tiles.size() + (size_t)4 * kMiniMaxTiles * (kGroups * (4 * (size_t)c.L + 7) + kEvalLevels * (size_t)c.L);
   if (h->muon) {
     bf.mpart = cv.take<double>(plan.mtiles.size());
     bf.minv = cv.take<float>(plan.mmats.size());
@@ -1378,7 +1426,7 @@ int upload_plan(pack_handle* h, hipStream_t stream) {
     h->dx[hf] = plan.dx[hf];
     h->dw[hf] = plan.dw[hf];
   }
-  h->fwd1_eval = plan.fwd1_eval;
+  for (int lv = 0; lv < kEvalLevels; ++lv) h->ev[lv] = plan.ev[lv];
   h->dw_all = plan.dw_all;
   for (int g = 0; g <= kGroups; ++g) h->sumtile0[g] = plan.sumtile0[g];
   for (int i = 0; i <= kGroups; ++i) {
@@ -1545,6 +1593,7 @@ int pack_init(const pack_config* cfg, pack_handle** out) {
     m.scale = 1.0 / (1.0 - m.dropout);
   }
   plan_layout(h);
+  plan_eval(h);
   h->active.assign(cfg->K, 1);
   set_active_ids(h);
   h->small = small_pack(h, h->active_ids);
@@ -1615,6 +1664,7 @@ int pack_bind(pack_handle* h, void* workspace, size_t bytes, hipStream_t stream)
     for (hipEvent_t& e : h->ev_bias) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   }
   h->keep_ready = 0;
+  h->last_rows = h->Bp;
   HIP_TRY(hipMemsetAsync(workspace, 0, need, stream));
   HIP_TRY(hipMemcpyAsync(h->b.theta, h->theta_host.data(), h->P * sizeof(float), hipMemcpyHostToDevice, stream));
   std::vector<MemberDev> md(h->cfg.K);
@@ -1664,6 +1714,7 @@ int pack_train_step(pack_handle* h, const float* X, const void* y, int64_t N, co
     return fail(PACK_EINVAL, "X / N differ from the data bound with pack_bind_data (bind it again, or unbind "
                              "it with X = NULL)");
   const pack_config& c = h->cfg;
+  h->last_rows = h->Bp;
   const int nact = (int)h->active_ids.size();
   GemmArgs a = base_args(h);
   a.rows_valid = c.B;
@@ -1732,8 +1783,8 @@ int pack_train_step(pack_handle* h, const float* X, const void* y, int64_t N, co
                                  c.B, h->b.dY, h->b.rowloss, h->b.dz, h->b.headpart, h->b.status, gm, s);
       });
     const hipError_t e = timed(h, "head_fwd", 1, 0.0, nb, s, [&] {
-      return launch_head_fwd(h->prec, h->task, kHeadTrain, h->b.H, h->b.theta, h->b.d_mem, gk, h->Bp, c.d_out, y,
-                             idx, c.B, c.B, 0, N, h->b.dY, h->b.rowloss, nullptr, h->b.status, gm, s);
+      return launch_head_fwd(h->prec, h->task, kHeadTrain, h->b.H, h->b.theta, h->b.d_mem, gk, h->Bp, h->Bp, c.d_out,
+                             y, idx, c.B, c.B, 0, N, h->b.dY, h->b.rowloss, nullptr, h->b.status, gm, s);
     });
     if (e != hipSuccess) return e;
     return timed(h, "head_bwd", 1, 0.0, 2.0 * nb, s, [&] {
@@ -1935,29 +1986,35 @@ int pack_train_step(pack_handle* h, const float* X, const void* y, int64_t N, co
 }  // extern "C"
 
 namespace {
+// The smallest chunk level that holds `rows` rows, or the largest level.
+int eval_level(const pack_handle* h, int64_t rows) {
+  int lv = 0;
+  while (lv + 1 < h->eval_levels && h->eval_rows(lv + 1) >= rows) ++lv;
+  return lv;
+}
+
 // Forward pass without dropout of every active member over rows r0 ..
-// r0 + a.rows_valid - 1 of X (N rows): the first layer (on the rows gathered
-// once for all members, or, with embeddings, producing each member's
-// embedded rows in the GEMM from the column tables, which the caller has
-// built), then the hidden layers; the last hidden activations are left in H
-// for the head.
-hipError_t eval_forward(pack_handle* h, GemmArgs a, const float* X, int64_t N, int64_t r0, hipStream_t stream) {
+// r0 + a.rows_valid - 1 of X (N rows), a chunk of the given level: the first
+// layer (on the rows gathered once for all members, or, with embeddings,
+// producing each member's embedded rows in the GEMM from the column tables,
+// which the caller has built), then the hidden layers; the last hidden
+// activations are left in H for the head.
+hipError_t eval_forward(pack_handle* h, GemmArgs a, const float* X, int64_t N, int64_t r0, int level,
+                        hipStream_t stream) {
   const pack_config& c = h->cfg;
+  const int R = h->eval_rows(level);
+  h->last_rows = R;
   hipError_t e = hipSuccess;
   if (!h->emb)
-    e = launch_gather(h->prec, X, N, c.d_in, h->Pin, nullptr, c.B, r0, a.rows_valid, 1, h->Bp, h->b.H0, nullptr,
-                      stream);
-  if (e != hipSuccess) return e;
-  for (int l = 1; l <= c.L; ++l) {
-    for (int hf = 0; hf < (l == 1 ? 1 : h->ngroups); ++hf) {
-      GemmArgs al = for_launch(a, l == 1 ? h->fwd1_eval : h->fwd[0][hf][l - 1]);
-      al.layer = l;
-      const OpKind ak = l == 1 && h->emb ? OP_EMB : OP_KMAJ;
-      if (ak == OP_EMB) set_emb(h, al, X, N, nullptr, r0);
-      if ((e = launch_gemm(h->prec, ak, OP_KMAJ, EPI_FWD_EVAL, al, stream)) != hipSuccess) return e;
-    }
+    e = launch_gather(h->prec, X, N, c.d_in, h->Pin, nullptr, c.B, r0, a.rows_valid, 1, R, h->b.H0, nullptr, stream);
+  for (int l = 1; l <= c.L && e == hipSuccess; ++l) {
+    GemmArgs al = for_launch(a, h->ev[level][l - 1]);
+    al.layer = l;
+    const OpKind ak = l == 1 && h->emb ? OP_EMB : OP_KMAJ;
+    if (ak == OP_EMB) set_emb(h, al, X, N, nullptr, r0);
+    e = launch_gemm(h->prec, ak, OP_KMAJ, EPI_FWD_EVAL, al, stream);
   }
-  return hipSuccess;
+  return e;
 }
 }  // namespace
 
@@ -1974,12 +2031,14 @@ int pack_eval_members(pack_handle* h, const float* Xv, const void* yv, int64_t N
   const int nact = (int)h->active_ids.size();
   GemmArgs a = base_args(h);
   if (h->emb) HIP_TRY(emb_tables(h, h->b.d_active, h->active_ids, stream));
-  for (int64_t r0 = 0; r0 < Nv; r0 += h->Bp) {
-    a.rows_valid = (int)std::min<int64_t>(h->Bp, Nv - r0);
-    HIP_TRY(eval_forward(h, a, Xv, Nv, r0, stream));
-    HIP_TRY(launch_head_fwd(h->prec, h->task, kHeadEval, h->b.H, h->b.theta, h->b.d_mem, nact, h->Bp, c.d_out,
+  for (int64_t r0 = 0; r0 < Nv;) {
+    const int lv = eval_level(h, Nv - r0), R = h->eval_rows(lv);
+    a.rows_valid = (int)std::min<int64_t>(R, Nv - r0);
+    HIP_TRY(eval_forward(h, a, Xv, Nv, r0, lv, stream));
+    HIP_TRY(launch_head_fwd(h->prec, h->task, kHeadEval, h->b.H, h->b.theta, h->b.d_mem, nact, h->Bp, R, c.d_out,
                             yv, nullptr, c.B, a.rows_valid, r0, Nv, nullptr, nullptr, pred_out, nullptr,
                             h->b.d_active, stream));
+    r0 += R;
   }
   HIP_TRY(launch_eval_score(h->task, pred_out, yv, nact, Nv, score_out, h->b.d_active, stream));
   return PACK_OK;
@@ -1996,21 +2055,23 @@ int pack_predict(pack_handle* h, const float* X, int64_t N, int32_t mode, float*
   const int nact = (int)h->active_ids.size();
   GemmArgs a = base_args(h);
   if (h->emb) HIP_TRY(emb_tables(h, h->b.d_active, h->active_ids, stream));
-  for (int64_t r0 = 0; r0 < N; r0 += h->Bp) {
-    a.rows_valid = (int)std::min<int64_t>(h->Bp, N - r0);
-    HIP_TRY(eval_forward(h, a, X, N, r0, stream));
+  for (int64_t r0 = 0; r0 < N;) {
+    const int lv = eval_level(h, N - r0), R = h->eval_rows(lv);
+    a.rows_valid = (int)std::min<int64_t>(R, N - r0);
+    HIP_TRY(eval_forward(h, a, X, N, r0, lv, stream));
     if (mode == PACK_PREDICT_MEMBERS) {
       // member i (i-th active id) writes rows r0.. of out[i, :, :]
-      HIP_TRY(launch_head_fwd(h->prec, h->task, kHeadPredict, h->b.H, h->b.theta, h->b.d_mem, nact, h->Bp,
+      HIP_TRY(launch_head_fwd(h->prec, h->task, kHeadPredict, h->b.H, h->b.theta, h->b.d_mem, nact, h->Bp, R,
                               c.d_out, nullptr, nullptr, c.B, a.rows_valid, r0, N, nullptr, nullptr, out,
                               nullptr, h->b.d_active, stream));
     } else {
-      // the chunk's member predictions go to the dY buffer ([K, Bp, d_out]), then their mean to out
-      HIP_TRY(launch_head_fwd(h->prec, h->task, kHeadPredict, h->b.H, h->b.theta, h->b.d_mem, nact, h->Bp,
-                              c.d_out, nullptr, nullptr, c.B, a.rows_valid, 0, h->Bp, nullptr, nullptr, h->b.dY,
+      // the chunk's member predictions go to the dY buffer ([K, R, d_out]), then their mean to out
+      HIP_TRY(launch_head_fwd(h->prec, h->task, kHeadPredict, h->b.H, h->b.theta, h->b.d_mem, nact, h->Bp, R,
+                              c.d_out, nullptr, nullptr, c.B, a.rows_valid, 0, R, nullptr, nullptr, h->b.dY,
                               nullptr, h->b.d_active, stream));
-      HIP_TRY(launch_ensemble_mean(h->b.dY, nact, h->Bp, a.rows_valid, c.d_out, r0, out, stream));
+      HIP_TRY(launch_ensemble_mean(h->b.dY, nact, R, a.rows_valid, c.d_out, r0, out, stream));
     }
+    r0 += R;
   }
   return PACK_OK;
 }
@@ -2196,10 +2257,12 @@ int pack_debug_activation(pack_handle* h, int32_t layer, int32_t member, float* 
     return fail(PACK_EINVAL, "layer %d out of [1, %d] for member %d", layer, h->mem[member].depth, member);
   if (!host_out) return fail(PACK_EINVAL, "host_out is NULL");
   const Member& m = h->mem[member];
-  const size_t n = (size_t)h->Bp * m.dp;
-  std::vector<uint8_t> tmp(n * h->elt());
+  // blocks of last_rows rows; a chunk of fewer rows than B leaves the others zero
+  const size_t R = (size_t)h->last_rows, n = (size_t)std::min(h->Bp, h->last_rows) * m.dp;
+  const size_t off = ((size_t)(layer - 1) * (h->A / h->Bp) + (size_t)(m.act_off / h->Bp)) * R;
+  std::vector<uint8_t> tmp((size_t)h->Bp * m.dp * h->elt());
   HIP_TRY(hipDeviceSynchronize());
-  HIP_TRY(hipMemcpy(tmp.data(), (char*)h->Hl(layer) + (size_t)m.act_off * h->elt(), tmp.size(), hipMemcpyDeviceToHost));
+  HIP_TRY(hipMemcpy(tmp.data(), h->b.H + off * h->elt(), n * h->elt(), hipMemcpyDeviceToHost));
   for (int r = 0; r < h->cfg.B; ++r)
     for (int c = 0; c < m.width; ++c) {
       const size_t i = (size_t)r * m.dp + c;

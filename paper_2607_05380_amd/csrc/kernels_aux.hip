@@ -245,10 +245,12 @@ __device__ __forceinline__ int64_t batch_row(const int32_t* idx, int64_t i, int6
 // all d_out prediction values (kHeadPredict: outputs, P(class 1) or the softmax
 // probabilities) at pred[((blockIdx.y * Nv) + row_base + row) * d_out + o].
 // D >= d_out is the output count rounded up to a power of two.  H is the start
-// of the activation buffers; member k reads its last hidden layer at H + h_last.
+// of the activation buffers; member k reads its last hidden layer at H + h_last
+// (evaluation chunks of Bp rows: offsets of the training batch's blocks times
+// 2^grow, or over 2^-grow).
 template <typename T, int MODE, int D>
 __global__ __launch_bounds__(256) void head_fwd_kernel(Task task, const T* H, const float* theta,
-                                                       const MemberDev* mem, int Bp, int d_out,
+                                                       const MemberDev* mem, int Bp, int d_out, int grow,
                                                        const void* y, const int32_t* idx, int B,
                                                        int rows_valid, int64_t row_base, int64_t Nv,
                                                        float* dY, float* rowloss, float* pred, uint32_t* status,
@@ -256,10 +258,12 @@ __global__ __launch_bounds__(256) void head_fwd_kernel(Task task, const T* H, co
   const int k = members ? members[blockIdx.y] : (int)blockIdx.y;
   const int lane = threadIdx.x & 63, sub = lane & 7;
   const int row = blockIdx.x * 32 + (threadIdx.x >> 3);
-  if (row >= Bp) return;  // Bp is a multiple of 32: whole 8-lane groups leave together
+  // Bp is a multiple of 32, and a row's 8 lanes leave together
+  if (row >= (MODE == kHeadTrain ? Bp : rows_valid)) return;
   const MemberDev md = mem[k];
   float acc[D], z[kMaxOut];
-  head_row<T, D>(H + md.h_last + (int64_t)row * md.dp, theta + md.w_out_off, md.dp, d_out, sub, acc);
+  const int64_t h_last = MODE == kHeadTrain ? md.h_last : grow >= 0 ? md.h_last << grow : md.h_last >> -grow;
+  head_row<T, D>(H + h_last + (int64_t)row * md.dp, theta + md.w_out_off, md.dp, d_out, sub, acc);
   head_outputs<D>(acc, theta + md.b_out_off, d_out, z);
   if (sub != 0) return;
 
@@ -676,14 +680,21 @@ __global__ void to_shadow_kernel(const float* theta, uint16_t* shadow, int64_t n
 }
 
 // ------------------------------------------------------------ eval scores --
-__global__ __launch_bounds__(256) void eval_score_kernel(Task task, const float* pred,
+// One workgroup a member; its 16 waves take the rows 1,024 at a time: bound by the
+// latency of the loads and, for probabilities, the fp64 logarithms.
+constexpr int kScoreThreads = 1024;
+__global__ __launch_bounds__(kScoreThreads) void eval_score_kernel(Task task, const float* pred,
                                                          const void* yv, int64_t Nv,
                                                          double* score_out, const int32_t* members) {
-  __shared__ double sh[4];
+  __shared__ double sh[kScoreThreads / 64];
   const int k = members ? members[blockIdx.x] : (int)blockIdx.x;
   double s = 0.0;
-  for (int64_t i = threadIdx.x; i < Nv; i += 256) s += row_score(task, (double)pred[k * Nv + i], yv, i);
-  s = block_sum_d(s, sh);
+  for (int64_t i = threadIdx.x; i < Nv; i += kScoreThreads) s += row_score(task, (double)pred[k * Nv + i], yv, i);
+  s = wave_sum_d(s);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  s = wave_sum_d(threadIdx.x < kScoreThreads / 64 ? sh[threadIdx.x] : 0.0);
   if (threadIdx.x == 0) score_out[k] = finish_score(task, s, Nv);
 }
 
@@ -901,20 +912,21 @@ int select_blocks(int64_t Nv) { return (int)((Nv + kSelRows - 1) / kSelRows); }
 namespace {
 template <typename T, int MODE, int D>
 void head_fwd_t(dim3 grid, hipStream_t s, Task task, const void* H, const float* theta, const MemberDev* mem,
-                int Bp, int d_out, const void* y, const int32_t* idx, int B, int rows_valid, int64_t row_base,
-                int64_t Nv, float* dY, float* rowloss, float* pred, uint32_t* status, const int32_t* members) {
+                int Bp, int d_out, int grow, const void* y, const int32_t* idx, int B, int rows_valid,
+                int64_t row_base, int64_t Nv, float* dY, float* rowloss, float* pred, uint32_t* status,
+                const int32_t* members) {
   hipLaunchKernelGGL((head_fwd_kernel<T, MODE, D>), grid, dim3(256), 0, s, task, static_cast<const T*>(H), theta,
-                     mem, Bp, d_out, y, idx, B, rows_valid, row_base, Nv, dY, rowloss, pred, status,
+                     mem, Bp, d_out, grow, y, idx, B, rows_valid, row_base, Nv, dY, rowloss, pred, status,
                      members);
 }
 
 template <typename T, int MODE>
 void head_fwd_d(int d_out, dim3 grid, hipStream_t s, Task task, const void* H, const float* theta,
-                const MemberDev* mem, int Bp, const void* y, const int32_t* idx, int B, int rows_valid,
+                const MemberDev* mem, int Bp, int grow, const void* y, const int32_t* idx, int B, int rows_valid,
                 int64_t row_base, int64_t Nv, float* dY, float* rowloss, float* pred, uint32_t* status,
                 const int32_t* members) {
 #define TABPACK_HEAD_FWD(DD)                                                                                   \
-  head_fwd_t<T, MODE, DD>(grid, s, task, H, theta, mem, Bp, d_out, y, idx, B, rows_valid, row_base, Nv, dY, \
+  head_fwd_t<T, MODE, DD>(grid, s, task, H, theta, mem, Bp, d_out, grow, y, idx, B, rows_valid, row_base, Nv, dY, \
                           rowloss, pred, status, members)
   if (d_out <= 1) TABPACK_HEAD_FWD(1);
   else if (d_out <= 2) TABPACK_HEAD_FWD(2);
@@ -927,18 +939,23 @@ void head_fwd_d(int d_out, dim3 grid, hipStream_t s, Task task, const void* H, c
 }  // namespace
 
 hipError_t launch_head_fwd(Prec prec, Task task, int mode, const void* H, const float* theta,
-                           const MemberDev* mem, int K, int Bp, int d_out, const void* y,
+                           const MemberDev* mem, int K, int Bp, int rows, int d_out, const void* y,
                            const int32_t* idx, int B, int rows_valid, int64_t row_base, int64_t Nv,
                            float* dY, float* rowloss, float* pred, uint32_t* status, const int32_t* members,
                            hipStream_t s) {
-  if (Bp % 32 != 0 || d_out < 1 || d_out > kMaxOut || mode < kHeadTrain || mode > kHeadPredict)
+  int grow = 0;  // rows = Bp << grow
+  while (((int64_t)Bp << grow) < rows) ++grow;
+  while (grow <= 0 && (Bp >> -grow) > rows) --grow;
+  if (rows < 32 || rows % 32 != 0 || (mode == kHeadTrain && rows != Bp) ||
+      (grow >= 0 ? (int64_t)Bp << grow : (int64_t)rows << -grow) != (grow >= 0 ? rows : Bp) || d_out < 1 ||
+      d_out > kMaxOut || mode < kHeadTrain || mode > kHeadPredict)
     return hipErrorInvalidValue;
   if (mode == kHeadTrain && !status) return hipErrorInvalidValue;
   if (K <= 0) return hipSuccess;
-  const dim3 grid(Bp / 32, K);
+  const dim3 grid(rows / 32, K);
 #define TABPACK_HEAD_FWD_MODE(TT, MM)                                                                         \
-  head_fwd_d<TT, MM>(d_out, grid, s, task, H, theta, mem, Bp, y, idx, B, rows_valid, row_base, Nv, dY, rowloss, \
-                     pred, status, members)
+  head_fwd_d<TT, MM>(d_out, grid, s, task, H, theta, mem, rows, grow, y, idx, B, rows_valid, row_base, Nv, dY, \
+                     rowloss, pred, status, members)
   if (prec == Prec::BF16) {
     if (mode == kHeadTrain) TABPACK_HEAD_FWD_MODE(__bf16, kHeadTrain);
     else if (mode == kHeadEval) TABPACK_HEAD_FWD_MODE(__bf16, kHeadEval);
@@ -1081,7 +1098,7 @@ hipError_t launch_to_shadow(const float* theta, uint16_t* shadow, int64_t n, hip
 hipError_t launch_eval_score(Task task, const float* pred, const void* yv, int K, int64_t Nv,
                              double* score_out, const int32_t* members, hipStream_t s) {
   if (K <= 0) return hipSuccess;
-  hipLaunchKernelGGL(eval_score_kernel, dim3(K), dim3(256), 0, s, task, pred, yv, Nv, score_out, members);
+  hipLaunchKernelGGL(eval_score_kernel, dim3(K), dim3(kScoreThreads), 0, s, task, pred, yv, Nv, score_out, members);
   return hipGetLastError();
 }
 

@@ -1899,6 +1899,7 @@ template <typename T, int AK, int BK_, int EPI>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_kernel(GemmArgs a) {
   __shared__ __attribute__((aligned(16))) char smem[kLdsBig + XMapBytes<T, EPI>];
   const Tile t = a.tiles[blockIdx.x];
+  if (EPI == EPI_FWD_EVAL && t.m0 >= a.rows_valid) return;  // past the end of a last chunk: nothing reads it
   const GemmDesc d = a.descs[t.desc];
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
@@ -1922,6 +1923,7 @@ gemm_kernel_small(GemmArgs a) {
   static_assert(kTab == 0 || kLdsSmallBf16 == 2 * 2 * 128 * 32 * kSmallKs, "table stages follow the operand stages");
   __shared__ __attribute__((aligned(16))) char smem[kOps + kTab + XMapBytes<T, EPI>];
   const Tile t = a.tiles[blockIdx.x];
+  if (EPI == EPI_FWD_EVAL && t.m0 >= a.rows_valid) return;  // past the end of a last chunk: nothing reads it
   const GemmDesc d = a.descs[t.desc];
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1943,6 +1945,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   static_assert(8 * Shape<kShapeWide>::STAGE <= kOps, "epilogue staging of 8 waves");
   __shared__ __attribute__((aligned(16))) char smem[kOps + 2048];
   const Tile t = a.tiles[blockIdx.x];
+  if (EPI == EPI_FWD_EVAL && t.m0 >= a.rows_valid) return;  // past the end of a last chunk: nothing reads it
   const GemmDesc d = a.descs[t.desc];
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1959,6 +1962,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   static_assert(kLdsTall + XMapBytes<__bf16, EPI> <= 80 * 1024, "two tall-tile workgroups per CU");
   __shared__ __attribute__((aligned(16))) char smem[kLdsTall + XMapBytes<__bf16, EPI>];
   const Tile t = a.tiles[blockIdx.x];
+  if (EPI == EPI_FWD_EVAL && t.m0 >= a.rows_valid) return;  // past the end of a last chunk: nothing reads it
   const GemmDesc d = a.descs[t.desc];
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1983,6 +1987,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel_mini(GemmArgs a) {
   constexpr int kMap = sizeof(T) == 2 ? XMapBytes<T, EPI> : 0;
   __shared__ __attribute__((aligned(16))) char smem[kOps + kMap];
   const Tile t = a.tiles[blockIdx.x];
+  if (EPI == EPI_FWD_EVAL && t.m0 >= a.rows_valid) return;  // past the end of a last chunk: nothing reads it
   const GemmDesc d = a.descs[t.desc];
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

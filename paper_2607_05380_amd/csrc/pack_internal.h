@@ -231,10 +231,11 @@ hipError_t launch_gemm(Prec prec, OpKind a, OpKind b, EpiKind e, const GemmArgs&
 // Head forward modes: training loss and dY / score-ready eval value / all prediction values.
 constexpr int kHeadTrain = 0, kHeadEval = 1, kHeadPredict = 2;
 
-// Launchers (kernels_aux.hip).  Training: Nv is the number of data rows N; an
+// Launchers (kernels_aux.hip).  rows: rows of the activation blocks (Bp, or an
+// evaluation chunk's, Bp times or over a power of two).  Training: Nv is the number of data rows N; an
 // index outside [0, N) takes the target of row 0 and sets status[0] = 1.
 hipError_t launch_head_fwd(Prec prec, Task task, int mode, const void* H, const float* theta,
-                           const MemberDev* mem, int K, int Bp, int d_out, const void* y,
+                           const MemberDev* mem, int K, int Bp, int rows, int d_out, const void* y,
                            const int32_t* idx, int B, int rows_valid, int64_t row_base, int64_t Nv,
                            float* dY, float* rowloss, float* pred, uint32_t* status, const int32_t* members,
                            hipStream_t s);

@@ -131,3 +131,27 @@ def test_few_members_left_of_a_large_pack(monkeypatch):
                            for x in part])
     for a, b in zip(*runs):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("name,over", [
+    ("regression_onehot", dict(B=300)),
+    ("multiclass_lognormal", dict(B=700, d_in=24, L=2)),
+    ("binary_small", dict(B=64, L=3)),
+    ("binary_small", dict(emb_lo=8, emb_hi=16, emb_step=4))])
+def test_chunk_rows_do_not_change_predictions(name, over):
+    # an activation row depends on its data row alone, reduced in one order by
+    # every tile, so the rows of a short input have the bits they have in a long
+    # one; 8,600 rows take a chunk of the largest size and a last one
+    cfg = configs.workload(name, K=len(WIDTHS), **over)
+    mem = [dict(m, d_emb=8 + 4 * (i % 3), sigma=0.3) for i, m in enumerate(members((cfg["L"], 1, 2)))]
+    pk = tabpack.Pack(cfg, members=mem).bind()
+    Xtr, ytr, Xv, yv, _, idx = make_inputs(cfg, 900, 8600)
+    X, y, idx_d, Xv, yv = to_dev(Xtr, ytr, idx, Xv, yv)
+    pk.train_step(X, y, idx_d, 1)
+    whole = pk.predict(Xv, ensemble=False).cpu().numpy()
+    mean = pk.predict(Xv, ensemble=True).cpu().numpy()
+    pred = pk.eval_members(Xv, yv)[0].cpu().numpy()
+    for n in (1, 33, 64, 65, 257, 2100, 8191):
+        np.testing.assert_array_equal(pk.predict(Xv[:n], ensemble=False).cpu().numpy(), whole[:, :n])
+        np.testing.assert_array_equal(pk.predict(Xv[:n], ensemble=True).cpu().numpy(), mean[:n])
+        np.testing.assert_array_equal(pk.eval_members(Xv[:n], yv[:n])[0].cpu().numpy(), pred[:, :n])
