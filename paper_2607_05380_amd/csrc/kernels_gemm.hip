@@ -942,48 +942,89 @@ __device__ __forceinline__ void stage_flush(const char* stage, OT* C, int64_t ld
   }
 }
 
-// Rows of alpha * Y + beta * acc from the staged fp32 accumulators: each lane
-// takes 4 consecutive columns of a row (Y read as 4 elements), rounds once to
-// OT and stores them; rows >= M and columns >= N are skipped (N is a multiple
-// of 4).
+// Four consecutive elements of a GEMM-precision matrix as loaded, and their
+// values; four fp32 values rounded to it.
+template <typename OT>
+struct Quad;
+template <>
+struct Quad<__bf16> {
+  using V = u32x2;
+  static __device__ __forceinline__ f32x4 get(const V& v) {
+    return f32x4{__builtin_bit_cast(float, v[0] << 16), __builtin_bit_cast(float, v[0] & 0xffff0000u),
+                 __builtin_bit_cast(float, v[1] << 16), __builtin_bit_cast(float, v[1] & 0xffff0000u)};
+  }
+  static __device__ __forceinline__ V put(const f32x4& o) {
+    return V{(uint32_t)__builtin_bit_cast(uint16_t, (__bf16)o[0]) |
+                 ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)o[1]) << 16),
+             (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)o[2]) |
+                 ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)o[3]) << 16)};
+  }
+};
+template <>
+struct Quad<float> {
+  using V = f32x4;
+  static __device__ __forceinline__ f32x4 get(const V& v) { return v; }
+  static __device__ __forceinline__ V put(const f32x4& o) { return o; }
+};
+
+// The Newton-Schulz epilogues work on 32-row blocks of staged fp32
+// accumulators, lane vector `it` holding 4 consecutive columns of a row.
+// The matrix Y that is added is read ahead as 4-element vectors (its latency,
+// about 2,000 cycles a read, was paid once per vector before; the 64-member
+// Muon step went from 4.94 to 4.64 ms with the weights of the update read ahead
+// too).
 template <typename OT, int NB>
-__device__ __forceinline__ void stage_flush_ns(const char* stage, OT* C, int64_t ldc, const OT* Y, int64_t ldy,
-                                               float alpha, float beta, int row0, int col0, int M, int N,
-                                               int lane) {
+struct NsRows {
+  static constexpr int PER = Stage<float, NB>::PER_LANE;
+  typename Quad<OT>::V y[PER];
+  __device__ __forceinline__ void load(const GemmDesc& d, int row0, int col0, int lane) {
+    using S = Stage<float, NB>;
+    const OT* Y = static_cast<const OT*>(d.Y);
+#pragma unroll
+    for (int it = 0; it < PER; ++it) {
+      const int v = it * 64 + lane;
+      const int row = row0 + v / S::VPR, col = col0 + (v % S::VPR) * 4;
+      y[it] = typename Quad<OT>::V{};
+      if (Y && row < d.M && col < d.N)
+        y[it] = *glob(reinterpret_cast<const typename Quad<OT>::V*>(Y + (int64_t)row * d.ldy + col));
+    }
+  }
+};
+
+// alpha * Y + beta * (staged accumulators), rounded once to OT.  Rows >= M and
+// columns >= N (a multiple of 4) are left out.  STORE: to C (mirror: also left
+// in the stage, for the transposed copy); else left in the stage.
+template <typename OT, int NB, bool STORE>
+__device__ __forceinline__ void stage_rows_ns(const GemmArgs& a, const GemmDesc& d, char* stage,
+                                              const NsRows<OT, NB>& ys, int row0, int col0, bool mirror, int lane) {
   using S = Stage<float, NB>;
 #pragma unroll
   for (int it = 0; it < S::PER_LANE; ++it) {
     const int v = it * 64 + lane;
     const int r = v / S::VPR, c = v % S::VPR;
-    const f32x4 x = *reinterpret_cast<const f32x4*>(stage + r * S::RS + c * 16);
+    f32x4& x = *reinterpret_cast<f32x4*>(stage + r * S::RS + c * 16);
+    const f32x4 xv = x;
     const int row = row0 + r, col = col0 + c * 4;
-    if (row >= M || col >= N) continue;
-    float o[4] = {beta * x[0], beta * x[1], beta * x[2], beta * x[3]};
-    if (Y) {
-      const OT* yp = Y + (int64_t)row * ldy + col;
+    if (row >= d.M || col >= d.N) continue;
+    const f32x4 yv = Quad<OT>::get(ys.y[it]);
+    f32x4 o;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) o[q] = alpha * to_float(yp[q]) + o[q];
+    for (int q = 0; q < 4; ++q) {
+      o[q] = a.ns_beta * xv[q];
+      if (d.Y) o[q] = a.ns_alpha * yv[q] + o[q];
     }
-    OT* cp = C + (int64_t)row * ldc + col;
-    if constexpr (sizeof(OT) == 2) {
-      const uint32_t lo = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)o[0]) |
-                          ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)o[1]) << 16);
-      const uint32_t hi = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)o[2]) |
-                          ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)o[3]) << 16);
-      *glob(reinterpret_cast<u32x2*>(cp)) = u32x2{lo, hi};
-    } else {
-      *glob(reinterpret_cast<f32x4*>(cp)) = f32x4{o[0], o[1], o[2], o[3]};
-    }
+    const typename Quad<OT>::V p = Quad<OT>::put(o);
+    if (STORE) *glob(reinterpret_cast<typename Quad<OT>::V*>(static_cast<OT*>(d.C) + (int64_t)row * d.ldc + col)) = p;
+    if (!STORE || mirror) x = Quad<OT>::get(p);
   }
 }
 
-// The transpose of the staged block, for symmetric results: staged column c
-// (C column col0 + c) becomes C row col0 + c, whose elements row0 .. row0 + 31
-// each lane writes 4 at a time (Y read at the same transposed positions).
+// The transpose of the staged results, for symmetric matrices (Y is symmetric
+// to the bit, so the mirror image needs no Y): staged column c (C column
+// col0 + c) becomes C row col0 + c, whose elements row0 .. row0 + 31 each lane
+// writes 4 at a time.
 template <typename OT, int NB>
-__device__ __forceinline__ void stage_flush_ns_mirror(const char* stage, OT* C, int64_t ldc, const OT* Y,
-                                                      int64_t ldy, float alpha, float beta, int row0, int col0,
-                                                      int M, int N, int lane) {
+__device__ __forceinline__ void stage_mirror_ns(const GemmDesc& d, const char* stage, int row0, int col0, int lane) {
   using S = Stage<float, NB>;
   constexpr int CV = 32 / 4;  // 4-row vectors per staged column
 #pragma unroll
@@ -991,98 +1032,71 @@ __device__ __forceinline__ void stage_flush_ns_mirror(const char* stage, OT* C, 
     const int v = it * 64 + lane;
     const int c = v / CV, r = (v % CV) * 4;
     const int orow = col0 + c, ocol = row0 + r;
-    if (orow >= M || ocol >= N) continue;
-    float o[4];
+    if (orow >= d.M || ocol >= d.N) continue;
+    f32x4 o;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) o[q] = beta * *reinterpret_cast<const float*>(stage + (r + q) * S::RS + c * 4);
-    if (Y) {
-      const OT* yp = Y + (int64_t)orow * ldy + ocol;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) o[q] = alpha * to_float(yp[q]) + o[q];
-    }
-    OT* cp = C + (int64_t)orow * ldc + ocol;
-    if constexpr (sizeof(OT) == 2) {
-      const uint32_t lo = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)o[0]) |
-                          ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)o[1]) << 16);
-      const uint32_t hi = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)o[2]) |
-                          ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)o[3]) << 16);
-      *glob(reinterpret_cast<u32x2*>(cp)) = u32x2{lo, hi};
-    } else {
-      *glob(reinterpret_cast<f32x4*>(cp)) = f32x4{o[0], o[1], o[2], o[3]};
-    }
+    for (int q = 0; q < 4; ++q) o[q] = *reinterpret_cast<const float*>(stage + (r + q) * S::RS + c * 4);
+    *glob(reinterpret_cast<typename Quad<OT>::V*>(static_cast<OT*>(d.C) + (int64_t)orow * d.ldc + ocol)) =
+        Quad<OT>::put(o);
   }
 }
 
-// The last Newton-Schulz iteration's rows with the Muon update fused: the new
-// X = alpha Y + beta (staged block), rounded to OT as it would be stored,
-// replaces the staged values; then each weight element w it orthogonalises
-// becomes w decay - step x (no contraction, as in the separate update), read
-// row-wise or, for tall weights (W = X^T), column-wise from the stage.
-template <typename OT, int NB>
-__device__ __forceinline__ void stage_update_ns(const GemmArgs& a, const GemmDesc& d, char* stage, int row0, int col0,
-                                                int lane) {
-  using S = Stage<float, NB>;
-  const OT* Y = static_cast<const OT*>(d.Y);
-#pragma unroll
-  for (int it = 0; it < S::PER_LANE; ++it) {
+// The Muon update of the last Newton-Schulz iteration: the staged new X
+// (rounded to OT as it would be stored) turns each weight element w it
+// orthogonalises into w decay - step x (no contraction, as in the separate
+// update), vectors row-wise or, for tall weights (W = X^T), column-wise from
+// the stage.  The block's weights are loaded before any is stored.
+template <int NB>
+struct NsWeights {
+  static constexpr int PER = Stage<float, NB>::PER_LANE;
+  static_assert(PER == NB * 32 * (32 / 4) / 64, "as many vectors by rows as by columns");
+  f32x4 w[PER];
+  // vector `it`: its element offset in the weight (-1: outside)
+  static __device__ __forceinline__ int64_t at(const GemmDesc& d, int row0, int col0, int it, int lane) {
+    using S = Stage<float, NB>;
     const int v = it * 64 + lane;
-    const int r = v / S::VPR, c = v % S::VPR;
-    const int row = row0 + r, col = col0 + c * 4;
-    if (row >= d.M || col >= d.N) continue;
-    f32x4& x = *reinterpret_cast<f32x4*>(stage + r * S::RS + c * 16);
-    const f32x4 xv = x;
-    float o[4] = {a.ns_beta * xv[0], a.ns_beta * xv[1], a.ns_beta * xv[2], a.ns_beta * xv[3]};
-    if (Y) {
-      const OT* yp = Y + (int64_t)row * d.ldy + col;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) o[q] = a.ns_alpha * to_float(yp[q]) + o[q];
+    if (!d.ns_tall) {
+      const int row = row0 + v / S::VPR, col = col0 + (v % S::VPR) * 4;
+      return row < d.M && col < d.N ? (int64_t)row * d.N + col : -1;
     }
-    x = f32x4{to_float(from_float<OT>(o[0])), to_float(from_float<OT>(o[1])), to_float(from_float<OT>(o[2])),
-              to_float(from_float<OT>(o[3]))};
+    const int wrow = col0 + v / 8, wcol = row0 + (v % 8) * 4;
+    return wrow < d.N && wcol < d.M ? (int64_t)wrow * d.M + wcol : -1;
   }
-  wave_sync_lds();
-  const float decay = d.ns_decay, step = d.ns_step;
-  auto update = [&](int64_t e, const f32x4& x) {
-    float* tp = a.ns_theta + d.poff + e;
-    f32x4 w = *glob(reinterpret_cast<const f32x4*>(tp));
+  __device__ __forceinline__ void load(const GemmArgs& a, const GemmDesc& d, int row0, int col0, int lane) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-#pragma clang fp contract(off)
-      w[q] = w[q] * decay - step * x[q];
+    for (int it = 0; it < PER; ++it) {
+      const int64_t e = at(d, row0, col0, it, lane);
+      if (e >= 0) w[it] = __builtin_nontemporal_load(glob(reinterpret_cast<const f32x4*>(a.ns_theta + d.poff + e)));
     }
-    *glob(reinterpret_cast<f32x4*>(tp)) = w;
-    if (a.ns_shadow) {
-      const uint32_t lo = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)w[0]) |
-                          ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)w[1]) << 16);
-      const uint32_t hi = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)w[2]) |
-                          ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)w[3]) << 16);
-      *glob(reinterpret_cast<u32x2*>(a.ns_shadow + d.poff + e)) = u32x2{lo, hi};
-    }
-  };
-  if (!d.ns_tall) {  // W row = X row: the row-wise vectors above
+  }
+  __device__ __forceinline__ void update(const GemmArgs& a, const GemmDesc& d, const char* stage, int row0, int col0,
+                                         int lane) {
+    using S = Stage<float, NB>;
+    const float decay = d.ns_decay, step = d.ns_step;
 #pragma unroll
-    for (int it = 0; it < S::PER_LANE; ++it) {
+    for (int it = 0; it < PER; ++it) {
+      const int64_t e = at(d, row0, col0, it, lane);
       const int v = it * 64 + lane;
-      const int r = v / S::VPR, c = v % S::VPR;
-      const int row = row0 + r, col = col0 + c * 4;
-      if (row >= d.M || col >= d.N) continue;
-      update((int64_t)row * d.N + col, *reinterpret_cast<const f32x4*>(stage + r * S::RS + c * 16));
-    }
-  } else {  // W row = X column: 4 consecutive staged rows of one staged column
-    constexpr int CV = 32 / 4;
-#pragma unroll
-    for (int it = 0; it < NB * 32 * CV / 64; ++it) {
-      const int v = it * 64 + lane;
-      const int c = v / CV, r = (v % CV) * 4;
-      const int wrow = col0 + c, wcol = row0 + r;
-      if (wrow >= d.N || wcol >= d.M) continue;
       f32x4 x;
+      if (!d.ns_tall) {
+        x = *reinterpret_cast<const f32x4*>(stage + (v / S::VPR) * S::RS + (v % S::VPR) * 16);
+      } else {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) x[q] = *reinterpret_cast<const float*>(stage + (r + q) * S::RS + c * 4);
-      update((int64_t)wrow * d.M + wcol, x);
+        for (int q = 0; q < 4; ++q)
+          x[q] = *reinterpret_cast<const float*>(stage + ((v % 8) * 4 + q) * S::RS + (v / 8) * 4);
+      }
+      if (e < 0) continue;
+      f32x4 o;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+#pragma clang fp contract(off)
+        o[q] = w[it][q] * decay - step * x[q];
+      }
+      __builtin_nontemporal_store(o, glob(reinterpret_cast<f32x4*>(a.ns_theta + d.poff + e)));
+      if (a.ns_shadow) *glob(reinterpret_cast<u32x2*>(a.ns_shadow + d.poff + e)) = Quad<__bf16>::put(o);
     }
   }
-}
+};
 
 // Weight-gradient rows with the optimizer fused: each staged vector holds the
 // gradients of 4 consecutive weights, which are updated in place (theta, both
@@ -1252,16 +1266,28 @@ __device__ __forceinline__ void dw_adamw_tile(const GemmArgs& a, const GemmDesc&
 // the bias (forward), the keep/ReLU mask words of the previous layer (dX).
 // Word (i, j) covers rows 32*i .. 32*i+31 of the wave's block, column
 // lane%32 of block j.
-template <int SH>
+// Newton-Schulz: the rows of Y (tiles of at most four blocks a wave).
+struct EpiNone {};
+template <typename T, int EPI, int SH>
 struct EpiPre {
-  uint32_t w[Shape<SH>::MB][Shape<SH>::NB];
-  float bias[Shape<SH>::NB];
+  static constexpr int MB = Shape<SH>::MB, NB = Shape<SH>::NB;
+  uint32_t w[MB][NB];
+  float bias[NB];
+  std::conditional_t<EPI == EPI_NS && MB * NB <= 4, NsRows<T, NB>, EpiNone> y[MB];
 };
 
-template <int EPI, int SH>
+template <typename T, int EPI, int SH>
 __device__ __forceinline__ void epi_prefetch(const GemmDesc& d, const Tile& t, int wm, int wn, int lane,
-                                             EpiPre<SH>& pre) {
+                                             EpiPre<T, EPI, SH>& pre) {
   constexpr int MB = Shape<SH>::MB, NB = Shape<SH>::NB;
+  if constexpr (EPI == EPI_NS) {
+    if constexpr (MB * NB <= 4) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+        pre.y[i].load(d, t.m0 + wm * MB * 32 + 32 * i, t.n0 + wn * NB * 32, lane);
+    }
+    return;
+  }
   const int colL = t.n0 + wn * NB * 32 + (lane & 31);
   const int rb0 = (t.m0 + wm * MB * 32) / 32;
 #pragma unroll
@@ -1286,7 +1312,7 @@ __device__ __forceinline__ void epi_prefetch(const GemmDesc& d, const Tile& t, i
 template <typename T, int EPI, int SH>
 __device__ __forceinline__ void epilogue(const GemmArgs& a, const GemmDesc& d, const Tile& t,
                                          f32x16 (&acc)[Shape<SH>::MB][Shape<SH>::NB], int wm, int wn, int lane,
-                                         int mv, int nv, char* stage, const EpiPre<SH>& pre,
+                                         int mv, int nv, char* stage, const EpiPre<T, EPI, SH>& pre,
                                          char* xlds = nullptr) {
   constexpr int MB = Shape<SH>::MB, NB = Shape<SH>::NB;
   const int hv = lane >> 5;
@@ -1321,30 +1347,42 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const GemmDesc& d, c
     }
   } else if constexpr (EPI == EPI_NS) {
     using S = Stage<float, NB>;
+    static_assert(S::NPASS == 1, "whole 32-row blocks");
+    constexpr bool AHEAD = MB * NB <= 4;  // Y read at the tile's start; the larger tiles have no registers for it
+    const bool mirror = a.ns_sym && t.m0 < t.n0;  // uniform: a tile above the diagonal also writes its mirror image
+    NsWeights<NB> wt;
+    if (a.ns_theta && mv > 0) wt.load(a, d, row0, col0, lane);
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
       if (i >= mv) continue;
+      NsRows<T, NB> late;
+      if constexpr (!AHEAD) late.load(d, row0 + 32 * i, col0, lane);
 #pragma unroll
-      for (int p = 0; p < S::NPASS; ++p) {
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
+        for (int g = 0; g < S::GP; ++g)
 #pragma unroll
-          for (int g = 0; g < S::GP; ++g)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              stage_put<float, NB>(stage, j, g, q, lane, acc[i][j][4 * (p * S::GP + g) + q]);
+          for (int q = 0; q < 4; ++q) stage_put<float, NB>(stage, j, g, q, lane, acc[i][j][4 * g + q]);
+      wave_sync_lds();
+      const NsRows<T, NB>& ys = [&]() -> const NsRows<T, NB>& {
+        if constexpr (AHEAD)
+          return pre.y[i];
+        else
+          return late;
+      }();
+      if (a.ns_theta) {  // uniform: the last iteration applies the Muon update instead of storing X
+        stage_rows_ns<T, NB, false>(a, d, stage, ys, row0 + 32 * i, col0, false, lane);
         wave_sync_lds();
-        if (a.ns_theta) {  // uniform: the last iteration applies the Muon update instead of storing X
-          stage_update_ns<T, NB>(a, d, stage, row0 + 32 * i + S::ROWS * p, col0, lane);
-        } else {
-          stage_flush_ns<T, NB>(stage, static_cast<T*>(d.C), d.ldc, static_cast<const T*>(d.Y), d.ldy, a.ns_alpha,
-                                a.ns_beta, row0 + 32 * i + S::ROWS * p, col0, d.M, d.N, lane);
-          if (a.ns_sym && t.m0 < t.n0)  // uniform: a tile above the diagonal also writes its mirror image
-            stage_flush_ns_mirror<T, NB>(stage, static_cast<T*>(d.C), d.ldc, static_cast<const T*>(d.Y), d.ldy,
-                                         a.ns_alpha, a.ns_beta, row0 + 32 * i + S::ROWS * p, col0, d.M, d.N, lane);
+        wt.update(a, d, stage, row0 + 32 * i, col0, lane);
+        if (i + 1 < mv) wt.load(a, d, row0 + 32 * (i + 1), col0, lane);
+      } else {
+        stage_rows_ns<T, NB, true>(a, d, stage, ys, row0 + 32 * i, col0, mirror, lane);
+        if (mirror) {
+          wave_sync_lds();
+          stage_mirror_ns<T, NB>(d, stage, row0 + 32 * i, col0, lane);
         }
-        wave_sync_lds();
       }
+      wave_sync_lds();
     }
   } else if constexpr (EPI == EPI_DX) {
     // dZ = dH * [H_prev > 0] * s; the keep/ReLU decisions of the forward pass
@@ -1615,8 +1653,8 @@ __device__ __forceinline__ void run_tile(const GemmArgs& a, const GemmDesc& d, c
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-  EpiPre<SH> pre;
-  epi_prefetch<EPI, SH>(d, t, wm, wn, lane, pre);
+  EpiPre<T, EPI, SH> pre;
+  epi_prefetch<T, EPI, SH>(d, t, wm, wn, lane, pre);
 
   if constexpr (LA::dma) {
     static_assert(LB::dma, "both operands staged the same way");
@@ -1745,8 +1783,8 @@ __device__ __forceinline__ void run_tile_emb(const GemmArgs& a, const GemmDesc& 
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-  EpiPre<SH> pre;
-  epi_prefetch<EPI, SH>(d, t, wm, wn, lane, pre);
+  EpiPre<T, EPI, SH> pre;
+  epi_prefetch<T, EPI, SH>(d, t, wm, wn, lane, pre);
   // the producer (A or B) and the streamed operand (B = W_1, or A = dZ_1)
   std::conditional_t<FWD, EmbRowsProducer<T, TM, 64 * NW>, EmbColsProducer<T>> ep;
   if constexpr (FWD) {
