@@ -497,13 +497,15 @@ void add_tiles(Plan& p, Launch& ln, int d, int M, int N, int kdepth) {
     const int r = E % kBigTile;
     return r == 0 ? E : (r > kSmallTile ? E - r + kBigTile : E - r);
   };
-  if (p.tile_set == TILES_WIDE) {
-    // 128 x 256 tiles; a last strip of at most 128 columns on 256 x 128 tiles
+  if (p.tile_set == TILES_WIDE || p.tile_set == TILES_HUGE) {
+    // 128 x 256 (huge: 256 x 256) tiles; a last strip of at most 128 columns on 256 x 128 tiles
     const int r = N % kBigTile, Nw = r > 0 && r <= kSmallTile ? N - r : N;
-    for (int m0 = 0; m0 < M; m0 += kSmallTile)
+    const bool huge = p.tile_set == TILES_HUGE;
+    const int tm = huge ? kBigTile : kSmallTile;
+    for (int m0 = 0; m0 < M; m0 += tm)
       for (int n0 = 0; n0 < Nw; n0 += kBigTile) {
-        p.tiles.push_back(Tile{d, m0, n0, kShapeWide});
-        p.cost.push_back((int64_t)kdepth * std::min(kSmallTile, M - m0) * std::min(kBigTile, N - n0));
+        p.tiles.push_back(Tile{d, m0, n0, huge ? kShapeHuge : kShapeWide});
+        p.cost.push_back((int64_t)kdepth * std::min(tm, M - m0) * std::min(kBigTile, N - n0));
       }
     if (Nw < N)
       for (int m0 = 0; m0 < M; m0 += kBigTile) {
@@ -756,10 +758,19 @@ constexpr int kTallMinTiles = 1024, kTallMinDepthDw = 2048;
 // 256..1024 at batch 1024 (~220 a launch) 636 / 634 us; with mini tiles up to
 // 640 small ones 668 us.
 constexpr int kMiniMaxTiles = 256;
-TileSet launch_tiles(const pack_handle* h, int forced, int64_t n_small, int min_depth = 0) {
+// Huge tiles for forward (and evaluation) launches from kHugeMinFwd small ones
+// on and data-gradient launches from kHugeMinDx on: at one workgroup per CU a
+// launch needs several rounds of them.  Measured, tall / huge: evaluation of 64
+// members of widths 256..1024 (5,400 small tiles a launch) 22.29 / 21.44 ms, a
+// prediction by 32 of them (5,600) 3.46 / 3.31 ms; steps, all tall / forward
+// huge / data gradients too: widths 64..2048 at batch 2048 (4,350) 6.36 / 6.26 /
+// 6.13 ms, 256..1024 at batch 1024 (1,350) 1.279 / 1.265 / 1.284 ms.
+constexpr int kHugeMinFwd = 1024, kHugeMinDx = 2048;
+TileSet launch_tiles(const pack_handle* h, int forced, int64_t n_small, int huge_min = 0, int min_depth = 0) {
   if (forced >= 0) return (TileSet)forced;
   if (n_small < kMiniMaxTiles) return TILES_MINI;
   if (h->prec != Prec::BF16 || h->Bp < min_depth) return TILES_SMALL;
+  if (huge_min > 0 && n_small >= huge_min) return TILES_HUGE;
   return n_small >= kTallMinTiles ? TILES_TALL : TILES_SMALL;
 }
 
@@ -925,8 +936,8 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
                 bool sizing = false) {
   Plan p;
   // sizing: small tiles for the main GEMMs (the largest tile count of any choice)
-  auto choose = [&](int forced, int64_t n_small, int min_depth = 0) {
-    return sizing ? TILES_SMALL : launch_tiles(h, forced, n_small, min_depth);
+  auto choose = [&](int forced, int64_t n_small, int huge_min, int min_depth = 0) {
+    return sizing ? TILES_SMALL : launch_tiles(h, forced, n_small, huge_min, min_depth);
   };
   p.tile_set = h->tiles;
   const pack_config& c = h->cfg;
@@ -955,7 +966,7 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     for (int k : group[hf])
       if (h->mem[k].depth >= l) nsm += small_tiles(h->Bp, h->mem[k].dp);
     // the embedded first layer (E produced in the GEMM): its own tile set
-    p.tile_set = l == 1 && h->emb ? (sizing ? TILES_SMALL : h->emb_tiles) : choose(h->tiles_fwd, nsm);
+    p.tile_set = l == 1 && h->emb ? (sizing ? TILES_SMALL : h->emb_tiles) : choose(h->tiles_fwd, nsm, kHugeMinFwd);
     for (int k : group[hf]) {
       const Member& m = h->mem[k];
       if (m.depth < l) continue;
@@ -1011,7 +1022,7 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
       for (int hf = 0; hf < kGroups; ++hf)
         for (int k : group[hf])
           if (h->mem[k].depth >= l) nsm += small_tiles(R, h->mem[k].dp);
-      p.tile_set = l == 1 && h->emb ? (sizing ? TILES_SMALL : h->emb_tiles) : choose(h->tiles_fwd, nsm);
+      p.tile_set = l == 1 && h->emb ? (sizing ? TILES_SMALL : h->emb_tiles) : choose(h->tiles_fwd, nsm, kHugeMinFwd);
       for (int hf = 0; hf < kGroups; ++hf)
         for (int k : group[hf]) {
           const Member& m = h->mem[k];
@@ -1043,7 +1054,7 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     int64_t nsm = 0;
     for (int k : group[hf])
       if (h->mem[k].depth >= l) nsm += small_tiles(h->mem[k].dp, l == 1 ? h->mem[k].p_in : h->mem[k].dp);
-    p.tile_set = l == 1 && h->emb ? TILES_SMALL : choose(h->tiles_dw, nsm, kTallMinDepthDw);
+    p.tile_set = l == 1 && h->emb ? TILES_SMALL : choose(h->tiles_dw, nsm, 0, kTallMinDepthDw);
     for (int k : group[hf]) {
       const Member& m = h->mem[k];
       if (m.depth < l) continue;
@@ -1097,7 +1108,7 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
       int64_t nsx = 0;
       for (int k : group[hf])
         if (h->mem[k].depth >= l) nsx += small_tiles(h->Bp, h->mem[k].dp);
-      p.tile_set = choose(h->tiles_dx, nsx);
+      p.tile_set = choose(h->tiles_dx, nsx, kHugeMinDx);
       for (int k : group[hf]) {
         const Member& m = h->mem[k];
         if (m.depth < l) continue;
@@ -1137,7 +1148,7 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
         const GemmDesc& d = p.descs[p.dw[0][l - 1].desc0 + i];
         nsm += small_tiles(d.M, d.N);
       }
-    p.tile_set = choose(h->tiles_dw, nsm, kTallMinDepthDw);
+    p.tile_set = choose(h->tiles_dw, nsm, 0, kTallMinDepthDw);
     for (int l = h->emb ? 2 : 1; l <= c.L; ++l) {
       const Launch& ln = p.dw[0][l - 1];
       for (int i = 0; i < ln.ndesc; ++i) {
@@ -1539,17 +1550,18 @@ int pack_init(const pack_config* cfg, pack_handle** out) {
     h->tiles = v == "big" ? TILES_BIG : (v == "tall" ? TILES_TALL : TILES_SMALL);
   }
   if (h->prec == Prec::FP32) h->tiles = TILES_SMALL;
-  auto tile_env = [&](const char* name, bool main = true) {
+  auto tile_env = [&](const char* name, bool main = true, bool huge = false) {
     const char* e = getenv(name);
     if (!e && main) e = getenv("TABPACK_GEMM_TILES");
     if (!e) return -1;
     const std::string v(e);
     if (v == "mini") return (int)TILES_MINI;
     if (h->prec == Prec::FP32) return (int)TILES_SMALL;
+    if (v == "huge" && huge) return (int)TILES_HUGE;
     return (int)(v == "big" ? TILES_BIG : (v == "tall" ? TILES_TALL : TILES_SMALL));
   };
-  h->tiles_fwd = tile_env("TABPACK_TILES_FWD");
-  h->tiles_dx = tile_env("TABPACK_TILES_DX");
+  h->tiles_fwd = tile_env("TABPACK_TILES_FWD", true, true);
+  h->tiles_dx = tile_env("TABPACK_TILES_DX", true, true);
   h->tiles_dw = tile_env("TABPACK_TILES_DW");
   // Newton-Schulz GEMMs: small tiles measured 3.79 ms per Muon step on the
   // 64-member regression workload, tall 4.03, big 5.53; TABPACK_NS_TILES overrides

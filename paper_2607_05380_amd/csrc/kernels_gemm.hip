@@ -14,6 +14,8 @@
 //         on a member's row edge.
 //   big   256 x 256 (waves 128 x 128), one workgroup per CU, with small tiles
 //         on a member's edges.
+//   huge  256 x 256 on 8 waves (128 x 64), one workgroup per CU (run_tile8).
+//   mini  64 x 64 (waves 32 x 32), for launches that would leave CUs idle.
 // The small tile is bound by the bytes in flight per CU rather than by LDS or
 // MFMA throughput: each workgroup has one 64-deep K step (32 KB) in flight
 // while it computes the previous one, against a direct-load latency of about
@@ -162,6 +164,12 @@ struct Shape<kShapeWide> {
 template <>
 struct Shape<kShapeTall8> {
   static constexpr int MB = 2, NB = 2, TM = 256, TN = 128;
+  static constexpr int STAGE = 32 * (NB * 128 + 32);
+};
+
+template <>
+struct Shape<kShapeHuge> {
+  static constexpr int MB = 4, NB = 2, TM = 256, TN = 256;
   static constexpr int STAGE = 32 * (NB * 128 + 32);
 };
 
@@ -380,12 +388,13 @@ __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, char* lds, uint3
 // w*PER .. w*PER+PER-1.  Lane i lands at row (i / CPR) of the block, chunk
 // position i % CPR, so it fetches the row's chunk (i % CPR) ^ f(row).  f of a
 // block's rows depends only on the block's parity.
-template <int R, int KS>
+template <int R, int KS, int NW = 4>
 struct DmaKmaj {
   static constexpr int CPR = 2 * KS;           // 16-byte chunks per row
   static constexpr int BR = 64 / CPR;          // rows per 1 KB block
-  static constexpr int PER = R / BR / 4;       // blocks per wave
-  static_assert(PER % 2 == 0, "block parity follows p");
+  static constexpr int PER = R / BR / NW;      // blocks per wave
+  // (32-deep steps: a block is 16 rows, a whole period of f)
+  static_assert(PER % 2 == 0 || (KS == 2 && PER == 1), "block parity follows p");
   __amdgpu_buffer_rsrc_t rsrc;
   uint32_t voff[PER];  // byte offset (depth 0) of this lane's vector in block p, or kOob
   int kofs[2];         // depth offset (elements) of this lane's vector per block parity
@@ -423,13 +432,17 @@ struct DmaKmaj {
         dma16(rsrc, lds + (wave * PER + p) * 1024, ((p & 1) ? kin1 : kin0) ? voff[p] : kOob, soff);
     }
   }
+  // load p of the K step at k0 (a step at or past kd reads zeros)
+  __device__ __forceinline__ void issue_one(char* lds, int k0, int kd, int p) const {
+    dma16(rsrc, lds + (wave * PER + p) * 1024, k0 + kofs[p & 1] < kd ? voff[p] : kOob, (uint32_t)k0 * 2u);
+  }
 };
 
 // Rows-contiguous bf16 operand -> rows-contiguous LDS layout (16*KS depth rows x R).
-template <int R, int KS>
+template <int R, int KS, int NW = 4>
 struct DmaRmaj {
   static constexpr int RBYTES = 2 * R;                      // bytes per depth row in LDS
-  static constexpr int PER = 16 * KS * RBYTES / 1024 / 4;   // chunks per wave
+  static constexpr int PER = 16 * KS * RBYTES / 1024 / NW;  // chunks per wave
   __amdgpu_buffer_rsrc_t rsrc;
   uint32_t ldb;        // bytes per depth row in HBM
   uint32_t voff[PER];  // byte offset (depth 0) of the vector this lane fetches for chunk p, or kOob
@@ -476,6 +489,10 @@ struct DmaRmaj {
       for (int p = 0; p < PER; ++p)
         dma16(rsrc, lds + (wave * PER + p) * 1024, k0 + krow[p] < kd ? voff[p] : kOob, soff);
     }
+  }
+  // load p of the K step at k0, without a row table (a step at or past kd reads zeros)
+  __device__ __forceinline__ void issue_one(char* lds, int k0, int kd, int p) const {
+    dma16(rsrc, lds + (wave * PER + p) * 1024, k0 + krow[p] < kd ? voff[p] : kOob, (uint32_t)k0 * ldb);
   }
 };
 
@@ -1930,7 +1947,162 @@ __device__ __forceinline__ void run_tile_emb(const GemmArgs& a, const GemmDesc& 
   epilogue<T, EPI, SH>(a, d, t, acc, wm, wn, lane, mv, nv, lds0 + wave * Shape<SH>::STAGE, pre);
 }
 
+// One output tile on 8 waves, one workgroup per CU: 256 x 256 (waves in 2 x 4,
+// 128 x 64 each) or, for a last strip of at most 128 columns, 256 x 128 (waves
+// in 4 x 2, 64 x 64 each).  Operands stream through five stages of 32-deep steps
+// (all 160 KB of LDS).  What bounds the main loop is the latency of panels that
+// every tile of a round touches first, beyond L2, so the stages are as many as
+// LDS holds (four: 2.5% more time for an evaluation pass), and half the operand
+// bytes per product of the 128 x 128 tiles help by as much: 22.3 -> 21.4 ms for
+// 64 members of widths 256..1024 on 70,000 rows.
+// There is no second workgroup to cover this one's waits, so they are covered
+// inside it: at the top of step kt the loads of step kt + 1 have landed (two
+// steps are in flight, a fourth is issued), and a wave reads the fragments of its
+// next 16-deep half step, across the step's barrier, while the MFMAs of the
+// present one run.  The loads are issued one by one between the MFMAs: in one
+// burst after the barrier they fill the address unit's queue and every wave
+// waits in issue (4,330 -> 4,020 cycles per 64-deep step; 2,048 are MFMA).
+constexpr int kHugeKs = 2, kHugeNs = 5;
+constexpr int kLdsHuge = kHugeNs * 512 * 32 * kHugeKs;
+template <int AK, int BK_, int EPI, int SH>
+__device__ __forceinline__ void run_tile8(const GemmArgs& a, const GemmDesc& d, const Tile& t, char* lds0, int tid,
+                                          int wave) {
+  using T = __bf16;
+  constexpr int MB = Shape<SH>::MB, NB = Shape<SH>::NB, TM = Shape<SH>::TM, TN = Shape<SH>::TN;
+  constexpr int KS = kHugeKs, NS = kHugeNs, WC = SH == kShapeHuge ? 4 : 2;
+  static_assert(AK == OP_KMAJ && KS == 2 && NS >= 4 && kLdsHuge <= 160 * 1024, "the loop below");
+  static_assert((TM / (MB * 32)) * WC == 8 && TN == WC * NB * 32, "8 waves");
+  static_assert(8 * Shape<SH>::STAGE <= kLdsHuge, "epilogue staging");
+  constexpr bool TRB = BK_ == OP_RMAJ;
+  using LA = DmaKmaj<TM, KS, 8>;
+  using LB = std::conditional_t<TRB, DmaRmaj<TN, KS, 8>, DmaKmaj<TN, KS, 8>>;
+  const int lane = tid & 63;
+  const int wm = wave / WC, wn = wave % WC;
+  int mv, nv;
+  tile_extents<EPI, SH>(d, t, wm, wn, mv, nv);
+  f32x16 acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  EpiPre<T, EPI, SH> pre;
+  epi_prefetch<T, EPI, SH>(d, t, wm, wn, lane, pre);
+  constexpr int BKE = 16 * KS, TA = TM * 32 * KS, ST = TA + TN * 32 * KS;
+  constexpr int PS = LA::PER + LB::PER;
+  constexpr int NRD = MB + (TRB ? 2 * NB : NB);  // LDS reads per half step
+  const int nk = (d.Kd + BKE - 1) / BKE;
+  LA la;
+  LB lb;
+  if constexpr (EPI == EPI_FWD || EPI == EPI_FWD_EVAL)
+    la.init(static_cast<const T*>(d.A), d.lda, t.m0, d.M, d.Kd, wave, lane,
+            d.xrows_n > 0 ? a.idx + (int64_t)d.member * d.xrows_n : nullptr, d.xrows_n, d.xsrc_rows);
+  else
+    la.init(static_cast<const T*>(d.A), d.lda, t.m0, d.M, d.Kd, wave, lane);
+  lb.init(static_cast<const T*>(d.B), d.ldb, t.n0, d.N, d.Kd, wave, lane);
+  // load p (of PS) of step s; a step past the last one reads zeros into a stage nobody reads
+  // (b: its stage)
+  auto issue = [&](char* b, int s, int p) {
+    if (p < LA::PER)
+      la.issue_one(b, s * BKE, d.Kd, p);
+    else
+      lb.issue_one(b + TA, s * BKE, d.Kd, p - LA::PER);
+  };
+  struct Frag {
+    bf16x8 a[MB], b[NB];
+  } f0, f1;
+  auto rd = [&](Frag& f, const char* b, int ks) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i) f.a[i] = frag_kmaj_asm<KS>(b, wm * MB * 32 + i * 32, ks, lane);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if constexpr (TRB)
+        f.b[j] = frag_tr_asm<TN>(b + TA, wn * NB * 32 + j * 32, ks, lane);
+      else
+        f.b[j] = frag_kmaj_asm<KS>(b + TA, wn * NB * 32 + j * 32, ks, lane);
+    }
+  };
+  // every LDS read but the last n of this wave is done (n: the reads of the half step just requested)
+  auto wait_rd = [](auto newer) {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xc07f | ((newer.value ? NRD : 0) << 8));  // lgkmcnt(NRD) or (0)
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  static_assert(NRD < 16, "lgkmcnt range");
+  // the MFMAs of a half step, and between them the loads p0 .. p1 - 1 of step s
+  auto mma = [&](const Frag& f, char* b, int s, auto P0, auto P1) {
+    constexpr int NP = P1.value - P0.value, G = NP > 0 ? MB * NB / NP : 0;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
+        const int n = i * NB + j;  // load after the first half of each group of G products
+        if (NP > 0 && n % G == G / 2) {
+          __builtin_amdgcn_sched_barrier(0);
+          issue(b, s, P0.value + n / G);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using P0 = std::integral_constant<int, 0>;
+  using PH = std::integral_constant<int, PS / 2>;
+  using PE = std::integral_constant<int, PS>;
+  static_assert(PS % 2 == 0 || PS == 3, "loads of a step between the products of its two halves");
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s)
+#pragma unroll
+    for (int p = 0; p < PS; ++p) issue(lds0 + s * ST, s, p);
+  wait_vm<(NS - 3) * PS, true>();
+  bar();
+  // Blocks outside the member hold zeros and are computed anyway (the two waves
+  // of a SIMD have the same columns, so skipping them frees nothing).
+  rd(f0, lds0, 0);
+  wait_rd(std::false_type{});  // nothing in flight is carried into the loop, here or at its end
+  char* const end = lds0 + NS * ST;
+  char *cur = lds0, *ahead = end - ST;  // stages of steps kt and kt + NS - 1
+#pragma unroll 1
+  for (int kt = 0; kt < nk; ++kt) {
+    if (kt > 0) {
+      // step kt + 1 has landed in every wave's share, and every wave is done
+      // with step kt - 1, whose stage the loads of step kt + NS - 1 overwrite
+      wait_vm<(NS - 3) * PS, true>();
+      bar();
+    }
+    char* const nxt = cur + ST == end ? lds0 : cur + ST;
+    __builtin_amdgcn_sched_barrier(0);
+    rd(f1, cur, 1);
+    mma(f0, ahead, kt + NS - 1, P0{}, PH{});
+    rd(f0, nxt, 0);  // after the last step: zeros of the step past it, unused
+    wait_rd(std::true_type{});
+    mma(f1, ahead, kt + NS - 1, PH{}, PE{});
+    wait_rd(std::false_type{});
+    ahead = cur;
+    cur = nxt;
+  }
+  wait_vm<0, true>();
+  bar();  // the epilogue stages results in the operand buffers
+  epilogue<T, EPI, SH>(a, d, t, acc, wm, wn, lane, mv, nv, lds0 + wave * Shape<SH>::STAGE, pre);
+}
+
 // ----------------------------------------------------------------- kernel --
+// Launches of huge tiles (256 x 256, a last column strip on 256 x 128), bf16.
+template <int AK, int BK_, int EPI>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_kernel_huge(GemmArgs a) {
+  __shared__ __attribute__((aligned(16))) char smem[kLdsHuge];
+  const Tile t = a.tiles[blockIdx.x];
+  if (EPI == EPI_FWD_EVAL && t.m0 >= a.rows_valid) return;  // past the end of a last chunk: nothing reads it
+  const GemmDesc d = a.descs[t.desc];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (t.shape == kShapeHuge)
+    run_tile8<AK, BK_, EPI, kShapeHuge>(a, d, t, smem, tid, wave);
+  else
+    run_tile8<AK, BK_, EPI, kShapeTall8>(a, d, t, smem, tid, wave);
+}
+
 // Launches whose tiles include the big shape: 256x256 tiles with two 64-deep
 // stages (128 KB of LDS), one workgroup (one wave per SIMD) per CU.
 template <typename T, int AK, int BK_, int EPI>
@@ -2050,6 +2222,12 @@ hipError_t launch_t(const GemmArgs& args, hipStream_t s) {
       case TILES_TALL:
         hipLaunchKernelGGL((gemm_kernel_tall<AK, BK_, EPI>), dim3(args.ntiles), dim3(NT), 0, s, args);
         break;
+      case TILES_HUGE:
+        if constexpr (EPI == EPI_FWD || EPI == EPI_FWD_EVAL || EPI == EPI_DX) {
+          hipLaunchKernelGGL((gemm_kernel_huge<AK, BK_, EPI>), dim3(args.ntiles), dim3(512), 0, s, args);
+          break;
+        }
+        return hipErrorInvalidValue;
       case TILES_BIG:
         hipLaunchKernelGGL((gemm_kernel<T, AK, BK_, EPI>), dim3(args.ntiles), dim3(NT), 0, s, args);
         break;

@@ -155,3 +155,34 @@ def test_chunk_rows_do_not_change_predictions(name, over):
         np.testing.assert_array_equal(pk.predict(Xv[:n], ensemble=False).cpu().numpy(), whole[:, :n])
         np.testing.assert_array_equal(pk.predict(Xv[:n], ensemble=True).cpu().numpy(), mean[:n])
         np.testing.assert_array_equal(pk.eval_members(Xv[:n], yv[:n])[0].cpu().numpy(), pred[:, :n])
+
+
+@pytest.mark.parametrize("name,over", [
+    ("regression_onehot", dict(B=300, d_in=8, features="normal")),
+    ("regression_onehot", dict(B=257, d_in=37, features="normal")),
+    ("multiclass_lognormal", dict(B=512, d_in=96)),
+    ("binary_wide", dict(B=65, d_in=200))])
+def test_huge_tiles_bit_identical(monkeypatch, name, over):
+    # 256 x 256 tiles of 8 waves: column remainders from 32 to 256, depths of one
+    # to ten 32-deep steps and ones that end inside a step, partly filled row
+    # tiles; the accumulation order is the small tiles', so the bits are too
+    cfg = configs.workload(name, K=6, L=3, **{k: v for k, v in over.items()})
+    mem = [dict(width=w, dropout=0.1 * (i % 3), lr=2e-3, wd=1e-3, depth=(3, 1, 2)[i % 3])
+           for i, w in enumerate((31, 65, 129, 257, 300, 420))]
+    Xtr, ytr, Xv, yv, _, idx = make_inputs(cfg, 900, 530)
+    X, y, idx_d, Xv, yv = to_dev(Xtr, ytr, idx, Xv, yv)
+    runs = []
+    for tiles in ("small", "huge"):
+        monkeypatch.setenv("TABPACK_TILES_FWD", tiles)
+        monkeypatch.setenv("TABPACK_TILES_DX", tiles)
+        for bind in (False, True):
+            pk = tabpack.Pack(cfg, members=mem).bind()
+            if bind:
+                pk.bind_data(X)
+            got = [pk.train_step(X, y, idx_d, s).cpu().numpy() for s in (1, 2)]
+            got += [t.cpu().numpy() for t in pk.eval_members(Xv, yv)] + [pk.predict(Xv).cpu().numpy()]
+            runs.append(got + state(pk, cfg.get("keep_grads", 1)))
+    for i in (0, 1):
+        assert len(runs[i]) == len(runs[i + 2])
+        for a, b in zip(runs[i], runs[i + 2]):
+            np.testing.assert_array_equal(a, b)
