@@ -759,13 +759,14 @@ constexpr int kTallMinTiles = 1024, kTallMinDepthDw = 2048;
 // 640 small ones 668 us.
 constexpr int kMiniMaxTiles = 256;
 // Huge tiles for forward (and evaluation) launches from kHugeMinFwd small ones
-// on and data-gradient launches from kHugeMinDx on: at one workgroup per CU a
-// launch needs several rounds of them.  Measured, tall / huge: evaluation of 64
-// members of widths 256..1024 (5,400 small tiles a launch) 22.29 / 21.44 ms, a
-// prediction by 32 of them (5,600) 3.46 / 3.31 ms; steps, all tall / forward
-// huge / data gradients too: widths 64..2048 at batch 2048 (4,350) 6.36 / 6.26 /
-// 6.13 ms, 256..1024 at batch 1024 (1,350) 1.279 / 1.265 / 1.284 ms.
-constexpr int kHugeMinFwd = 1024, kHugeMinDx = 2048;
+// on and data-gradient launches from kHugeMinDx on.  Measured, small / tall /
+// huge forward launches: 1,000 rows by 16 of 32 members of widths 256..1024 (700
+// small tiles a launch) 146 / 141 / 137 us, by all 32 (1,400) 205 / 220 / 198;
+// a step of 32 such members (700) 644 / 634 / 632 us, of 24 (525) 504 / 512 /
+// 511; tall / huge: evaluation of 64 members (5,400) 22.3 / 21.4 ms.  Data
+// gradients, steps with tall / huge ones: widths 64..2048 at batch 2048 (4,350)
+// 6.26 / 6.13 ms, 256..1024 at batch 1024 (1,350) 1.265 / 1.284 ms.
+constexpr int kHugeMinFwd = 640, kHugeMinDx = 2048;
 TileSet launch_tiles(const pack_handle* h, int forced, int64_t n_small, int huge_min = 0, int min_depth = 0) {
   if (forced >= 0) return (TileSet)forced;
   if (n_small < kMiniMaxTiles) return TILES_MINI;
