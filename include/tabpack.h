@@ -312,6 +312,20 @@ int pack_debug_dropout_mask(pack_handle* h, uint64_t step, int32_t layer, int32_
                             uint8_t* dev_out, hipStream_t stream);
 int pack_debug_activation(pack_handle* h, int32_t layer, int32_t member, float* host_out);
 
+/* What the planner lays out for a pack, computed on the host (no GPU, no
+ * parameters): pack_debug_plan fills it for `cfg` with the members of
+ * `active` ([K] bytes 0 / 1; NULL: all) in the launches. */
+#define PACK_EVAL_LEVELS 8
+typedef struct pack_plan_info {
+  int64_t tiles, tile_capacity; /* GEMM tiles of the launch tables; entries of their table in the workspace */
+  int64_t eval_operand;         /* bytes of the largest operand read by rows in an evaluation GEMM */
+  int32_t groups, one_stream;   /* member groups of a training step; 1: all its launches on the caller's stream */
+  int32_t eval_levels;          /* sizes of evaluation chunks, largest first: */
+  int32_t eval_rows[PACK_EVAL_LEVELS];  /* their rows */
+  int32_t eval_tiles[PACK_EVAL_LEVELS]; /* the tile set of their last layer's launch */
+} pack_plan_info;
+int pack_debug_plan(const pack_config* cfg, const uint8_t* active, pack_plan_info* out);
+
 /* Per-kernel timing of pack_train_step() with HIP events recorded on the
  * stream each kernel runs on, around every launch (measurement aid; it adds
  * two event records per launch).  pack_profile_enable(h, 1) clears and starts

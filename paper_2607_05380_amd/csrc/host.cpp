@@ -40,7 +40,7 @@ int fail(int code, const char* fmt, ...) {
 constexpr uint32_t kTagHparam = 1, kTagInit = 2;
 // Evaluation and prediction take their rows in chunks of eval_rows() of the
 // levels 0 .. eval_levels - 1 (each a quarter of the one before).
-constexpr int kEvalLevels = 8;
+constexpr int kEvalLevels = PACK_EVAL_LEVELS;
 constexpr int kGroups = 4;  // at most this many member groups run their GEMM chains concurrently
 
 int64_t round_up(int64_t x, int64_t q) { return (x + q - 1) / q * q; }
@@ -178,6 +178,7 @@ struct pack_handle {
   // chunk level; chunks of level i hold Bp << eval_shift >> 2 i rows
   std::vector<Launch> ev[kEvalLevels];
   int eval_shift = 0, eval_levels = 1;
+  int64_t eval_cap = 0;  // rows of a chunk that the GEMM loaders reach (kOperandBytes)
   int last_rows = 0;  // rows of the last forward pass's activation blocks (Bp, or an evaluation chunk's)
   // The members are split into ngroups groups of about equal GEMM work; each
   // group's GEMM chain runs on its own stream (group 0 on the caller's), which
@@ -784,13 +785,26 @@ TileSet launch_tiles(const pack_handle* h, int forced, int64_t n_small, int huge
 // member group / these chunks: 64 members of widths 256..1024 on 70,000 rows
 // 26.1 / 21.6 ms, 32 of them on 20,000 rows 4.56 / 3.38 ms, 16 members of
 // 128..512 on 37 rows 39.9 / 28.6 us (chunks of 512 rows, of 128).
-constexpr int64_t kEvalTiles = 8192, kEvalRows = 8192;
+// Wide inputs bound the growth too: the gathered rows H_0 are one GEMM operand,
+// which must stay below kOperandBytes, and would dominate the workspace
+// (kEvalInputBytes: 8,192 rows of 8,192 fp32 or 16,384 bf16 features).  Where
+// even a chunk of Bp rows holds a larger operand, a chunk takes the rows below
+// the limit (eval_cap).
+constexpr int64_t kEvalTiles = 8192, kEvalRows = 8192, kEvalInputBytes = (int64_t)256 << 20;
 void plan_eval(pack_handle* h) {
-  int64_t n = 0;
-  for (const Member& m : h->mem) n += small_tiles(h->Bp, m.dp);
+  int64_t n = 0, row = h->emb ? 0 : h->Pin;
+  for (const Member& m : h->mem) {
+    n += small_tiles(h->Bp, m.dp);
+    row = std::max(row, (int64_t)m.dp);
+  }
+  const int64_t in_row = h->emb ? 0 : h->Pin * (int64_t)h->elt();
+  h->eval_cap = kOperandBytes / (row * (int64_t)h->elt());
   h->eval_shift = 0;
-  while ((n << (h->eval_shift + 1)) <= kEvalTiles && ((int64_t)h->Bp << (h->eval_shift + 1)) <= kEvalRows)
-    ++h->eval_shift;
+  auto fits = [&](int shift) {
+    const int64_t rows = (int64_t)h->Bp << shift;
+    return n << shift <= kEvalTiles && rows <= kEvalRows && rows * in_row <= kEvalInputBytes;
+  };
+  while (fits(h->eval_shift + 1)) ++h->eval_shift;
   h->eval_levels = 1;
   while (h->eval_levels < kEvalLevels && h->eval_rows(h->eval_levels) >= 64 && h->eval_rows(h->eval_levels) % 32 == 0)
     ++h->eval_levels;
@@ -1524,15 +1538,9 @@ const char* gemm_name(Prec p, OpKind a, OpKind b, EpiKind e) {
   return buf;
 }
 
-}  // namespace
-
-extern "C" {
-
-const char* pack_last_error(void) { return g_err.c_str(); }
-
-int pack_init(const pack_config* cfg, pack_handle** out) {
-  if (!out) return fail(PACK_EINVAL, "out is NULL");
-  *out = nullptr;
+// A handle of the pack with its members, layout and launch rules, without the
+// parameters' initial values.
+int make_pack(const pack_config* cfg, pack_handle** out) {
   int rc = validate(cfg);
   if (rc) return rc;
   pack_handle* h = new (std::nothrow) pack_handle();
@@ -1611,9 +1619,59 @@ int pack_init(const pack_config* cfg, pack_handle** out) {
   set_active_ids(h);
   h->small = small_pack(h, h->active_ids);
   split_members(h);
+  *out = h;
+  return PACK_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+const char* pack_last_error(void) { return g_err.c_str(); }
+
+int pack_init(const pack_config* cfg, pack_handle** out) {
+  if (!out) return fail(PACK_EINVAL, "out is NULL");
+  *out = nullptr;
+  pack_handle* h = nullptr;
+  const int rc = make_pack(cfg, &h);
+  if (rc) return rc;
   init_params(h);
   *out = h;
   g_err.clear();
+  return PACK_OK;
+}
+
+int pack_debug_plan(const pack_config* cfg, const uint8_t* active, pack_plan_info* out) {
+  if (!out) return fail(PACK_EINVAL, "out is NULL");
+  pack_handle* h = nullptr;
+  const int rc = make_pack(cfg, &h);
+  if (rc) return rc;
+  carve(h, nullptr, h->b);  // addresses from 0, never read
+  if (active) {
+    for (int k = 0; k < cfg->K; ++k) h->active[k] = active[k] ? 1 : 0;
+    set_active_ids(h);
+    split_members(h);
+  }
+  const Plan plan = build_plan(h, h->b, h->group);
+  *out = pack_plan_info{};
+  out->tiles = (int64_t)plan.tiles.size();
+  out->tile_capacity = (int64_t)h->b.tile_cap;
+  out->groups = h->ngroups;
+  out->one_stream = h->one_stream ? 1 : 0;
+  out->eval_levels = h->eval_levels;
+  for (int lv = 0; lv < h->eval_levels; ++lv) {
+    out->eval_rows[lv] = h->eval_rows(lv);
+    for (const Launch& ln : plan.ev[lv]) {
+      if (lv == 0)
+        for (int i = 0; i < ln.ndesc; ++i) {
+          const GemmDesc& d = plan.descs[ln.desc0 + i];
+          const int64_t rows = std::min((int64_t)d.M, h->eval_cap);
+          if (d.A) out->eval_operand = std::max(out->eval_operand, rows * d.lda * (int64_t)h->elt());
+        }
+      if (!plan.ev[lv].empty()) out->eval_tiles[lv] = plan.ev[lv].back().ts;
+    }
+  }
+  pack_destroy(h);
   return PACK_OK;
 }
 
@@ -2046,12 +2104,12 @@ int pack_eval_members(pack_handle* h, const float* Xv, const void* yv, int64_t N
   if (h->emb) HIP_TRY(emb_tables(h, h->b.d_active, h->active_ids, stream));
   for (int64_t r0 = 0; r0 < Nv;) {
     const int lv = eval_level(h, Nv - r0), R = h->eval_rows(lv);
-    a.rows_valid = (int)std::min<int64_t>(R, Nv - r0);
+    a.rows_valid = (int)std::min({(int64_t)R, Nv - r0, h->eval_cap});
     HIP_TRY(eval_forward(h, a, Xv, Nv, r0, lv, stream));
     HIP_TRY(launch_head_fwd(h->prec, h->task, kHeadEval, h->b.H, h->b.theta, h->b.d_mem, nact, h->Bp, R, c.d_out,
                             yv, nullptr, c.B, a.rows_valid, r0, Nv, nullptr, nullptr, pred_out, nullptr,
                             h->b.d_active, stream));
-    r0 += R;
+    r0 += a.rows_valid;
   }
   HIP_TRY(launch_eval_score(h->task, pred_out, yv, nact, Nv, score_out, h->b.d_active, stream));
   return PACK_OK;
@@ -2070,7 +2128,7 @@ int pack_predict(pack_handle* h, const float* X, int64_t N, int32_t mode, float*
   if (h->emb) HIP_TRY(emb_tables(h, h->b.d_active, h->active_ids, stream));
   for (int64_t r0 = 0; r0 < N;) {
     const int lv = eval_level(h, N - r0), R = h->eval_rows(lv);
-    a.rows_valid = (int)std::min<int64_t>(R, N - r0);
+    a.rows_valid = (int)std::min({(int64_t)R, N - r0, h->eval_cap});
     HIP_TRY(eval_forward(h, a, X, N, r0, lv, stream));
     if (mode == PACK_PREDICT_MEMBERS) {
       // member i (i-th active id) writes rows r0.. of out[i, :, :]
@@ -2084,7 +2142,7 @@ int pack_predict(pack_handle* h, const float* X, int64_t N, int32_t mode, float*
                               nullptr, h->b.d_active, stream));
       HIP_TRY(launch_ensemble_mean(h->b.dY, nact, R, a.rows_valid, c.d_out, r0, out, stream));
     }
-    r0 += R;
+    r0 += a.rows_valid;
   }
   return PACK_OK;
 }

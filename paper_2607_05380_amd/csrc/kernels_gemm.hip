@@ -276,6 +276,7 @@ __device__ __forceinline__ const TABPACK_GLOBAL V* glob(const V* p) {
 // as zero -- no branch and no select on the data, so the loads stay in flight
 // across the MFMAs of the current step.
 constexpr uint32_t kOob = 0x80000000u;   // an offset outside every operand buffer
+static_assert(kOperandBytes + 16 == (int64_t)kOob, "operands end below the offset that stands for outside");
 constexpr int kRsrcWord3 = 0x00020000;   // gfx9 raw buffer descriptor: 32-bit data format, no swizzle
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, int64_t bytes) {

@@ -37,6 +37,10 @@ enum TileSet : int {
   TILES_MINI = 4,
   TILES_HUGE = 5
 };
+// The GEMM loaders address an operand by 32-bit byte offsets, those from 2 GiB
+// on standing for "outside" (they read as zeros): a larger operand would lose
+// its last rows.
+constexpr int64_t kOperandBytes = ((int64_t)1 << 31) - 16;
 constexpr int kPartRows = 64;   // rows per bias-gradient partial written by the dX epilogue
 constexpr int kXcds = 8;        // MI355X: workgroups go round-robin to 8 XCDs
 static_assert(kRowAlign % kBigTile == 0, "row padding must cover whole GEMM row tiles");

@@ -27,7 +27,7 @@ SYMBOLS = ["pack_last_error", "pack_init", "pack_destroy", "pack_get_hparams", "
            "pack_select", "pack_member_param_count", "pack_get_params", "pack_set_params",
            "pack_get_grads", "pack_get_moments", "pack_debug_dropout_mask", "pack_debug_activation",
            "pack_profile_enable", "pack_profile_read", "pack_set_active", "pack_predict", "pack_status",
-           "pack_stream_copy", "pack_select_static", "pack_bind_data"]
+           "pack_stream_copy", "pack_select_static", "pack_bind_data", "pack_debug_plan"]
 
 
 class MemberHP(ctypes.Structure):
@@ -62,6 +62,12 @@ class KernelStat(ctypes.Structure):
     _fields_ = [("name", ctypes.c_char * 64), ("kind", ctypes.c_int32), ("launches", ctypes.c_int32),
                 ("total_ms", ctypes.c_double), ("flops", ctypes.c_double),
                 ("bytes", ctypes.c_double), ("busy_ms", ctypes.c_double)]
+
+
+class PlanInfo(ctypes.Structure):
+    _fields_ = [("tiles", ctypes.c_int64), ("tile_capacity", ctypes.c_int64), ("eval_operand", ctypes.c_int64),
+                ("groups", ctypes.c_int32), ("one_stream", ctypes.c_int32), ("eval_levels", ctypes.c_int32),
+                ("eval_rows", ctypes.c_int32 * 8), ("eval_tiles", ctypes.c_int32 * 8)]
 
 
 class PackError(RuntimeError):
@@ -107,6 +113,7 @@ def load_library(path=LIB_PATH):
         "pack_status": ([H, ctypes.POINTER(ctypes.c_uint32), vp], ctypes.c_int),
         "pack_stream_copy": ([vp, vp, sz, vp], ctypes.c_int),
         "pack_bind_data": ([H, vp, i64, vp, sz, vp], ctypes.c_int),
+        "pack_debug_plan": ([ctypes.POINTER(PackConfig), vp, ctypes.POINTER(PlanInfo)], ctypes.c_int),
     }
     for name, (args, res) in sig.items():
         fn = getattr(L, name)
@@ -408,6 +415,19 @@ class Pack:
         out = np.empty((self.B, w), dtype=np.float32)
         _check(self.lib.pack_debug_activation(self.h, layer, k, out.ctypes.data))
         return out
+
+
+def debug_plan(cfg, members=None, active=None):
+    """What the planner lays out for a pack (pack_plan_info as a dict); host only, no parameters are made."""
+    c, keep = make_config(cfg, members)
+    on = None if active is None else (ctypes.c_uint8 * c.K)(*[1 if a else 0 for a in active])
+    info = PlanInfo()
+    _check(load_library().pack_debug_plan(ctypes.byref(c), on, ctypes.byref(info)))
+    del keep
+    n = info.eval_levels
+    return dict(tiles=info.tiles, tile_capacity=info.tile_capacity, eval_operand=info.eval_operand,
+                groups=info.groups, one_stream=bool(info.one_stream), eval_rows=list(info.eval_rows[:n]),
+                eval_tiles=list(info.eval_tiles[:n]))
 
 
 def stream_copy(src, dst):

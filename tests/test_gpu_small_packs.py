@@ -186,3 +186,24 @@ def test_huge_tiles_bit_identical(monkeypatch, name, over):
         assert len(runs[i]) == len(runs[i + 2])
         for a, b in zip(runs[i], runs[i + 2]):
             np.testing.assert_array_equal(a, b)
+
+
+def test_wide_inputs_predict_the_same_in_chunks():
+    # 8,200 rows of 66,000 fp32 features are 2.02 GiB: chunks must end below the
+    # loaders' 32-bit offsets.  The last rows of a long input are those of a
+    # short one, and a block of rows agrees with the oracle's layer in fp64.
+    import torch
+    d_in, N = 66_000, 8_200
+    cfg = configs.workload("regression_onehot", K=2, B=256, L=1, d_in=d_in, precision="fp32")
+    pk = tabpack.Pack(cfg, members=[dict(width=w, dropout=0.0, lr=1e-3, wd=1e-3) for w in (16, 33)]).bind()
+    g = torch.Generator(device="cuda").manual_seed(3)
+    X = torch.randn(N, d_in, device="cuda", generator=g)
+    whole = pk.predict(X).cpu().numpy()
+    for r0, r1 in ((0, 40), (4_050, 4_110), (8_100, 8_200)):
+        np.testing.assert_array_equal(pk.predict(X[r0:r1].contiguous()).cpu().numpy(), whole[:, r0:r1])
+    for k in range(2):
+        (W1, b1), (W2, b2) = [(W.astype(np.float64), b.astype(np.float64)) for W, b in pk.get_params(k)]
+        z = np.maximum(X[8_135:].cpu().numpy().astype(np.float64) @ W1.T + b1, 0.0) @ W2.T + b2
+        # 66,000 fp32 products with weights of at most 66,000^-1/2 and normal
+        # features: rounding of about 66,000^1/2 2^-24 per activation of size 0.6
+        assert np.abs(whole[k, 8_135:] - z).max() < 1e-4
