@@ -1153,8 +1153,9 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     }
     p.dx[hf].push_back(x);
   }
-  if (h->one_stream && h->small && !sizing) {
-    // one launch for the weight gradients of all layers, from the same descriptors
+  if (h->small && (h->one_stream || sizing)) {
+    // one launch for the weight gradients of all layers, from the same
+    // descriptors: a second copy of their tiles in the table
     Launch& w = p.dw_all;
     w = Launch{0, 0, (int)p.tiles.size(), 0, 0.0, 0.0};
     int64_t nsm = 0;
@@ -1289,15 +1290,18 @@ size_t carve(const pack_handle* h, char* base, Bufs& bf) {
     bf.mB = cv.take<char>((size_t)ae * h->elt());
   }
   // The tables are sized by a plan with every member in one launch per layer
-  // and small tiles for the main GEMMs: any tile set, and any split of the
-  // members, takes at most as many tiles.
-  // Mini tiles are chosen only below kMiniMaxTiles small ones (or forced):
-  // at most 4 times as many, in every launch of every group.
+  // (and, for small packs, the weight gradients of all layers once more in
+  // one) and small tiles for the main GEMMs.  Tall, wide, huge and big tile
+  // sets take at most as many, and a split of the members the same.  Mini
+  // tiles, four times as many at most, are chosen only for launches of fewer
+  // than kMiniMaxTiles small ones (up to 4 L + 5 launches a group -- forward
+  // twice, data and weight gradients, dE, five Newton-Schulz products --, the
+  // weight gradients in one, L an evaluation level), or forced.
   Plan plan = build_plan(h, bf, all, true);
   const bool mini_forced = h->tiles_fwd == TILES_MINI || h->tiles_dx == TILES_MINI || h->tiles_dw == TILES_MINI ||
                            h->ns_tiles == TILES_MINI;
-  bf.tile_cap = mini_forced ? 4 * plan.tiles.size()
-                            : plan.tiles.size() + (size_t)4 * kMiniMaxTiles * (kGroups * (4 * (size_t)c.L + 7) + kEvalLevels * (size_t)c.L);
+  const size_t launches = kGroups * (4 * (size_t)c.L + 5) + 1 + kEvalLevels * (size_t)c.L;
+  bf.tile_cap = mini_forced ? 4 * plan.tiles.size() : plan.tiles.size() + (size_t)4 * kMiniMaxTiles * launches;
   if (h->muon) {
     bf.mpart = cv.take<double>(plan.mtiles.size());
     bf.minv = cv.take<float>(plan.mmats.size());

@@ -20,3 +20,26 @@ def test_evaluation_operands_below_the_loaders_limit(K, width, B, d_in, precisio
     p = tabpack.debug_plan(cfg, members=members(K, width))
     assert 0 < p["eval_operand"] <= OPERAND_MAX
     assert all(r >= 32 and r % 32 == 0 for r in p["eval_rows"])
+
+
+@pytest.mark.parametrize("K,width,d_in,over", [
+    (64, 512, 32_768, {}), (32, 512, 65_536, {}), (30, 128, 262_144, {}), (256, 128, 30_000, {}),
+    (128, 256, 40_000, {}), (2, 16_384, 64, dict(L=2)), (256, 128, 30_000, dict(optimizer="muon")),
+    (64, 512, 2_048, dict(emb_lo=16, emb_hi=16)), (4, 256, 256, dict(L=2)), (6, 130, 37, dict(L=3, B=300)),
+    (40, 512, 512, dict(L=4, B=512))])
+@pytest.mark.parametrize("tiles", [None, "mini", "small", "tall", "big", "huge"])
+@pytest.mark.parametrize("streams", [None, "1", "3"])
+def test_tile_table_holds_every_plan(monkeypatch, K, width, d_in, over, tiles, streams):
+    # a bind fails when the launches' tiles outnumber the table's entries: packs
+    # whose weight gradients have most of them, under every choice of tiles and
+    # streams, with all members, one, or two thirds of them
+    if tiles is not None:
+        monkeypatch.setenv("TABPACK_GEMM_TILES", tiles)
+        monkeypatch.setenv("TABPACK_NS_TILES", tiles)
+    if streams is not None:
+        monkeypatch.setenv("TABPACK_STREAMS", streams)
+    cfg = configs.workload("regression_onehot", K=K, d_in=d_in, **dict(dict(L=1, B=256), **over))
+    mem = members(K, width)
+    for active in (None, [k == 0 for k in range(K)], [k % 3 > 0 or k == K - 1 for k in range(K)]):
+        p = tabpack.debug_plan(cfg, members=mem, active=active)
+        assert 0 < p["tiles"] <= p["tile_capacity"]
