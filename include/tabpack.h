@@ -306,8 +306,9 @@ int pack_get_moments(pack_handle* h, int32_t member, float* m_out, float* v_out)
  * [B, d_k]) of hidden layer `layer` (1-based) of member k at `step` to device
  * memory using the same device function as the training epilogue.
  * pack_debug_activation copies the stored post-dropout activation H_layer of
- * member k ([B, d_k] as fp32) of the last forward pass to a host buffer.
- * layer must lie in [1, L_k]. */
+ * member k ([B, d_k] as fp32) of the last forward pass to a host buffer: rows
+ * past the pass's own (the last chunk of an evaluation may have fewer than B)
+ * and members outside it are zeros.  layer must lie in [1, L_k]. */
 int pack_debug_dropout_mask(pack_handle* h, uint64_t step, int32_t layer, int32_t member,
                             uint8_t* dev_out, hipStream_t stream);
 int pack_debug_activation(pack_handle* h, int32_t layer, int32_t member, float* host_out);

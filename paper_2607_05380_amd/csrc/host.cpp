@@ -179,7 +179,9 @@ struct pack_handle {
   std::vector<Launch> ev[kEvalLevels];
   int eval_shift = 0, eval_levels = 1;
   int64_t eval_cap = 0;  // rows of a chunk that the GEMM loaders reach (kOperandBytes)
-  int last_rows = 0;  // rows of the last forward pass's activation blocks (Bp, or an evaluation chunk's)
+  // the last forward pass: rows of its activation blocks (Bp, or an evaluation
+  // chunk's), and how many of them it computed
+  int last_rows = 0, last_valid = 0;
   // The members are split into ngroups groups of about equal GEMM work; each
   // group's GEMM chain runs on its own stream (group 0 on the caller's), which
   // measured faster than one launch over all members.
@@ -1740,6 +1742,7 @@ int pack_bind(pack_handle* h, void* workspace, size_t bytes, hipStream_t stream)
   }
   h->keep_ready = 0;
   h->last_rows = h->Bp;
+  h->last_valid = h->cfg.B;
   HIP_TRY(hipMemsetAsync(workspace, 0, need, stream));
   HIP_TRY(hipMemcpyAsync(h->b.theta, h->theta_host.data(), h->P * sizeof(float), hipMemcpyHostToDevice, stream));
   std::vector<MemberDev> md(h->cfg.K);
@@ -1790,6 +1793,7 @@ int pack_train_step(pack_handle* h, const float* X, const void* y, int64_t N, co
                              "it with X = NULL)");
   const pack_config& c = h->cfg;
   h->last_rows = h->Bp;
+  h->last_valid = c.B;
   const int nact = (int)h->active_ids.size();
   GemmArgs a = base_args(h);
   a.rows_valid = c.B;
@@ -2079,6 +2083,7 @@ hipError_t eval_forward(pack_handle* h, GemmArgs a, const float* X, int64_t N, i
   const pack_config& c = h->cfg;
   const int R = h->eval_rows(level);
   h->last_rows = R;
+  h->last_valid = a.rows_valid;
   hipError_t e = hipSuccess;
   if (!h->emb)
     e = launch_gather(h->prec, X, N, c.d_in, h->Pin, nullptr, c.B, r0, a.rows_valid, 1, R, h->b.H0, nullptr, stream);
@@ -2332,12 +2337,14 @@ int pack_debug_activation(pack_handle* h, int32_t layer, int32_t member, float* 
     return fail(PACK_EINVAL, "layer %d out of [1, %d] for member %d", layer, h->mem[member].depth, member);
   if (!host_out) return fail(PACK_EINVAL, "host_out is NULL");
   const Member& m = h->mem[member];
-  // blocks of last_rows rows; a chunk of fewer rows than B leaves the others zero
-  const size_t R = (size_t)h->last_rows, n = (size_t)std::min(h->Bp, h->last_rows) * m.dp;
+  // blocks of last_rows rows; those past the rows of the pass (never computed by
+  // a short evaluation chunk) are zeros, as are those of a member outside it
+  const size_t R = (size_t)h->last_rows;
+  const size_t n = h->active[member] ? (size_t)std::min(h->cfg.B, h->last_valid) * m.dp : 0;
   const size_t off = ((size_t)(layer - 1) * (h->A / h->Bp) + (size_t)(m.act_off / h->Bp)) * R;
   std::vector<uint8_t> tmp((size_t)h->Bp * m.dp * h->elt());
   HIP_TRY(hipDeviceSynchronize());
-  HIP_TRY(hipMemcpy(tmp.data(), h->b.H + off * h->elt(), n * h->elt(), hipMemcpyDeviceToHost));
+  if (n) HIP_TRY(hipMemcpy(tmp.data(), h->b.H + off * h->elt(), n * h->elt(), hipMemcpyDeviceToHost));
   for (int r = 0; r < h->cfg.B; ++r)
     for (int c = 0; c < m.width; ++c) {
       const size_t i = (size_t)r * m.dp + c;

@@ -207,3 +207,29 @@ def test_wide_inputs_predict_the_same_in_chunks():
         # 66,000 fp32 products with weights of at most 66,000^-1/2 and normal
         # features: rounding of about 66,000^1/2 2^-24 per activation of size 0.6
         assert np.abs(whole[k, 8_135:] - z).max() < 1e-4
+
+
+@pytest.mark.parametrize("rows", [1, 33, 200])
+def test_debug_activation_past_a_short_input_is_zero(rows):
+    # the rows a short evaluation does not compute hold the step's activations
+    # in the workspace; the hook must not return them
+    cfg = configs.workload("regression_onehot", K=3, B=300, d_in=24, features="normal")
+    mem = [dict(width=w, dropout=0.0, lr=1e-3, wd=1e-3) for w in (40, 129, 70)]
+    Xtr, ytr, Xv, yv, _, idx = make_inputs(cfg, 900, 300)
+    X, y, idx_d, Xv = to_dev(Xtr, ytr, idx, Xv)
+    pk = tabpack.Pack(cfg, members=mem).bind()
+    pk.predict(Xv)
+    full = {(l, k): pk.debug_activation(l, k) for l in (1, 2, 3) for k in range(3)}
+    pk.train_step(X, y, idx_d, 1)
+    fresh = tabpack.Pack(cfg, members=mem).bind()
+    for p in (pk, fresh):
+        p.predict(Xv[:rows].contiguous())
+        for l in (1, 2, 3):
+            for k in range(3):
+                H = p.debug_activation(l, k)
+                assert not H[rows:].any()
+                if p is fresh:
+                    np.testing.assert_array_equal(H[:rows], full[l, k][:rows])
+    pk.set_active([1, 0, 1])
+    pk.predict(Xv)
+    assert not pk.debug_activation(1, 1).any() and pk.debug_activation(1, 2).any()
