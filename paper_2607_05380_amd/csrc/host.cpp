@@ -607,13 +607,17 @@ void sort_launch(Plan& p, const Launch& ln) {
 
 // Whether the given members make a small pack: their activations are at most
 // kOneStreamTiles 128 x 128 tiles a layer (two for each CU).  Its step is one
-// chain of 5 + 2 L launches or less (bound data: 2 + 2 L) instead of up to 30
-// launches and as many event operations in three streams, which took the host
-// about 150 us.  Measured, two groups / one stream: 4 fp32 members of widths
-// 64..256 at batch 256 (16 tiles) 200 / 52 us; 16 bf16 members of 128..512 at
-// batch 512 (~180) 200 / 107 us; 41 of 159..502 at batch 372 (490) 361 / 286
-// us; 32 of 256..1024 at batch 1024 (~1,300) 639 / 641 us, where side by side
-// the groups' weight-update traffic and matrix products overlap.
+// chain of 3 + 2 L launches (2 + 2 L with bound data, 6 + 2 L with embeddings;
+// Muon's products besides) instead of up to 30 launches and as many event
+// operations in three streams, which took the host about 150 us.  Measured, two
+// groups / one stream: 4 fp32 members of widths 64..256 at batch 256 (16 tiles)
+// 200 / 52 us; 16 bf16 members of 128..512 at batch 512 (~180) 200 / 107 us; 41 of
+// 159..502 at batch 372 (490) 361 / 286 us; 32 of 256..1024 at batch 1024 (~1,300)
+// 639 / 641 us, where side by side the groups' weight-update traffic and matrix
+// products overlap.  The size of the first layer does not move the line: 4
+// members of width 256 on 16,000 features 261 / 199 us, 64 of 512 on 4,000 (8,192
+// weight-gradient tiles) 838 / 795; embedded 8 of 512 on 100 features 206 / 163, 16
+// of 512 on 400 at batch 512 656 / 643.  (Muon: muon_split.)
 constexpr int64_t kOneStreamTiles = 512;
 bool small_pack(const pack_handle* h, const std::vector<int>& ids) {
   int64_t n = 0;
@@ -621,15 +625,62 @@ bool small_pack(const pack_handle* h, const std::vector<int>& ids) {
   return n <= kOneStreamTiles;
 }
 
+// Shape of the Newton-Schulz iterate of member m's hidden weight l (1-based):
+// padded [R x Cp] storage; X is [S x L], U or U^T (tall: true rows > true columns).
+struct MuonShape {
+  int R, Cp, S, L, r, c;
+  bool tall;
+};
+MuonShape muon_shape(const pack_handle* h, const Member& m, int l) {
+  MuonShape q;
+  q.R = m.dp;
+  q.Cp = l == 1 ? m.p_in : m.dp;
+  q.r = m.width;
+  q.c = l == 1 ? (m.d_emb ? h->cfg.d_in * m.d_emb : h->cfg.d_in) : m.width;
+  q.tall = q.r > q.c;
+  q.S = q.tall ? q.Cp : q.R;
+  q.L = q.tall ? q.R : q.Cp;
+  return q;
+}
+
+// Whether a small pack's Newton-Schulz products are better split over two
+// streams than one launch each: their X' products (S x L, over all hidden
+// weights) number kMuonSplitTiles small tiles or more, and in bf16 not so many
+// that the split costs the caches more than it overlaps (from kMuonSplitMax on
+// one launch measured up to 30% faster, or the same within 4%, but for 3 members
+// of width 4096).  fp32 products run at 1/16 of the bf16 rate: they split earlier
+// (into mini tiles) and have no such end.  Measured on 64 features at batch 256, one
+// stream / two groups (us): bf16 8 members of width 1024 (576 tiles) 504 / 528; 32
+// of 512 (640) 422 / 399; 3 of 2048 (816) 957 / 1,023; 4 of 2048 (1,088) 1,358 /
+// 1,165; 64 of 512 (1,280) 757 / 651; 2 of 3072 (1,200) 1,937 / 1,663; 2 of 4096
+// (2,112) 3,839 / 3,535; 10 of 2048 (2,720) 2,769 / 2,887; 5 of 3072 (3,000) 4,139 /
+// 4,505; 16 of 2048 (4,352) 4,361 / 4,308; 2 of 4096, L 4 (6,208) 10,961 / 14,297; fp32
+// 2 of 1024 (144) 860 / 878, 4 of 1024 (288) 1,486 / 1,182, 2 of 2048 (544) 5,185 /
+// 3,897, 4 of 2048 (1,088) 8,099 / 6,578, 16 of 2048 (4,352) 24,649 / 24,030.
+constexpr int64_t kMuonSplitTiles = 1024, kMuonSplitTilesF32 = 256, kMuonSplitMax = 2560;
+bool muon_split(const pack_handle* h, const std::vector<int>& ids) {
+  if (!h->muon || ids.size() < 2) return false;
+  int64_t n = 0;
+  for (int k : ids)
+    for (int l = 1; l <= h->mem[k].depth; ++l) {
+      const MuonShape q = muon_shape(h, h->mem[k], l);
+      n += small_tiles(q.S, q.L);
+    }
+  if (h->prec == Prec::FP32) return n >= kMuonSplitTilesF32;
+  return n >= kMuonSplitTiles && n < kMuonSplitMax;
+}
+
 // Members into ngroups groups of about equal GEMM work (longest first, each
 // to the lightest group).  Default: 2 groups, 3 with Muon, whose per-group
 // Newton-Schulz chains overlap better in three (regression_large: 1.398
 // against 1.409 ms per step, Muon 5.33 against 5.39 ms; one group 1.53 ms;
-// 4 groups exceed the four hardware queues).  TABPACK_STREAMS (1 .. 4)
-// overrides it.
+// 4 groups exceed the four hardware queues); small packs one, or two where
+// muon_split says so (three: 64 members of width 512 720 us, two 651).
+// TABPACK_STREAMS (1 .. 4) overrides it.
 void split_members(pack_handle* h) {
-  h->one_stream = small_pack(h, h->active_ids);
-  int ng = h->one_stream ? 1 : h->muon ? 3 : 2;
+  const bool small = small_pack(h, h->active_ids);
+  h->one_stream = small && !muon_split(h, h->active_ids);
+  int ng = h->one_stream ? 1 : h->muon && !small ? 3 : 2;
   if (const char* e = getenv("TABPACK_STREAMS")) ng = std::max(1, std::min(kGroups, atoi(e)));
   h->ngroups = std::max(1, std::min(ng, (int)h->active_ids.size()));
   h->one_stream = h->one_stream && h->ngroups == 1;
@@ -658,24 +709,6 @@ int max_pin(const pack_handle* h, const std::vector<int>& ids) {
 
 // Rows per head-backward block: up to 256, dividing Bp.
 int head_rows(const pack_handle* h) { return h->small ? kHeadRows : h->Bp % 256 == 0 ? 256 : h->Bp; }
-
-// Shape of the Newton-Schulz iterate of member m's hidden weight l (1-based):
-// padded [R x Cp] storage; X is [S x L], U or U^T (tall: true rows > true columns).
-struct MuonShape {
-  int R, Cp, S, L, r, c;
-  bool tall;
-};
-MuonShape muon_shape(const pack_handle* h, const Member& m, int l) {
-  MuonShape q;
-  q.R = m.dp;
-  q.Cp = l == 1 ? m.p_in : m.dp;
-  q.r = m.width;
-  q.c = l == 1 ? (m.d_emb ? h->cfg.d_in * m.d_emb : h->cfg.d_in) : m.width;
-  q.tall = q.r > q.c;
-  q.S = q.tall ? q.Cp : q.R;
-  q.L = q.tall ? q.R : q.Cp;
-  return q;
-}
 
 // Elements of one X buffer and of the A (or B') buffer for the given members.
 template <typename It>

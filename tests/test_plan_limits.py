@@ -43,3 +43,17 @@ def test_tile_table_holds_every_plan(monkeypatch, K, width, d_in, over, tiles, s
     for active in (None, [k == 0 for k in range(K)], [k % 3 > 0 or k == K - 1 for k in range(K)]):
         p = tabpack.debug_plan(cfg, members=mem, active=active)
         assert 0 < p["tiles"] <= p["tile_capacity"]
+
+
+@pytest.mark.parametrize("K,width,B,over,groups,one", [
+    # X' products of 128 x 128 tiles, on 64 features: K ((width / 128)^2 + width / 128)
+    (16, 1024, 256, dict(), 2, False), (14, 1024, 256, dict(), 1, True),       # 1,152 and 1,008 of 1,024
+    (2, 4096, 256, dict(), 2, False), (1, 4096, 256, dict(), 1, True),        # 2,112; one member cannot be split
+    (5, 3072, 256, dict(), 1, True), (4, 3072, 256, dict(), 2, False),        # 3,000 and 2,400 of 2,560
+    (4, 1024, 256, dict(precision="fp32"), 2, False), (3, 1024, 256, dict(precision="fp32"), 1, True),  # 288, 216 of 256
+    (5, 3072, 256, dict(precision="fp32"), 2, False),
+    (16, 1024, 256, dict(optimizer="adamw"), 1, True), (16, 1024, 2048, dict(), 3, False)])
+def test_muon_split_rule(K, width, B, over, groups, one):
+    cfg = configs.workload("regression_onehot", K=K, B=B, L=2, **dict(dict(optimizer="muon"), **over))
+    p = tabpack.debug_plan(cfg, members=members(K, width))
+    assert (p["groups"], p["one_stream"]) == (groups, one)
