@@ -845,10 +845,45 @@ void plan_eval(pack_handle* h) {
     ++h->eval_levels;
 }
 
+// Tile set of the Newton-Schulz products of a step, the symmetric ones (A, B') or
+// X': mini tiles where a launch has fewer than kMiniMaxTiles small ones and, with
+// several groups in bf16, all of the groups' launches together, which run side by
+// side and fill the CUs already, are below kSideSym / kSideX (128 x 128 tiles times
+// depth).  Measured, products of all groups small / sym mini / both mini (us a step,
+// three groups): 16 members of width 512 at batch 2048 (sym 92 thousand, X' 135) 494 /
+// 412 / 406; 32 of 512 (180, 270) 548 / 512 / 538; 6 of 1024 (227, 396) 780 / 706 / 728; 8
+// of 1024 (303, 528) 720 / 707 / 751; 64 of 512 (360, 541) 707 / 737 / 794; 12 of 1024
+// (454, 793) 835 / 881 / 970; 4 of 2048 (1,122, 2,102) 1,347 / 1,715 / 1,919.  fp32 products,
+// at 1/16 of the rate, gain from them at any depth: 3 of 2048 (sym 137, X' 272 tiles a
+// group) 7,805 / 7,559 / 7,705, 4 of 1024 (148, 288 in all) 3,080 / 2,451 / 2,148.
+constexpr int64_t kSideSym = 256 << 10, kSideX = 176 << 10;
+TileSet ns_tiles(const pack_handle* h, const std::vector<int> (&group)[kGroups], bool sym, bool sizing) {
+  if (h->ns_tiles >= 0) return (TileSet)h->ns_tiles;
+  if (sizing) return TILES_SMALL;
+  int64_t most = 0, work = 0;
+  int groups = 0;
+  for (const std::vector<int>& g : group) {
+    int64_t n = 0;
+    for (int k : g)
+      for (int l = 1; l <= h->mem[k].depth; ++l) {
+        const MuonShape q = muon_shape(h, h->mem[k], l);
+        const int64_t r = (q.S + kSmallTile - 1) / kSmallTile;
+        const int64_t t = sym ? r * (r + 1) / 2 : small_tiles(q.S, q.L);
+        n += t;
+        work += t * (sym ? q.L : q.S);
+      }
+    groups += !g.empty();
+    most = std::max(most, n);
+  }
+  if (most >= kMiniMaxTiles) return TILES_SMALL;
+  return groups > 1 && h->prec == Prec::BF16 && work >= (sym ? kSideSym : kSideX) ? TILES_SMALL : TILES_MINI;
+}
+
 void plan_muon(const pack_handle* h, const Bufs& bf, const std::vector<int> (&group)[kGroups], Plan& p,
                bool sizing) {
   const size_t es = h->elt();
   const TileSet saved = p.tile_set;
+  const TileSet sym_set = ns_tiles(h, group, true, sizing), x_set = ns_tiles(h, group, false, sizing);
   int64_t xo = 0, ao = 0;
   struct Item {
     MuonShape q;
@@ -886,17 +921,7 @@ void plan_muon(const pack_handle* h, const Bufs& bf, const std::vector<int> (&gr
         ao += round_up((int64_t)q.S * q.S, kChunk);
       }
     }
-    // the launches' small tiles: symmetric products (A, B') and X'
-    int64_t n_sym = 0, n_x = 0;
-    for (const Item& it : items) {
-      const int64_t n = (it.q.S + kSmallTile - 1) / kSmallTile;
-      n_sym += n * (n + 1) / 2;
-      n_x += small_tiles(it.q.S, it.q.L);
-    }
-    auto ns_set = [&](int64_t n_small) {
-      return h->ns_tiles >= 0 ? (TileSet)h->ns_tiles : n_small < kMiniMaxTiles && !sizing ? TILES_MINI : TILES_SMALL;
-    };
-    p.tile_set = ns_set(n_sym);
+    p.tile_set = sym_set;
     // A = X X^T, one launch per parity of the X buffer it reads
     for (int par = 0; par < 2; ++par) {
       Launch& ln = p.nsA[par][hf];
@@ -941,7 +966,7 @@ void plan_muon(const pack_handle* h, const Bufs& bf, const std::vector<int> (&gr
       }
       sort_launch(p, ln);
     }
-    p.tile_set = ns_set(n_x);
+    p.tile_set = x_set;
     // X' = a X + B' X, reading X from buffer par and writing buffer 1 - par
     for (int par = 0; par < 2; ++par) {
       Launch& ln = p.nsX[par][hf];
@@ -1697,6 +1722,10 @@ int pack_debug_plan(const pack_config* cfg, const uint8_t* active, pack_plan_inf
   out->tile_capacity = (int64_t)h->b.tile_cap;
   out->groups = h->ngroups;
   out->one_stream = h->one_stream ? 1 : 0;
+  if (h->muon) {
+    out->ns_sym = plan.nsB[0].ts;
+    out->ns_x = plan.nsX[0][0].ts;
+  }
   out->eval_levels = h->eval_levels;
   for (int lv = 0; lv < h->eval_levels; ++lv) {
     out->eval_rows[lv] = h->eval_rows(lv);

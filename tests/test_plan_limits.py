@@ -57,3 +57,21 @@ def test_muon_split_rule(K, width, B, over, groups, one):
     cfg = configs.workload("regression_onehot", K=K, B=B, L=2, **dict(dict(optimizer="muon"), **over))
     p = tabpack.debug_plan(cfg, members=members(K, width))
     assert (p["groups"], p["one_stream"]) == (groups, one)
+
+
+SMALL, MINI = 1, 4  # tile sets
+
+
+@pytest.mark.parametrize("K,width,B,over,sym,x", [
+    # one stream: fewer than 256 tiles a launch -- K ((width / 128)^2 / 2 + ...) and X'
+    (3, 1024, 256, dict(), MINI, MINI), (4, 1024, 256, dict(), MINI, SMALL), (8, 1024, 256, dict(), SMALL, SMALL),
+    # three groups in bf16: tiles times depth of all groups' launches below 256 Ki (sym), 176 Ki (X')
+    (16, 512, 2048, dict(), MINI, MINI), (32, 512, 1024, dict(), MINI, SMALL), (6, 1024, 4096, dict(), MINI, SMALL),
+    (8, 1024, 2048, dict(), SMALL, SMALL), (4, 2048, 2048, dict(), SMALL, SMALL),
+    # fp32: fewer than 256 tiles in the group with most
+    (8, 1024, 2048, dict(precision="fp32"), MINI, MINI), (3, 2048, 4096, dict(precision="fp32"), MINI, SMALL),
+    (4, 2048, 2048, dict(precision="fp32"), SMALL, SMALL)])
+def test_newton_schulz_tile_rule(K, width, B, over, sym, x):
+    cfg = configs.workload("regression_onehot", K=K, B=B, L=2, optimizer="muon", **over)
+    p = tabpack.debug_plan(cfg, members=members(K, width))
+    assert (p["ns_sym"], p["ns_x"]) == (sym, x)
