@@ -802,6 +802,9 @@ constexpr int kMiniMaxTiles = 256;
 // 511; tall / huge: evaluation of 64 members (5,400) 22.3 / 21.4 ms.  Data
 // gradients, steps with tall / huge ones: widths 64..2048 at batch 2048 (4,350)
 // 6.26 / 6.13 ms, 256..1024 at batch 1024 (1,350) 1.265 / 1.284 ms.
+// Evaluation chunks of fewer rows than one huge tile keep the smaller tiles
+// (huge / tall, us): 37 rows by 64 members of width 2048 (chunks of 64 rows, 1,024
+// tiles) 189 / 176, 100 rows (of 128) 242 / 222, by 200 of width 512 165 / 149.
 constexpr int kHugeMinFwd = 640, kHugeMinDx = 2048;
 TileSet launch_tiles(const pack_handle* h, int forced, int64_t n_small, int huge_min = 0, int min_depth = 0) {
   if (forced >= 0) return (TileSet)forced;
@@ -1097,7 +1100,8 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
       for (int hf = 0; hf < kGroups; ++hf)
         for (int k : group[hf])
           if (h->mem[k].depth >= l) nsm += small_tiles(R, h->mem[k].dp);
-      p.tile_set = l == 1 && h->emb ? (sizing ? TILES_SMALL : h->emb_tiles) : choose(h->tiles_fwd, nsm, kHugeMinFwd);
+      p.tile_set = l == 1 && h->emb ? (sizing ? TILES_SMALL : h->emb_tiles)
+                                    : choose(h->tiles_fwd, nsm, R >= kBigTile ? kHugeMinFwd : 0);
       for (int hf = 0; hf < kGroups; ++hf)
         for (int k : group[hf]) {
           const Member& m = h->mem[k];

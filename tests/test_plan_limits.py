@@ -75,3 +75,11 @@ def test_newton_schulz_tile_rule(K, width, B, over, sym, x):
     cfg = configs.workload("regression_onehot", K=K, B=B, L=2, optimizer="muon", **over)
     p = tabpack.debug_plan(cfg, members=members(K, width))
     assert (p["ns_sym"], p["ns_x"]) == (sym, x)
+
+
+@pytest.mark.parametrize("K,width,B", [(64, 2048, 256), (64, 2048, 2048), (200, 512, 256), (96, 1024, 1024)])
+def test_huge_tiles_only_for_chunks_of_their_height(K, width, B):
+    p = tabpack.debug_plan(configs.workload("regression_onehot", K=K, B=B, L=2), members=members(K, width))
+    huge = 5
+    assert [t == huge for t in p["eval_tiles"]] == [r >= 256 for r in p["eval_rows"]]
+    assert p["eval_rows"][0] >= 256 > p["eval_rows"][-1]
