@@ -462,9 +462,10 @@ int64_t member_span_end(const pack_handle* h, int k) {
 // Device-table sizes.
 struct Plan {
   TileSet tile_set = TILES_SMALL;
+  bool unsorted = false;  // only the tables' sizes are wanted: sort_launch leaves the tiles as they are
   std::vector<GemmDesc> descs;
   std::vector<Tile> tiles;
-  std::vector<int64_t> cost;  // planner's cost of each tile (depth x valid area)
+  std::vector<int64_t> cost;  // planner's cost of each tile (depth x valid area), as added (before sort_launch)
   std::vector<ColTile> coltiles;
   std::vector<HeadTile> headtiles;
   std::vector<Launch> fwd[2][kGroups], dx[kGroups], dw[kGroups];
@@ -563,35 +564,39 @@ void add_tiles(Plan& p, Launch& ln, int d, int M, int N, int kdepth) {
 // packed into the 8 XCD bins longest-first by total cost), and within a bin
 // tiles run longest-first so the launch ends on short tiles.
 void sort_launch(Plan& p, const Launch& ln) {
-  struct Item {
-    Tile t;
-    int64_t cost;
-  };
-  std::vector<Item> items;
-  for (int i = 0; i < ln.ntiles; ++i) items.push_back(Item{p.tiles[ln.tile0 + i], p.cost[ln.tile0 + i]});
-  std::vector<std::pair<int64_t, int>> member_cost;  // (cost, desc)
-  for (const Item& it : items) {
-    auto f = std::find_if(member_cost.begin(), member_cost.end(),
-                          [&](const std::pair<int64_t, int>& e) { return e.second == it.t.desc; });
-    if (f == member_cost.end())
-      member_cost.push_back({it.cost, it.t.desc});
-    else
-      f->first += it.cost;
+  if (p.unsorted || ln.ntiles == 0) return;
+  const Tile* tiles = p.tiles.data() + ln.tile0;
+  const int64_t* cost = p.cost.data() + ln.tile0;
+  int lo = tiles[0].desc, hi = lo;
+  for (int i = 1; i < ln.ntiles; ++i) {
+    lo = std::min(lo, tiles[i].desc);
+    hi = std::max(hi, tiles[i].desc);
+  }
+  std::vector<int> bin_of(hi - lo + 1, -1);              // the descriptor's entry of member_cost, then its XCD
+  std::vector<std::pair<int64_t, int>> member_cost;  // (cost, desc - lo)
+  for (int i = 0; i < ln.ntiles; ++i) {
+    int& e = bin_of[tiles[i].desc - lo];
+    if (e < 0) {
+      e = (int)member_cost.size();
+      member_cost.push_back({0, tiles[i].desc - lo});
+    }
+    member_cost[e].first += cost[i];
   }
   std::stable_sort(member_cost.begin(), member_cost.end(),
                    [](const std::pair<int64_t, int>& a, const std::pair<int64_t, int>& b) { return a.first > b.first; });
   std::vector<int64_t> load(kXcds, 0);
-  std::vector<int> bin_of(p.descs.size() + 1, 0);
   for (const auto& mc : member_cost) {
     const int b = (int)(std::min_element(load.begin(), load.end()) - load.begin());
     load[b] += mc.first;
     bin_of[mc.second] = b;
   }
-  std::vector<std::vector<Item>> bins(kXcds);
-  for (const Item& it : items) bins[bin_of[it.t.desc]].push_back(it);
+  std::vector<std::pair<int64_t, int>> bins[kXcds];  // (cost, tile)
+  for (int i = 0; i < ln.ntiles; ++i) bins[bin_of[tiles[i].desc - lo]].push_back({cost[i], i});
+  auto longer = [](const std::pair<int64_t, int>& a, const std::pair<int64_t, int>& b) { return a.first > b.first; };
   for (auto& b : bins)
-    std::stable_sort(b.begin(), b.end(), [](const Item& x, const Item& y) { return x.cost > y.cost; });
-  std::vector<size_t> next(kXcds, 0);
+    if (!std::is_sorted(b.begin(), b.end(), longer)) std::stable_sort(b.begin(), b.end(), longer);
+  std::vector<Tile> out(ln.ntiles);
+  size_t next[kXcds] = {};
   for (int i = 0; i < ln.ntiles; ++i) {
     int b = i % kXcds;
     if (next[b] == bins[b].size()) {  // this XCD's bin is empty: take from the fullest remaining
@@ -599,10 +604,9 @@ void sort_launch(Plan& p, const Launch& ln) {
       for (int c = 0; c < kXcds; ++c)
         if (bins[c].size() - next[c] > best) best = bins[c].size() - next[c], b = c;
     }
-    p.tiles[ln.tile0 + i] = bins[b][next[b]].t;
-    p.cost[ln.tile0 + i] = bins[b][next[b]].cost;
-    ++next[b];
+    out[i] = tiles[bins[b][next[b]++].second];
   }
+  std::copy(out.begin(), out.end(), p.tiles.begin() + ln.tile0);
 }
 
 // Whether the given members make a small pack: their activations are at most
@@ -1013,6 +1017,7 @@ void plan_muon(const pack_handle* h, const Bufs& bf, const std::vector<int> (&gr
 Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&group)[kGroups],
                 bool sizing = false) {
   Plan p;
+  p.unsorted = sizing;
   // sizing: small tiles for the main GEMMs (the largest tile count of any choice)
   auto choose = [&](int forced, int64_t n_small, int huge_min, int min_depth = 0) {
     return sizing ? TILES_SMALL : launch_tiles(h, forced, n_small, huge_min, min_depth);
