@@ -137,7 +137,10 @@ const char* pack_last_error(void);
  * plan the packed layout and generate the initial parameters on the host
  * (torch.nn.Linear's default U(-1/sqrt(fan_in), 1/sqrt(fan_in)) for weights
  * and biases, fan_in = the member's true input width; padding exactly zero).
- * On success *out owns the handle; release it with pack_destroy(). */
+ * On success *out owns the handle; release it with pack_destroy().
+ * A GEMM reads operands of at most 2 GiB: a member whose weight matrix or
+ * whose activations of one batch are larger is refused, as is a training step
+ * whose gathered batch of one member (B x d_in; not with pack_bind_data()) is. */
 int pack_init(const pack_config* cfg, pack_handle** out);
 
 /* Release the handle and its host memory.  The bound workspace stays the
@@ -148,7 +151,11 @@ int pack_destroy(pack_handle* h);
 int pack_get_hparams(const pack_handle* h, pack_member_hp* out);
 
 /* Device workspace (bytes) that pack_bind() needs: parameters, gradients,
- * AdamW moments, bf16 weight shadow, activations and launch tables. */
+ * AdamW moments, bf16 weight shadow, activations and launch tables.  The
+ * activations are sized for evaluation chunks of up to 8,192 rows (8,192 tiles
+ * of 128 x 128 a layer, 256 MiB of gathered input): at most 0.25 GiB a layer in
+ * bf16 (0.5 in fp32) more than training alone needs, most of a small pack's
+ * workspace. */
 int pack_workspace_size(const pack_handle* h, size_t* bytes);
 
 /* Bind a caller-owned device workspace of at least pack_workspace_size()

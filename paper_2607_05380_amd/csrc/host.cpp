@@ -1687,6 +1687,19 @@ int make_pack(const pack_config* cfg, pack_handle** out) {
     m.scale = 1.0 / (1.0 - m.dropout);
   }
   plan_layout(h);
+  // Operands the GEMM loaders cannot reach whole would lose their last rows.
+  for (int k = 0; k < cfg->K; ++k) {
+    const Member& m = h->mem[k];
+    const int64_t e = (int64_t)h->elt(), cols = m.depth > 1 ? std::max(m.p_in, m.dp) : m.p_in;
+    const int64_t weight = m.width * cols * e, act = (int64_t)cfg->B * m.dp * e;
+    if (weight > kOperandBytes || act > kOperandBytes) {
+      const int64_t width = m.width;
+      delete h;
+      return fail(PACK_EINVAL, "member %d (width %lld): %s of %lld bytes; a GEMM operand is limited to 2 GiB", k,
+                  (long long)width, weight > kOperandBytes ? "a weight matrix" : "activations",
+                  (long long)std::max(weight, act));
+    }
+  }
   plan_eval(h);
   h->active.assign(cfg->K, 1);
   set_active_ids(h);
@@ -1863,6 +1876,9 @@ int pack_train_step(pack_handle* h, const float* X, const void* y, int64_t N, co
     return fail(PACK_EINVAL, "X / N differ from the data bound with pack_bind_data (bind it again, or unbind "
                              "it with X = NULL)");
   const pack_config& c = h->cfg;
+  if (!h->stream_rows && !h->emb && (int64_t)c.B * h->Pin * (int64_t)h->elt() > kOperandBytes)
+    return fail(PACK_EINVAL, "a gathered batch of %d rows of %d features passes the GEMMs' operand limit of 2 GiB", c.B,
+                c.d_in);
   h->last_rows = h->Bp;
   h->last_valid = c.B;
   const int nact = (int)h->active_ids.size();

@@ -1,5 +1,5 @@
 """Small packs: the 64 x 64 GEMM tiles give the results of the 128 x 128 ones, the one-stream step those of the step on
-several streams, and the fused training head those of the oracle."""
+several streams, and the fused training head those of the oracle; evaluation in chunks, and inputs too wide for them."""
 import numpy as np
 import pytest
 
@@ -137,7 +137,8 @@ def test_few_members_left_of_a_large_pack(monkeypatch):
     ("regression_onehot", dict(B=300)),
     ("multiclass_lognormal", dict(B=700, d_in=24, L=2)),
     ("binary_small", dict(B=64, L=3)),
-    ("binary_small", dict(emb_lo=8, emb_hi=16, emb_step=4))])
+    ("binary_small", dict(emb_lo=8, emb_hi=16, emb_step=4)),
+    ("regression_onehot", dict(B=300, d_in=20, features="normal", emb_lo=8, emb_hi=16, emb_step=4))])
 def test_chunk_rows_do_not_change_predictions(name, over):
     # an activation row depends on its data row alone, reduced in one order by
     # every tile, so the rows of a short input have the bits they have in a long
@@ -233,3 +234,20 @@ def test_debug_activation_past_a_short_input_is_zero(rows):
     pk.set_active([1, 0, 1])
     pk.predict(Xv)
     assert not pk.debug_activation(1, 1).any() and pk.debug_activation(1, 2).any()
+
+
+def test_batch_wider_than_an_operand():
+    # a gathered batch of 600 x 2^20 fp32 features passes 2 GiB: the step is
+    # refused, and evaluation takes the 511 rows of a chunk below the limit
+    import torch
+    cfg = configs.workload("regression_onehot", K=1, B=600, L=1, d_in=1 << 20, precision="fp32")
+    pk = tabpack.Pack(cfg, members=[dict(width=9, dropout=0.0, lr=1e-3, wd=1e-3)]).bind()
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X = torch.randn(600, 1 << 20, device="cuda", generator=g)
+    y, idx = torch.zeros(600, device="cuda"), torch.zeros(1, 600, dtype=torch.int32, device="cuda")
+    with pytest.raises(tabpack.PackError, match="operand limit"):
+        pk.train_step(X, y, idx, 1)
+    whole = pk.predict(X).cpu().numpy()
+    for r0, r1 in ((0, 30), (500, 530), (570, 600)):
+        np.testing.assert_array_equal(pk.predict(X[r0:r1].contiguous()).cpu().numpy(), whole[:, r0:r1])
+    assert np.isfinite(whole).all() and np.unique(whole).size > 590

@@ -180,7 +180,8 @@ def test_embedding_hparams_and_init_match_oracle():
 def test_workspace_independent_of_tile_sets(monkeypatch):
     # The GEMM tile sets are chosen per launch (or forced by the environment);
     # the device tile table is sized for the largest choice (small tiles), so
-    # the workspace is the same under every setting.  multiclass_lognormal's
+    # the workspace is the same under every setting but forced mini tiles, which
+    # are four times as many.  multiclass_lognormal's
     # evaluation launch of all 32 members has 1,280 small tiles: tall by default.
     sizes = {}
     for v in (None, "small", "tall", "big"):

@@ -13,7 +13,7 @@ def members(K, w, **hp):
 
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
 @pytest.mark.parametrize("d_in", [8, 4_000, 65_536, 65_537, 66_000, 131_072, 131_080, 262_144, 1 << 20])
-@pytest.mark.parametrize("K,width,B", [(1, 32, 1), (4, 128, 256), (1, 128, 2048), (40, 512, 700), (1, 128, 65_536)])
+@pytest.mark.parametrize("K,width,B", [(1, 32, 1), (4, 128, 256), (1, 128, 2048), (40, 480, 700), (1, 128, 65_536)])
 def test_evaluation_operands_below_the_loaders_limit(K, width, B, d_in, precision):
     # rows past the limit read as zeros or as other rows: wrong predictions
     cfg = configs.workload("regression_onehot", K=K, B=B, L=1, d_in=d_in, precision=precision)
@@ -83,3 +83,19 @@ def test_huge_tiles_only_for_chunks_of_their_height(K, width, B):
     huge = 5
     assert [t == huge for t in p["eval_tiles"]] == [r >= 256 for r in p["eval_rows"]]
     assert p["eval_rows"][0] >= 256 > p["eval_rows"][-1]
+
+
+@pytest.mark.parametrize("K,width,B,d_in,over,refused", [
+    (1, 511, 256, 1 << 20, dict(precision="fp32"), False), (1, 512, 256, 1 << 20, dict(precision="fp32"), True),
+    (2, 1023, 256, 1 << 20, dict(), False), (2, 1024, 256, 1 << 20, dict(), True),
+    (1, 1000, 256, 65_536, dict(emb_lo=16, emb_hi=16), False), (1, 1025, 256, 65_536, dict(emb_lo=16, emb_hi=16), True),
+    (1, 8_192, 65_535, 8, dict(precision="fp32"), False), (1, 8_192, 65_536, 8, dict(precision="fp32"), True),
+    (1, 16_384, 65_536, 8, dict(), True)])
+def test_operands_past_the_limit_are_refused(K, width, B, d_in, over, refused):
+    # weights [width, d_in] or activations [B, width] of 2 GiB: their last rows would read as zeros
+    cfg = configs.workload("regression_onehot", K=K, B=B, L=1, d_in=d_in, **over)
+    if refused:
+        with pytest.raises(tabpack.PackError, match="limited to 2 GiB"):
+            tabpack.debug_plan(cfg, members=members(K, width))
+    else:
+        assert tabpack.debug_plan(cfg, members=members(K, width))["tiles"] > 0
