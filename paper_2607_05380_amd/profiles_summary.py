@@ -33,11 +33,10 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 COPY_BYTES = 256 << 20
 OPS = ["kmaj", "rmaj", "emb"]
 EPIS = ["fwd", "fwd_eval", "dx", "dw", "ns", "de"]
-SIMPLE = ["dropout_words", "grad_sums", "head_grad_reduce", "head_fwd", "head_bwd", "head_train", "loss_reduce",
-          "bias_from_partials", "gather", "adamw", "to_shadow", "eval_score", "dropout_mask", "select_partial",
-          "select_pick",
-          "select_update", "select_init", "select_final", "ensemble_mean", "muon_prep", "muon_norm",
-          "muon_convert", "muon_update", "embed_table", "embed_grad", "idx_check", "stream_copy"]
+SIMPLE = ["dropout_words", "grad_sums", "head_fwd", "head_bwd", "head_train", "gather", "rows_to_bf16", "to_shadow",
+          "eval_score", "dropout_mask", "select_partial", "select_pick", "select_update", "select_init", "select_final",
+          "ensemble_mean", "muon_prep", "muon_norm", "muon_convert", "muon_update", "embed_table", "embed_grad",
+          "idx_check", "stream_copy"]
 
 
 def source_digest():
@@ -63,12 +62,12 @@ def short_name(kernel):
         epi = int(m.group(1) or m.group(2))
         return f"gemm_bf16_{OPS[2]}_{OPS[0]}_{EPIS[epi]}" if epi < len(EPIS) else None
     if "gemm_kernel" in kernel:
-        m = re.search(r"gemm_kernel(?:_small|_tall)?I(DF16b|f)?(?:Li(\d)E)(?:Li(\d)E)(?:Li(\d)E)", kernel)
+        m = re.search(r"gemm_kernel(?:_small|_tall|_mini|_huge)?I(DF16b|f)?(?:Li(\d)E)(?:Li(\d)E)(?:Li(\d)E)", kernel)
         if m:
             t = "f32" if m.group(1) == "f" else "bf16"
             ak, bk, epi = int(m.group(2)), int(m.group(3)), int(m.group(4))
         else:
-            m = re.search(r"gemm_kernel(?:_small|_tall)?<(?:([^,<>]*), )?(\d), (\d), (\d)>", kernel)
+            m = re.search(r"gemm_kernel(?:_small|_tall|_mini|_huge)?<(?:([^,<>]*), )?(\d), (\d), (\d)>", kernel)
             if m:
                 t = "f32" if m.group(1) and "float" in m.group(1) else "bf16"
                 ak, bk, epi = int(m.group(2)), int(m.group(3)), int(m.group(4))
@@ -76,7 +75,7 @@ def short_name(kernel):
                 # demangled with the leading arguments lost: the operand kind of A
                 # follows from the epilogue (the forward, data-gradient and Newton-
                 # Schulz GEMMs read A depth-contiguous, the weight gradient row-major)
-                m = re.search(r"gemm_kernel(?:_small|_tall)?<.*, (\d), (\d)>", kernel)
+                m = re.search(r"gemm_kernel(?:_small|_tall|_mini|_huge)?<.*, (\d), (\d)>", kernel)
                 if not m:
                     return None
                 t, bk, epi = "bf16", int(m.group(1)), int(m.group(2))

@@ -20,6 +20,12 @@ from paper_2607_05380_amd import profiles_summary as ps
     ("_ZN7tabpack12_GLOBAL__N_111gemm_kernelIDF16bLi0ELi0ELi1EEEvNS_8GemmArgsE", "gemm_bf16_kmaj_kmaj_fwd_eval"),
     ("_ZN7tabpack12_GLOBAL__N_120gemm_kernel_emb_wideILi0EEEvNS_8GemmArgsE", "gemm_bf16_emb_kmaj_fwd"),
     ("void tabpack::(anonymous namespace)::gemm_kernel_emb_wide<1>(tabpack::GemmArgs)", "gemm_bf16_emb_kmaj_fwd_eval"),
+    ("_ZN7tabpack12_GLOBAL__N_116gemm_kernel_hugeILi0ELi1ELi2EEEvNS_8GemmArgsE", "gemm_bf16_kmaj_rmaj_dx"),
+    ("void tabpack::(anonymous namespace)::gemm_kernel_huge<0, 0, 1>(tabpack::GemmArgs)", "gemm_bf16_kmaj_kmaj_fwd_eval"),
+    ("_ZN7tabpack12_GLOBAL__N_116gemm_kernel_miniIDF16bLi1ELi1ELi3EEEvNS_8GemmArgsE", "gemm_bf16_rmaj_rmaj_dw"),
+    ("_ZN7tabpack12_GLOBAL__N_116gemm_kernel_miniIfLi0ELi0ELi4EEEvNS_8GemmArgsE", "gemm_f32_kmaj_kmaj_ns"),
+    ("void tabpack::(anonymous namespace)::gemm_kernel_mini<float, 0, 1, 2>(tabpack::GemmArgs)", "gemm_f32_kmaj_rmaj_dx"),
+    ("void tabpack::(anonymous namespace)::head_train_kernel<__bf16, 1>(...)", "head_train"),
     ("void tabpack::(anonymous namespace)::muon_update_kernel<__bf16>(...)", "muon_update"),
     ("void tabpack::(anonymous namespace)::select_partial_kernel(...)", "select_partial"),
     ("void at::native::elementwise_kernel<128, 4>(...)", None),
