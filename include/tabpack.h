@@ -170,7 +170,7 @@ int pack_bind(pack_handle* h, void* workspace, size_t bytes, hipStream_t stream)
  *   active  host uint8 [K], 1 = member k is trained and evaluated, 0 = removed
  * A removed member's parameters and AdamW moments are frozen as they are (its
  * getters keep working, its rows of loss_out / pred_out / score_out are no
- * longer written) and its GEMM tiles, head work and optimizer chunks leave the
+ * longer written) and its GEMM tiles, head work and optimizer updates leave the
  * launches.  A member may be re-activated.  All members start active.  With a
  * bound workspace the call re-plans the launches and uploads the tables on
  * `stream` and synchronizes it.  Any subset is valid, including the empty one;

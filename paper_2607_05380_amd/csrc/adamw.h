@@ -1,5 +1,6 @@
-// adamw.h -- the per-parameter AdamW update shared by the optimizer kernel and
-// the fused weight-gradient epilogue (torch.optim.AdamW semantics: decoupled
+// adamw.h -- the per-parameter AdamW update shared by the weight-gradient
+// GEMMs' epilogues, the gradient sums (biases and head) and the embedding
+// gradients (torch.optim.AdamW semantics: decoupled
 // decay applied to the parameter first, then the bias-corrected Adam step with
 // eps added after the square root of the corrected second moment).
 #pragma once
@@ -9,8 +10,8 @@
 namespace tabpack {
 
 // Contraction into fused multiply-adds is off: the optimizer runs inside
-// several kernels (the weight-gradient GEMM's epilogues of each tile shape and
-// the standalone kernel), and every one of them must round each operation the
+// several kernels (the weight-gradient GEMM's epilogues of each tile shape,
+// grad_sums and embed_grad), and every one of them must round each operation the
 // same way for results not to depend on the tile shape.
 __device__ __forceinline__ void adamw_elem(float& th, float g, float& m, float& v, float decay, float step,
                                            const AdamConst& c) {

@@ -186,9 +186,9 @@ struct pack_handle {
   // group's GEMM chain runs on its own stream (group 0 on the caller's), which
   // measured faster than one launch over all members.
   int ngroups = 1;
-  // Small packs (small_pack) run the whole step on the caller's stream, with
-  // if it can with one weight-gradient launch for all layers: such a step is
-  // bound by its launches and events, not by what runs side by side.
+  // Small packs (small_pack, but not muon_split) run the whole step on the
+  // caller's stream, with one weight-gradient launch for all layers: such a step
+  // is bound by its launches and events, not by what runs side by side.
   bool one_stream = false;
   Launch dw_all{};                   // one_stream and small: the weight gradients of all layers (embedded packs: 2..L)
   // a small pack with all its members active: the training head in one kernel,
@@ -209,7 +209,6 @@ struct pack_handle {
   int nheadtiles = 0;
   int head_rb = 0;  // rows per head-backward block
   uint64_t t = 0;
-  TileSet tiles = TILES_SMALL;  // tile set of the bf16 GEMMs (fp32 GEMMs run small tiles only)
   // tile sets of the forward, data- and weight-gradient GEMMs: -1 chooses per
   // launch (launch_tiles), else a fixed TileSet
   int tiles_fwd = -1, tiles_dx = -1, tiles_dw = -1;
@@ -1022,7 +1021,6 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
   auto choose = [&](int forced, int64_t n_small, int huge_min, int min_depth = 0) {
     return sizing ? TILES_SMALL : launch_tiles(h, forced, n_small, huge_min, min_depth);
   };
-  p.tile_set = h->tiles;
   const pack_config& c = h->cfg;
   const size_t es = h->elt();
   const void* wsrc = h->prec == Prec::BF16 ? (const void*)bf.shadow : (const void*)bf.theta;
@@ -1402,7 +1400,7 @@ GemmArgs base_args(const pack_handle* h) {
   a.descs = h->b.d_descs;
   a.tiles = h->b.d_tiles;
   a.zeros = h->b.zeros;
-  a.tile_set = h->tiles;
+  a.tile_set = TILES_SMALL;
   const Key kd = stream_key(h->cfg.seed, kTagDropout);
   a.key0 = kd.k0;
   a.key1 = kd.k1;
@@ -1624,14 +1622,9 @@ int make_pack(const pack_config* cfg, pack_handle** out) {
   h->task = (Task)cfg->task;
   h->q = cfg->quantum ? cfg->quantum : 32;
   // The tile sets of the main GEMMs are chosen per launch (launch_tiles);
-  // TABPACK_GEMM_TILES=big|tall|small fixes them all, TABPACK_TILES_FWD / _DX /
-  // _DW one kind.  h->tiles: the set of the remaining bf16 GEMM launches.
-  h->tiles = TILES_SMALL;
-  if (const char* e = getenv("TABPACK_GEMM_TILES")) {
-    const std::string v(e);
-    h->tiles = v == "big" ? TILES_BIG : (v == "tall" ? TILES_TALL : TILES_SMALL);
-  }
-  if (h->prec == Prec::FP32) h->tiles = TILES_SMALL;
+  // TABPACK_GEMM_TILES=big|tall|small|mini|huge fixes them all (huge: forward and
+  // data gradient, the weight gradient small; fp32: small or mini),
+  // TABPACK_TILES_FWD / _DX / _DW one kind.
   auto tile_env = [&](const char* name, bool main = true, bool huge = false) {
     const char* e = getenv(name);
     if (!e && main) e = getenv("TABPACK_GEMM_TILES");

@@ -1,6 +1,6 @@
 // Non-GEMM kernels of the packed MLP step on gfx950: the linear head with the
-// loss and its gradient, column sweeps for bias gradients, the packed AdamW
-// update, validation scoring and greedy ensemble selection.
+// loss and its gradient, the sums of the bias and head gradients with their
+// AdamW update, validation scoring and greedy ensemble selection.
 //
 // Reductions use wave64 shuffles and fixed-order LDS trees so that every
 // result is bit-reproducible run to run (no float atomics anywhere).

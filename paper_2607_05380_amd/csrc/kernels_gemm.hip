@@ -9,7 +9,8 @@
 // Workgroup: 256 threads = 4 wave64s in a 2 x 2 grid.  Tile shapes (uniform
 // per workgroup; one launch runs one tile set, chosen by the host):
 //   small 128 x 128: each wave owns 64 x 64 = 2 x 2 MFMA 32x32 blocks; 64 KB
-//         of LDS, two workgroups per CU.  The default for every GEMM.
+//         of LDS, two workgroups per CU.  For every GEMM that none of the
+//         others measured faster for (launch_tiles).
 //   tall  256 x 128 (waves 128 x 64), two workgroups per CU, with small tiles
 //         on a member's row edge.
 //   big   256 x 256 (waves 128 x 128), one workgroup per CU, with small tiles
@@ -987,10 +988,9 @@ struct Quad<float> {
 
 // The Newton-Schulz epilogues work on 32-row blocks of staged fp32
 // accumulators, lane vector `it` holding 4 consecutive columns of a row.
-// The matrix Y that is added is read ahead as 4-element vectors (its latency,
-// about 2,000 cycles a read, was paid once per vector before; the 64-member
-// Muon step went from 4.94 to 4.64 ms with the weights of the update read ahead
-// too).
+// The matrix Y that is added is read ahead as 4-element vectors (its latency
+// was paid once per vector before; the 64-member Muon step went from 4.94 to
+// 4.64 ms with the weights of the update read ahead too).
 template <typename OT, int NB>
 struct NsRows {
   static constexpr int PER = Stage<float, NB>::PER_LANE;
@@ -1957,12 +1957,13 @@ __device__ __forceinline__ void run_tile_emb(const GemmArgs& a, const GemmDesc& 
 // bytes per product of the 128 x 128 tiles help by as much: 22.3 -> 21.4 ms for
 // 64 members of widths 256..1024 on 70,000 rows.
 // There is no second workgroup to cover this one's waits, so they are covered
-// inside it: at the top of step kt the loads of step kt + 1 have landed (two
-// steps are in flight, a fourth is issued), and a wave reads the fragments of its
+// inside it: at the top of step kt the loads of step kt + 1 have landed (those of
+// two more are in flight and a third's are issued), and a wave reads the fragments of its
 // next 16-deep half step, across the step's barrier, while the MFMAs of the
 // present one run.  The loads are issued one by one between the MFMAs: in one
 // burst after the barrier they fill the address unit's queue and every wave
-// waits in issue (4,330 -> 4,020 cycles per 64-deep step; 2,048 are MFMA).
+// waits in issue (with four stages, that evaluation pass 21.65 -> 21.46 ms, a step
+// of 64 members of widths 64..2048 at batch 2048 6.08 -> 5.97 ms).
 constexpr int kHugeKs = 2, kHugeNs = 5;
 constexpr int kLdsHuge = kHugeNs * 512 * 32 * kHugeKs;
 template <int AK, int BK_, int EPI, int SH>

@@ -112,7 +112,7 @@ struct Tile {
   int32_t desc;
   int32_t m0;
   int32_t n0;
-  int32_t shape;       // kShapeBig or kShapeSmall
+  int32_t shape;       // kShape*, one that the launch's tile set holds
 };
 
 struct AdamConst {
