@@ -646,31 +646,44 @@ MuonShape muon_shape(const pack_handle* h, const Member& m, int l) {
   return q;
 }
 
-// Whether a small pack's Newton-Schulz products are better split over two
-// streams than one launch each: their X' products (S x L, over all hidden
-// weights) number kMuonSplitTiles small tiles or more, and in bf16 not so many
-// that the split costs the caches more than it overlaps (from kMuonSplitMax on
-// one launch measured up to 30% faster, or the same within 4%, but for 3 members
-// of width 4096).  fp32 products run at 1/16 of the bf16 rate: they split earlier
-// (into mini tiles) and have no such end.  Measured on 64 features at batch 256, one
-// stream / two groups (us): bf16 8 members of width 1024 (576 tiles) 504 / 528; 32
-// of 512 (640) 422 / 399; 3 of 2048 (816) 957 / 1,023; 4 of 2048 (1,088) 1,358 /
-// 1,165; 64 of 512 (1,280) 757 / 651; 2 of 3072 (1,200) 1,937 / 1,663; 2 of 4096
-// (2,112) 3,839 / 3,535; 10 of 2048 (2,720) 2,769 / 2,887; 5 of 3072 (3,000) 4,139 /
-// 4,505; 16 of 2048 (4,352) 4,361 / 4,308; 2 of 4096, L 4 (6,208) 10,961 / 14,297; fp32
-// 2 of 1024 (144) 860 / 878, 4 of 1024 (288) 1,486 / 1,182, 2 of 2048 (544) 5,185 /
-// 3,897, 4 of 2048 (1,088) 8,099 / 6,578, 16 of 2048 (4,352) 24,649 / 24,030.
-constexpr int64_t kMuonSplitTiles = 1024, kMuonSplitTilesF32 = 256, kMuonSplitMax = 2560;
-bool muon_split(const pack_handle* h, const std::vector<int>& ids) {
-  if (!h->muon || ids.size() < 2) return false;
+// The Newton-Schulz products of the given members in 128 x 128 tiles: the
+// symmetric ones (on and above the diagonal) or X' (S x L); *work: tiles times depth.
+int64_t ns_small_tiles(const pack_handle* h, const std::vector<int>& ids, bool sym, int64_t* work = nullptr) {
   int64_t n = 0;
   for (int k : ids)
     for (int l = 1; l <= h->mem[k].depth; ++l) {
       const MuonShape q = muon_shape(h, h->mem[k], l);
-      n += small_tiles(q.S, q.L);
+      const int64_t r = (q.S + kSmallTile - 1) / kSmallTile;
+      const int64_t t = sym ? r * (r + 1) / 2 : small_tiles(q.S, q.L);
+      n += t;
+      if (work) *work += t * (sym ? q.L : q.S);
     }
-  if (h->prec == Prec::FP32) return n >= kMuonSplitTilesF32;
-  return n >= kMuonSplitTiles && n < kMuonSplitMax;
+  return n;
+}
+
+// Whether a small pack's Newton-Schulz products are better split over two
+// streams than one launch each: X' numbers kMuonSplitX small tiles or more, the
+// symmetric ones kMuonSplitSym (fewer: a wide first layer, whose products are
+// shallow), and in bf16 X' not so many that the split costs the caches more than
+// it overlaps (from kMuonSplitMax on one launch measured up to 30% faster, or the
+// same within 4%, but for 3 members of width 4096).  fp32 products run at 1/16 of
+// the bf16 rate: they split earlier (into mini tiles) and have no such end.
+// Measured at batch 256, one stream / two groups (us; X' and symmetric tiles): bf16
+// 8 members of width 1024 (576, 296) 504 / 528; 32 of 512 (640, 352) 422 / 399; 3 of
+// 2048 (816, 411) 957 / 1,023; 4 of 2048 (1,088, 548) 1,358 / 1,165; 64 of 512 (1,280,
+// 704) 757 / 651; 90 of 128 on 1,500 features (1,080, 90) 393 / 403; 60 of 128 on 3,000
+// (1,500, 120) 537 / 569; 40 embedded of 256 (1,200, 160) 554 / 525; 2 of 3072 (1,200,
+// 602) 1,937 / 1,663; 2 of 4096 (2,112, 1,058) 3,839 / 3,535; 10 of 2048 (2,720) 2,769 /
+// 2,887; 5 of 3072 (3,000) 4,139 / 4,505; 16 of 2048 (4,352) 4,361 / 4,308; 2 of 4096, L 4
+// (6,208) 10,961 / 14,297; fp32 3 of 1024 (216, 111) 970 / 1,053; 16 embedded of 256 (320,
+// 64) 759 / 818; 4 of 1024 (288, 148) 1,486 / 1,182; 64 of 256 (384, 256) 630 / 514; 2 of
+// 2048 (544, 274) 5,185 / 3,897; 16 of 2048 (4,352, 2,192) 24,649 / 24,030.
+constexpr int64_t kMuonSplitX = 1024, kMuonSplitXF32 = 256, kMuonSplitSym = 144, kMuonSplitMax = 2560;
+bool muon_split(const pack_handle* h, const std::vector<int>& ids) {
+  if (!h->muon || ids.size() < 2 || ns_small_tiles(h, ids, true) < kMuonSplitSym) return false;
+  const int64_t n = ns_small_tiles(h, ids, false);
+  if (h->prec == Prec::FP32) return n >= kMuonSplitXF32;
+  return n >= kMuonSplitX && n < kMuonSplitMax;
 }
 
 // Members into ngroups groups of about equal GEMM work (longest first, each
@@ -852,37 +865,33 @@ void plan_eval(pack_handle* h) {
 }
 
 // Tile set of the Newton-Schulz products of a step, the symmetric ones (A, B') or
-// X': mini tiles where a launch has fewer than kMiniMaxTiles small ones and, with
-// several groups in bf16, all of the groups' launches together, which run side by
-// side and fill the CUs already, are below kSideSym / kSideX (128 x 128 tiles times
-// depth).  Measured, products of all groups small / sym mini / both mini (us a step,
-// three groups): 16 members of width 512 at batch 2048 (sym 92 thousand, X' 135) 494 /
-// 412 / 406; 32 of 512 (180, 270) 548 / 512 / 538; 6 of 1024 (227, 396) 780 / 706 / 728; 8
-// of 1024 (303, 528) 720 / 707 / 751; 64 of 512 (360, 541) 707 / 737 / 794; 12 of 1024
-// (454, 793) 835 / 881 / 970; 4 of 2048 (1,122, 2,102) 1,347 / 1,715 / 1,919.  fp32 products,
-// at 1/16 of the rate, gain from them at any depth: 3 of 2048 (sym 137, X' 272 tiles a
-// group) 7,805 / 7,559 / 7,705, 4 of 1024 (148, 288 in all) 3,080 / 2,451 / 2,148.
-constexpr int64_t kSideSym = 256 << 10, kSideX = 176 << 10;
+// X': mini tiles where a launch has fewer than kMiniMaxTiles small ones -- with
+// several groups in bf16, whose launches run side by side and fill the CUs
+// together, only where all of them have fewer than kSideTiles or their work
+// (tiles times depth) is below kSideSym / kSideX.  Measured, products of all groups small / sym mini / both mini
+// (us a step, three groups; sym tiles and thousands of work, X' work): 16 members of
+// width 512 at batch 2048 (176, 92; 135) 494 / 412 / 406; 32 of 512 (352, 180; 270) 548 /
+// 512 / 538; 6 of 1024 (222, 227; 396) 780 / 706 / 728; 8 of 1024 (296, 303; 528) 720 / 707
+// / 751; 64 of 512 (704, 360; 541) 707 / 737 / 794; 12 of 1024 (444, 454; 793) 835 / 881 /
+// 970; 4 of 2048 (548, 1,122; 2,102) 1,347 / 1,715 / 1,919; in two groups 16 of 512 on 2,000
+// features (320, 402) 705 / 644.  fp32 products, at 1/16 of the rate, gain from them at any
+// depth: 3 of 2048 (sym 137, X' 272 tiles a group) 7,805 / 7,559 / 7,705, 4 of 1024 (148, 288
+// in all) 3,080 / 2,451 / 2,148.
+constexpr int64_t kSideTiles = 400, kSideSym = 256 << 10, kSideX = 176 << 10;
 TileSet ns_tiles(const pack_handle* h, const std::vector<int> (&group)[kGroups], bool sym, bool sizing) {
   if (h->ns_tiles >= 0) return (TileSet)h->ns_tiles;
   if (sizing) return TILES_SMALL;
-  int64_t most = 0, work = 0;
+  int64_t most = 0, all = 0, work = 0;
   int groups = 0;
   for (const std::vector<int>& g : group) {
-    int64_t n = 0;
-    for (int k : g)
-      for (int l = 1; l <= h->mem[k].depth; ++l) {
-        const MuonShape q = muon_shape(h, h->mem[k], l);
-        const int64_t r = (q.S + kSmallTile - 1) / kSmallTile;
-        const int64_t t = sym ? r * (r + 1) / 2 : small_tiles(q.S, q.L);
-        n += t;
-        work += t * (sym ? q.L : q.S);
-      }
     groups += !g.empty();
+    const int64_t n = ns_small_tiles(h, g, sym, &work);
     most = std::max(most, n);
+    all += n;
   }
   if (most >= kMiniMaxTiles) return TILES_SMALL;
-  return groups > 1 && h->prec == Prec::BF16 && work >= (sym ? kSideSym : kSideX) ? TILES_SMALL : TILES_MINI;
+  const bool full = groups > 1 && h->prec == Prec::BF16 && all >= kSideTiles;
+  return full && work >= (sym ? kSideSym : kSideX) ? TILES_SMALL : TILES_MINI;
 }
 
 void plan_muon(const pack_handle* h, const Bufs& bf, const std::vector<int> (&group)[kGroups], Plan& p,

@@ -52,9 +52,12 @@ def test_tile_table_holds_every_plan(monkeypatch, K, width, d_in, over, tiles, s
     (5, 3072, 256, dict(), 1, True), (4, 3072, 256, dict(), 2, False),        # 3,000 and 2,400 of 2,560
     (4, 1024, 256, dict(precision="fp32"), 2, False), (3, 1024, 256, dict(precision="fp32"), 1, True),  # 288, 216 of 256
     (5, 3072, 256, dict(precision="fp32"), 2, False),
+    # few symmetric tiles (of 144): wide first layers, whose products are shallow
+    (90, 128, 256, dict(L=1, d_in=1500), 1, True), (40, 256, 256, dict(d_in=100, emb_lo=16, emb_hi=16), 2, False),
+    (16, 256, 256, dict(precision="fp32", emb_lo=16, emb_hi=16), 1, True),
     (16, 1024, 256, dict(optimizer="adamw"), 1, True), (16, 1024, 2048, dict(), 3, False)])
 def test_muon_split_rule(K, width, B, over, groups, one):
-    cfg = configs.workload("regression_onehot", K=K, B=B, L=2, **dict(dict(optimizer="muon"), **over))
+    cfg = configs.workload("regression_onehot", K=K, B=B, **dict(dict(optimizer="muon", L=2), **over))
     p = tabpack.debug_plan(cfg, members=members(K, width))
     assert (p["groups"], p["one_stream"]) == (groups, one)
 
@@ -65,9 +68,10 @@ SMALL, MINI = 1, 4  # tile sets
 @pytest.mark.parametrize("K,width,B,over,sym,x", [
     # one stream: fewer than 256 tiles a launch -- K ((width / 128)^2 / 2 + ...) and X'
     (3, 1024, 256, dict(), MINI, MINI), (4, 1024, 256, dict(), MINI, SMALL), (8, 1024, 256, dict(), SMALL, SMALL),
-    # three groups in bf16: tiles times depth of all groups' launches below 256 Ki (sym), 176 Ki (X')
+    # groups in bf16: fewer than 400 tiles in all, or tiles times depth below 256 Ki (sym), 176 Ki (X')
     (16, 512, 2048, dict(), MINI, MINI), (32, 512, 1024, dict(), MINI, SMALL), (6, 1024, 4096, dict(), MINI, SMALL),
-    (8, 1024, 2048, dict(), SMALL, SMALL), (4, 2048, 2048, dict(), SMALL, SMALL),
+    (16, 512, 256, dict(d_in=2000), MINI, SMALL),  # (320 symmetric tiles in all, whatever their depth)
+    (8, 1024, 2048, dict(), MINI, SMALL), (12, 1024, 2048, dict(), SMALL, SMALL), (4, 2048, 2048, dict(), SMALL, SMALL),
     # fp32: fewer than 256 tiles in the group with most
     (8, 1024, 2048, dict(precision="fp32"), MINI, MINI), (3, 2048, 4096, dict(precision="fp32"), MINI, SMALL),
     (4, 2048, 2048, dict(precision="fp32"), SMALL, SMALL)])
