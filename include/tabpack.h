@@ -328,6 +328,7 @@ typedef struct pack_plan_info {
   int64_t tiles, tile_capacity; /* GEMM tiles of the launch tables; entries of their table in the workspace */
   int64_t eval_operand;         /* bytes of the largest operand read by rows in an evaluation GEMM */
   int32_t groups, one_stream;   /* member groups of a training step; 1: all its launches on the caller's stream */
+  int32_t tiles_fwd, tiles_dx, tiles_dw; /* tile sets of the first group's launches of layer L */
   int32_t ns_sym, ns_x;         /* Muon: tile sets of the symmetric Newton-Schulz products and of X' */
   int32_t eval_levels;          /* sizes of evaluation chunks, largest first: */
   int32_t eval_rows[PACK_EVAL_LEVELS];  /* their rows */

@@ -44,6 +44,7 @@ constexpr int kEvalLevels = PACK_EVAL_LEVELS;
 constexpr int kGroups = 4;  // at most this many member groups run their GEMM chains concurrently
 
 int64_t round_up(int64_t x, int64_t q) { return (x + q - 1) / q * q; }
+int64_t mini_tiles(int M, int N) { return (int64_t)((M + kMiniTile - 1) / kMiniTile) * ((N + kMiniTile - 1) / kMiniTile); }
 int64_t small_tiles(int M, int N) { return (int64_t)((M + kSmallTile - 1) / kSmallTile) * ((N + kSmallTile - 1) / kSmallTile); }
 
 struct Key {
@@ -806,10 +807,22 @@ constexpr int kTallMinTiles = 1024, kTallMinDepthDw = 2048;
 // ones above all, whose MFMAs run at 1/16 of the bf16 rate).  Measured, small /
 // mini: a prediction of 37 rows by 16 members of widths 128..512 (48 small
 // tiles a layer) 56 / 46 us; an fp32 step of 9 members of widths 33..301 at
-// batch 300 (at most 45) 464 / 265 us; a bf16 step of 32 members of widths
-// 256..1024 at batch 1024 (~220 a launch) 636 / 634 us; with mini tiles up to
-// 640 small ones 668 us.
-constexpr int kMiniMaxTiles = 256;
+// batch 300 (at most 45) 464 / 265 us.  In bf16 with several groups, whose launches
+// run side by side, all groups' launches of the layer together have fewer than
+// kMiniSide mini tiles (narrow members fill them better than small ones), in packs of
+// one block, whose groups reach them at the same time, kMiniSideL1 (two a CU).
+// Batches of at most kMiniSideRows rows of deeper packs leave them short, and mini ones
+// were never slower.
+// Measured, small / mini weight gradients of two groups (small tiles of both, us a
+// step): 10 members of widths 53..211 at batch 4806 (28, 22, 22) 361 / 261; 17 of 114..456
+// at batch 1411 (48, 154, 154) 259 / 220; 29 of 106..423 at batch 1080 (73, 207, 207, 207)
+// 314 / 275; 66 of width 185 at batch 7287 (264, 594 mini ones) 1,239 / 1,118; 26 of 378
+// (234, 936) 736 / 728; 9 of 338..1350 at batch 1831 (330, 391, 391) 441 / 495; 17 of
+// 274..1096 at batch 4960 (102, 341, 268) 839 / 908; one block: 20 of 36..142 at batch 7750
+// (24) 237 / 214, 108 of 83..329 (235, about 780) 178 / 185, 22 of 159..634 (308) 481 / 538; short batches:
+// 56 of 104..415 at batch 916 (420, 384, 384, 384) 455 / 438, 122 of 161 at batch 333 (488)
+// 270 / 256.
+constexpr int kMiniMaxTiles = 256, kMiniSide = 896, kMiniSideL1 = 512, kMiniSideRows = 1024;
 // Huge tiles for forward (and evaluation) launches from kHugeMinFwd small ones
 // on and data-gradient launches from kHugeMinDx on.  Measured, small / tall /
 // huge forward launches: 1,000 rows by 16 of 32 members of widths 256..1024 (700
@@ -822,12 +835,24 @@ constexpr int kMiniMaxTiles = 256;
 // (huge / tall, us): 37 rows by 64 members of width 2048 (chunks of 64 rows, 1,024
 // tiles) 189 / 176, 100 rows (of 128) 242 / 222, by 200 of width 512 165 / 149.
 constexpr int kHugeMinFwd = 640, kHugeMinDx = 2048;
-TileSet launch_tiles(const pack_handle* h, int forced, int64_t n_small, int huge_min = 0, int min_depth = 0) {
+// The output tiles of a launch, or of the launches of all member groups.
+struct LaunchSize {
+  int64_t small = 0, mini = 0;
+  void add(int M, int N) {
+    small += small_tiles(M, N);
+    mini += mini_tiles(M, N);
+  }
+};
+// own: the launch; side: it and those of the other groups, which run beside it.
+TileSet launch_tiles(const pack_handle* h, int forced, const LaunchSize& own, const LaunchSize& side, int huge_min = 0,
+                     int min_depth = 0) {
   if (forced >= 0) return (TileSet)forced;
-  if (n_small < kMiniMaxTiles) return TILES_MINI;
+  const bool one_block = h->cfg.L == 1;
+  const bool beside = h->prec == Prec::BF16 && h->ngroups > 1 && (one_block || h->Bp > kMiniSideRows);
+  if (own.small < kMiniMaxTiles && (!beside || side.mini < (one_block ? kMiniSideL1 : kMiniSide))) return TILES_MINI;
   if (h->prec != Prec::BF16 || h->Bp < min_depth) return TILES_SMALL;
-  if (huge_min > 0 && n_small >= huge_min) return TILES_HUGE;
-  return n_small >= kTallMinTiles ? TILES_TALL : TILES_SMALL;
+  if (huge_min > 0 && own.small >= huge_min) return TILES_HUGE;
+  return own.small >= kTallMinTiles ? TILES_TALL : TILES_SMALL;
 }
 
 // Rows of an evaluation chunk: the training batch's padded rows times a power
@@ -1027,9 +1052,23 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
   Plan p;
   p.unsorted = sizing;
   // sizing: small tiles for the main GEMMs (the largest tile count of any choice)
-  auto choose = [&](int forced, int64_t n_small, int huge_min, int min_depth = 0) {
-    return sizing ? TILES_SMALL : launch_tiles(h, forced, n_small, huge_min, min_depth);
+  auto choose = [&](int forced, const LaunchSize& own, const LaunchSize& side, int huge_min, int min_depth = 0) {
+    return sizing ? TILES_SMALL : launch_tiles(h, forced, own, side, huge_min, min_depth);
   };
+  // choose() for group hf's launch over the members that have layer l, whose output is shape(member, M, N)
+  auto choose_layer = [&](int forced, int hf, int l, auto shape, int huge_min, int min_depth = 0) {
+    LaunchSize own, side;
+    for (int g = 0; g < kGroups; ++g)
+      for (int k : group[g]) {
+        if (h->mem[k].depth < l) continue;
+        int M = 0, N = 0;
+        shape(h->mem[k], M, N);
+        side.add(M, N);
+        if (g == hf) own.add(M, N);
+      }
+    return choose(forced, own, side, huge_min, min_depth);
+  };
+  auto act_shape = [&](const Member& m, int& M, int& N) { M = h->Bp, N = m.dp; };
   const pack_config& c = h->cfg;
   const size_t es = h->elt();
   const void* wsrc = h->prec == Prec::BF16 ? (const void*)bf.shadow : (const void*)bf.theta;
@@ -1052,11 +1091,9 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     // forward: Z_l = H_{l-1} W_l^T + b_l, rows = batch (Bp), cols = dp; members
     // with fewer than l hidden blocks are not in the launch
     Launch f{(int)p.descs.size(), 0, (int)p.tiles.size(), 0, 0.0};
-    int64_t nsm = 0;
-    for (int k : group[hf])
-      if (h->mem[k].depth >= l) nsm += small_tiles(h->Bp, h->mem[k].dp);
     // the embedded first layer (E produced in the GEMM): its own tile set
-    p.tile_set = l == 1 && h->emb ? (sizing ? TILES_SMALL : h->emb_tiles) : choose(h->tiles_fwd, nsm, kHugeMinFwd);
+    p.tile_set = l == 1 && h->emb ? (sizing ? TILES_SMALL : h->emb_tiles)
+                                  : choose_layer(h->tiles_fwd, hf, l, act_shape, kHugeMinFwd);
     for (int k : group[hf]) {
       const Member& m = h->mem[k];
       if (m.depth < l) continue;
@@ -1108,12 +1145,12 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     };
     for (int l = 1; l <= c.L; ++l) {
       Launch f{(int)p.descs.size(), 0, (int)p.tiles.size(), 0, 0.0, 0.0};
-      int64_t nsm = 0;
+      LaunchSize z;
       for (int hf = 0; hf < kGroups; ++hf)
         for (int k : group[hf])
-          if (h->mem[k].depth >= l) nsm += small_tiles(R, h->mem[k].dp);
+          if (h->mem[k].depth >= l) z.add(R, h->mem[k].dp);
       p.tile_set = l == 1 && h->emb ? (sizing ? TILES_SMALL : h->emb_tiles)
-                                    : choose(h->tiles_fwd, nsm, R >= kBigTile ? kHugeMinFwd : 0);
+                                    : choose(h->tiles_fwd, z, LaunchSize{}, R >= kBigTile ? kHugeMinFwd : 0);
       for (int hf = 0; hf < kGroups; ++hf)
         for (int k : group[hf]) {
           const Member& m = h->mem[k];
@@ -1142,10 +1179,8 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
   for (int l = 1; l <= c.L; ++l) {
     // weight gradient: dW_l^T[out, in] = sum_rows dZ_l[row, out] H_{l-1}[row, in]
     Launch w{(int)p.descs.size(), 0, (int)p.tiles.size(), 0, 0.0};
-    int64_t nsm = 0;
-    for (int k : group[hf])
-      if (h->mem[k].depth >= l) nsm += small_tiles(h->mem[k].dp, l == 1 ? h->mem[k].p_in : h->mem[k].dp);
-    p.tile_set = l == 1 && h->emb ? TILES_SMALL : choose(h->tiles_dw, nsm, 0, kTallMinDepthDw);
+    auto dw_shape = [&](const Member& m, int& M, int& N) { M = m.dp, N = l == 1 ? m.p_in : m.dp; };
+    p.tile_set = l == 1 && h->emb ? TILES_SMALL : choose_layer(h->tiles_dw, hf, l, dw_shape, 0, kTallMinDepthDw);
     for (int k : group[hf]) {
       const Member& m = h->mem[k];
       if (m.depth < l) continue;
@@ -1196,10 +1231,7 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     // data gradient (l >= 2): dZ_{l-1} = (dZ_l W_l) * [H_{l-1} > 0] * s_k
     Launch x{(int)p.descs.size(), 0, (int)p.tiles.size(), 0, 0.0};
     if (l >= 2) {
-      int64_t nsx = 0;
-      for (int k : group[hf])
-        if (h->mem[k].depth >= l) nsx += small_tiles(h->Bp, h->mem[k].dp);
-      p.tile_set = choose(h->tiles_dx, nsx, kHugeMinDx);
+      p.tile_set = choose_layer(h->tiles_dx, hf, l, act_shape, kHugeMinDx);
       for (int k : group[hf]) {
         const Member& m = h->mem[k];
         if (m.depth < l) continue;
@@ -1234,13 +1266,13 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     // descriptors: a second copy of their tiles in the table
     Launch& w = p.dw_all;
     w = Launch{0, 0, (int)p.tiles.size(), 0, 0.0, 0.0};
-    int64_t nsm = 0;
+    LaunchSize z;
     for (int l = h->emb ? 2 : 1; l <= c.L; ++l)
       for (int i = 0; i < p.dw[0][l - 1].ndesc; ++i) {
         const GemmDesc& d = p.descs[p.dw[0][l - 1].desc0 + i];
-        nsm += small_tiles(d.M, d.N);
+        z.add(d.M, d.N);
       }
-    p.tile_set = choose(h->tiles_dw, nsm, 0, kTallMinDepthDw);
+    p.tile_set = choose(h->tiles_dw, z, LaunchSize{}, 0, kTallMinDepthDw);
     for (int l = h->emb ? 2 : 1; l <= c.L; ++l) {
       const Launch& ln = p.dw[0][l - 1];
       for (int i = 0; i < ln.ndesc; ++i) {
@@ -1750,6 +1782,9 @@ int pack_debug_plan(const pack_config* cfg, const uint8_t* active, pack_plan_inf
     out->ns_sym = plan.nsB[0].ts;
     out->ns_x = plan.nsX[0][0].ts;
   }
+  out->tiles_fwd = plan.fwd[0][0].back().ts;
+  out->tiles_dx = plan.dx[0].back().ts;
+  out->tiles_dw = plan.dw[0].back().ts;
   out->eval_levels = h->eval_levels;
   for (int lv = 0; lv < h->eval_levels; ++lv) {
     out->eval_rows[lv] = h->eval_rows(lv);

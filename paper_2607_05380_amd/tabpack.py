@@ -66,8 +66,9 @@ class KernelStat(ctypes.Structure):
 
 class PlanInfo(ctypes.Structure):
     _fields_ = [("tiles", ctypes.c_int64), ("tile_capacity", ctypes.c_int64), ("eval_operand", ctypes.c_int64),
-                ("groups", ctypes.c_int32), ("one_stream", ctypes.c_int32), ("ns_sym", ctypes.c_int32),
-                ("ns_x", ctypes.c_int32), ("eval_levels", ctypes.c_int32),
+                ("groups", ctypes.c_int32), ("one_stream", ctypes.c_int32),
+                ("tiles_fwd", ctypes.c_int32), ("tiles_dx", ctypes.c_int32), ("tiles_dw", ctypes.c_int32),
+                ("ns_sym", ctypes.c_int32), ("ns_x", ctypes.c_int32), ("eval_levels", ctypes.c_int32),
                 ("eval_rows", ctypes.c_int32 * 8), ("eval_tiles", ctypes.c_int32 * 8)]
 
 
@@ -427,7 +428,8 @@ def debug_plan(cfg, members=None, active=None):
     del keep
     n = info.eval_levels
     return dict(tiles=info.tiles, tile_capacity=info.tile_capacity, eval_operand=info.eval_operand,
-                groups=info.groups, one_stream=bool(info.one_stream), ns_sym=info.ns_sym, ns_x=info.ns_x,
+                groups=info.groups, one_stream=bool(info.one_stream), tiles_fwd=info.tiles_fwd,
+                tiles_dx=info.tiles_dx, tiles_dw=info.tiles_dw, ns_sym=info.ns_sym, ns_x=info.ns_x,
                 eval_rows=list(info.eval_rows[:n]),
                 eval_tiles=list(info.eval_tiles[:n]))
 

@@ -103,3 +103,15 @@ def test_operands_past_the_limit_are_refused(K, width, B, d_in, over, refused):
             tabpack.debug_plan(cfg, members=members(K, width))
     else:
         assert tabpack.debug_plan(cfg, members=members(K, width))["tiles"] > 0
+
+
+@pytest.mark.parametrize("K,width,B,L,over,dw", [
+    # two groups in bf16: fewer than 896 mini tiles (64 x 64) of both together, 512 in packs of one block
+    (24, 384, 2304, 2, dict(), MINI), (26, 384, 2304, 2, dict(), SMALL),  # 864 and 936
+    (62, 256, 2304, 1, dict(d_in=64), MINI), (130, 256, 2304, 1, dict(d_in=64), SMALL),  # 248 and 520
+    (26, 384, 1024, 2, dict(K=60), SMALL), (30, 384, 1024, 2, dict(), MINI),  # short batches: the group's 135 of 256
+    (26, 384, 2304, 2, dict(precision="fp32"), MINI), (60, 384, 2304, 2, dict(precision="fp32"), SMALL)])
+def test_mini_weight_gradients_of_several_groups(K, width, B, L, over, dw):
+    cfg = configs.workload("regression_onehot", B=B, L=L, **dict(dict(K=K), **over))
+    p = tabpack.debug_plan(cfg, members=members(cfg["K"], width))
+    assert p["groups"] == 2 and p["tiles_dw"] == dw
