@@ -811,8 +811,8 @@ constexpr int kTallMinTiles = 1024, kTallMinDepthDw = 2048;
 // run side by side, all groups' launches of the layer together have fewer than
 // kMiniSide mini tiles (narrow members fill them better than small ones), in packs of
 // one block, whose groups reach them at the same time, kMiniSideL1 (two a CU).
-// Batches of at most kMiniSideRows rows of deeper packs leave them short, and mini ones
-// were never slower.
+// (Not the weight gradients of deeper packs at batches of at most kMiniSideRows rows:
+// they are short, and mini tiles were never slower.)
 // Measured, small / mini weight gradients of two groups (small tiles of both, us a
 // step): 10 members of widths 53..211 at batch 4806 (28, 22, 22) 361 / 261; 17 of 114..456
 // at batch 1411 (48, 154, 154) 259 / 220; 29 of 106..423 at batch 1080 (73, 207, 207, 207)
@@ -848,7 +848,7 @@ TileSet launch_tiles(const pack_handle* h, int forced, const LaunchSize& own, co
                      int min_depth = 0) {
   if (forced >= 0) return (TileSet)forced;
   const bool one_block = h->cfg.L == 1;
-  const bool beside = h->prec == Prec::BF16 && h->ngroups > 1 && (one_block || h->Bp > kMiniSideRows);
+  const bool beside = h->prec == Prec::BF16 && h->ngroups > 1;
   if (own.small < kMiniMaxTiles && (!beside || side.mini < (one_block ? kMiniSideL1 : kMiniSide))) return TILES_MINI;
   if (h->prec != Prec::BF16 || h->Bp < min_depth) return TILES_SMALL;
   if (huge_min > 0 && own.small >= huge_min) return TILES_HUGE;
@@ -1056,7 +1056,8 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     return sizing ? TILES_SMALL : launch_tiles(h, forced, own, side, huge_min, min_depth);
   };
   // choose() for group hf's launch over the members that have layer l, whose output is shape(member, M, N)
-  auto choose_layer = [&](int forced, int hf, int l, auto shape, int huge_min, int min_depth = 0) {
+  auto choose_layer = [&](int forced, int hf, int l, auto shape, int huge_min, int min_depth = 0,
+                          bool alone = false) {
     LaunchSize own, side;
     for (int g = 0; g < kGroups; ++g)
       for (int k : group[g]) {
@@ -1066,7 +1067,7 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
         side.add(M, N);
         if (g == hf) own.add(M, N);
       }
-    return choose(forced, own, side, huge_min, min_depth);
+    return choose(forced, own, alone ? LaunchSize{} : side, huge_min, min_depth);
   };
   auto act_shape = [&](const Member& m, int& M, int& N) { M = h->Bp, N = m.dp; };
   const pack_config& c = h->cfg;
@@ -1180,7 +1181,9 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     // weight gradient: dW_l^T[out, in] = sum_rows dZ_l[row, out] H_{l-1}[row, in]
     Launch w{(int)p.descs.size(), 0, (int)p.tiles.size(), 0, 0.0};
     auto dw_shape = [&](const Member& m, int& M, int& N) { M = m.dp, N = l == 1 ? m.p_in : m.dp; };
-    p.tile_set = l == 1 && h->emb ? TILES_SMALL : choose_layer(h->tiles_dw, hf, l, dw_shape, 0, kTallMinDepthDw);
+    const bool alone = c.L > 1 && h->Bp <= kMiniSideRows;  // (short: the other groups' launches do not count)
+    p.tile_set = l == 1 && h->emb ? TILES_SMALL
+                                  : choose_layer(h->tiles_dw, hf, l, dw_shape, 0, kTallMinDepthDw, alone);
     for (int k : group[hf]) {
       const Member& m = h->mem[k];
       if (m.depth < l) continue;
