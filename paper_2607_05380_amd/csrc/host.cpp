@@ -823,8 +823,8 @@ constexpr int kTallMinTiles = 1024, kTallMinDepthDw = 2048;
 // 56 of 104..415 at batch 916 (420, 384, 384, 384) 455 / 438, 122 of 161 at batch 333 (488)
 // 270 / 256.
 constexpr int kMiniMaxTiles = 256, kMiniSide = 896, kMiniSideL1 = 512, kMiniSideRows = 1024;
-// Huge tiles for forward (and evaluation) launches from kHugeMinFwd small ones
-// on and data-gradient launches from kHugeMinDx on.  Measured, small / tall /
+// Huge tiles for forward (and evaluation) launches from kHugeFwd.tiles small ones
+// on and data-gradient launches from kHugeDx.tiles on.  Measured, small / tall /
 // huge forward launches: 1,000 rows by 16 of 32 members of widths 256..1024 (700
 // small tiles a launch) 146 / 141 / 137 us, by all 32 (1,400) 205 / 220 / 198;
 // a step of 32 such members (700) 644 / 634 / 632 us, of 24 (525) 504 / 512 /
@@ -834,24 +834,36 @@ constexpr int kMiniMaxTiles = 256, kMiniSide = 896, kMiniSideL1 = 512, kMiniSide
 // Evaluation chunks of fewer rows than one huge tile keep the smaller tiles
 // (huge / tall, us): 37 rows by 64 members of width 2048 (chunks of 64 rows, 1,024
 // tiles) 189 / 176, 100 rows (of 128) 242 / 222, by 200 of width 512 165 / 149.
-constexpr int kHugeMinFwd = 640, kHugeMinDx = 2048;
+// Shallow launches leave them nothing to cover the tile's start and end with
+// (one workgroup a CU): below a mean depth of kHuge*.depth they cost time.  small
+// or tall / huge forward launches of two groups (us a step; depth a layer): 108
+// members of width 329, one layer (104) 178 / 198; 27 of 192 at batch 6467 (16, 148) 391 /
+// 423; 26 of 378 (200, 384, 384, 384) 736 / 769; 17 of 373 (320, 284, 284) 587 / 620; 30 of
+// 505 (616, 512, 512) 1,033 / 1,003; 15 of 1154 (128, 853, 853) 655 / 639; 11 of 1909 (424,
+// 1,388, ..) 2,465 / 2,369; huge data gradients 77 of 362 (264) 1,772 / 1,841; 116 of 625
+// (640) 1,624 / 1,669; 18 of 1222 (1,248) 2,283 / 2,080.
+struct HugeMin {
+  int tiles = 0, depth = 0;  // least small tiles and tile-weighted mean depth of a launch (tiles 0: never)
+};
+constexpr HugeMin kHugeFwd{640, 512}, kHugeDx{2048, 768};
 // The output tiles of a launch, or of the launches of all member groups.
 struct LaunchSize {
-  int64_t small = 0, mini = 0;
-  void add(int M, int N) {
+  int64_t small = 0, mini = 0, work = 0;  // work: small tiles times depth
+  void add(int M, int N, int depth) {
     small += small_tiles(M, N);
     mini += mini_tiles(M, N);
+    work += small_tiles(M, N) * depth;
   }
 };
 // own: the launch; side: it and those of the other groups, which run beside it.
-TileSet launch_tiles(const pack_handle* h, int forced, const LaunchSize& own, const LaunchSize& side, int huge_min = 0,
+TileSet launch_tiles(const pack_handle* h, int forced, const LaunchSize& own, const LaunchSize& side, HugeMin huge = {},
                      int min_depth = 0) {
   if (forced >= 0) return (TileSet)forced;
   const bool one_block = h->cfg.L == 1;
   const bool beside = h->prec == Prec::BF16 && h->ngroups > 1;
   if (own.small < kMiniMaxTiles && (!beside || side.mini < (one_block ? kMiniSideL1 : kMiniSide))) return TILES_MINI;
   if (h->prec != Prec::BF16 || h->Bp < min_depth) return TILES_SMALL;
-  if (huge_min > 0 && own.small >= huge_min) return TILES_HUGE;
+  if (huge.tiles > 0 && own.small >= huge.tiles && own.work >= own.small * huge.depth) return TILES_HUGE;
   return own.small >= kTallMinTiles ? TILES_TALL : TILES_SMALL;
 }
 
@@ -1052,24 +1064,23 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
   Plan p;
   p.unsorted = sizing;
   // sizing: small tiles for the main GEMMs (the largest tile count of any choice)
-  auto choose = [&](int forced, const LaunchSize& own, const LaunchSize& side, int huge_min, int min_depth = 0) {
-    return sizing ? TILES_SMALL : launch_tiles(h, forced, own, side, huge_min, min_depth);
+  auto choose = [&](int forced, const LaunchSize& own, const LaunchSize& side, HugeMin huge, int min_depth = 0) {
+    return sizing ? TILES_SMALL : launch_tiles(h, forced, own, side, huge, min_depth);
   };
-  // choose() for group hf's launch over the members that have layer l, whose output is shape(member, M, N)
-  auto choose_layer = [&](int forced, int hf, int l, auto shape, int huge_min, int min_depth = 0,
+  // choose() for group hf's launch over the members that have layer l, whose products are shape(member, M, N, depth)
+  auto choose_layer = [&](int forced, int hf, int l, auto shape, HugeMin huge, int min_depth = 0,
                           bool alone = false) {
     LaunchSize own, side;
     for (int g = 0; g < kGroups; ++g)
       for (int k : group[g]) {
         if (h->mem[k].depth < l) continue;
-        int M = 0, N = 0;
-        shape(h->mem[k], M, N);
-        side.add(M, N);
-        if (g == hf) own.add(M, N);
+        int M = 0, N = 0, depth = 0;
+        shape(h->mem[k], M, N, depth);
+        side.add(M, N, depth);
+        if (g == hf) own.add(M, N, depth);
       }
-    return choose(forced, own, alone ? LaunchSize{} : side, huge_min, min_depth);
+    return choose(forced, own, alone ? LaunchSize{} : side, huge, min_depth);
   };
-  auto act_shape = [&](const Member& m, int& M, int& N) { M = h->Bp, N = m.dp; };
   const pack_config& c = h->cfg;
   const size_t es = h->elt();
   const void* wsrc = h->prec == Prec::BF16 ? (const void*)bf.shadow : (const void*)bf.theta;
@@ -1093,8 +1104,9 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     // with fewer than l hidden blocks are not in the launch
     Launch f{(int)p.descs.size(), 0, (int)p.tiles.size(), 0, 0.0};
     // the embedded first layer (E produced in the GEMM): its own tile set
+    auto fwd_shape = [&](const Member& m, int& M, int& N, int& d) { M = h->Bp, N = m.dp, d = l == 1 ? m.p_in : m.dp; };
     p.tile_set = l == 1 && h->emb ? (sizing ? TILES_SMALL : h->emb_tiles)
-                                  : choose_layer(h->tiles_fwd, hf, l, act_shape, kHugeMinFwd);
+                                  : choose_layer(h->tiles_fwd, hf, l, fwd_shape, kHugeFwd);
     for (int k : group[hf]) {
       const Member& m = h->mem[k];
       if (m.depth < l) continue;
@@ -1149,9 +1161,9 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
       LaunchSize z;
       for (int hf = 0; hf < kGroups; ++hf)
         for (int k : group[hf])
-          if (h->mem[k].depth >= l) z.add(R, h->mem[k].dp);
+          if (h->mem[k].depth >= l) z.add(R, h->mem[k].dp, l == 1 ? h->mem[k].p_in : h->mem[k].dp);
       p.tile_set = l == 1 && h->emb ? (sizing ? TILES_SMALL : h->emb_tiles)
-                                    : choose(h->tiles_fwd, z, LaunchSize{}, R >= kBigTile ? kHugeMinFwd : 0);
+                                    : choose(h->tiles_fwd, z, LaunchSize{}, R >= kBigTile ? kHugeFwd : HugeMin{});
       for (int hf = 0; hf < kGroups; ++hf)
         for (int k : group[hf]) {
           const Member& m = h->mem[k];
@@ -1180,10 +1192,10 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
   for (int l = 1; l <= c.L; ++l) {
     // weight gradient: dW_l^T[out, in] = sum_rows dZ_l[row, out] H_{l-1}[row, in]
     Launch w{(int)p.descs.size(), 0, (int)p.tiles.size(), 0, 0.0};
-    auto dw_shape = [&](const Member& m, int& M, int& N) { M = m.dp, N = l == 1 ? m.p_in : m.dp; };
+    auto dw_shape = [&](const Member& m, int& M, int& N, int& d) { M = m.dp, N = l == 1 ? m.p_in : m.dp, d = h->Bp; };
     const bool alone = c.L > 1 && h->Bp <= kMiniSideRows;  // (short: the other groups' launches do not count)
     p.tile_set = l == 1 && h->emb ? TILES_SMALL
-                                  : choose_layer(h->tiles_dw, hf, l, dw_shape, 0, kTallMinDepthDw, alone);
+                                  : choose_layer(h->tiles_dw, hf, l, dw_shape, {}, kTallMinDepthDw, alone);
     for (int k : group[hf]) {
       const Member& m = h->mem[k];
       if (m.depth < l) continue;
@@ -1234,7 +1246,8 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     // data gradient (l >= 2): dZ_{l-1} = (dZ_l W_l) * [H_{l-1} > 0] * s_k
     Launch x{(int)p.descs.size(), 0, (int)p.tiles.size(), 0, 0.0};
     if (l >= 2) {
-      p.tile_set = choose_layer(h->tiles_dx, hf, l, act_shape, kHugeMinDx);
+      auto dx_shape = [&](const Member& m, int& M, int& N, int& d) { M = h->Bp, N = d = m.dp; };
+      p.tile_set = choose_layer(h->tiles_dx, hf, l, dx_shape, kHugeDx);
       for (int k : group[hf]) {
         const Member& m = h->mem[k];
         if (m.depth < l) continue;
@@ -1273,9 +1286,9 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
     for (int l = h->emb ? 2 : 1; l <= c.L; ++l)
       for (int i = 0; i < p.dw[0][l - 1].ndesc; ++i) {
         const GemmDesc& d = p.descs[p.dw[0][l - 1].desc0 + i];
-        z.add(d.M, d.N);
+        z.add(d.M, d.N, d.Kd);
       }
-    p.tile_set = choose(h->tiles_dw, z, LaunchSize{}, 0, kTallMinDepthDw);
+    p.tile_set = choose(h->tiles_dw, z, LaunchSize{}, {}, kTallMinDepthDw);
     for (int l = h->emb ? 2 : 1; l <= c.L; ++l) {
       const Launch& ln = p.dw[0][l - 1];
       for (int i = 0; i < ln.ndesc; ++i) {
