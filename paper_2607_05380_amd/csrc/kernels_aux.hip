@@ -488,15 +488,23 @@ __global__ __launch_bounds__(256) void head_bwd_kernel(const T* H, const float* 
 }
 
 // sum over i < ceil(n / step) of term(i), added in order of i; the terms are
-// fetched 8 at a time before they are added, so their loads overlap
+// fetched 8 at a time before they are added, so their loads overlap (the last
+// ones by clamped indices: a load under a condition of its own waits for the one
+// before, 53 against 28 us for 88 members of width 352 at batch 3176)
 template <typename V, typename F>
 __device__ __forceinline__ V sum_in_order(int n, int step, F term) {
   const int m = n <= 0 ? 0 : (n + step - 1) / step;
-  V s = 0;
-  for (int i = 0; i < m; i += 8) {
-    V v[8];
+  V s = 0, v[8];
+  int i = 0;
+  for (; i + 8 <= m; i += 8) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = i + u < m ? term(i + u) : V(0);
+    for (int u = 0; u < 8; ++u) v[u] = term(i + u);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
+  if (i < m) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = term(i + u < m ? i + u : m - 1);
 #pragma unroll
     for (int u = 0; u < 8; ++u)
       if (i + u < m) s += v[u];
