@@ -841,18 +841,22 @@ constexpr int kMiniMaxTiles = 256, kMiniSide = 896, kMiniSideL1 = 512, kMiniSide
 // 423; 26 of 378 (200, 384, 384, 384) 736 / 769; 17 of 373 (320, 284, 284) 587 / 620; 30 of
 // 505 (616, 512, 512) 1,033 / 1,003; 15 of 1154 (128, 853, 853) 655 / 639; 11 of 1909 (424,
 // 1,388, ..) 2,465 / 2,369; huge data gradients 77 of 362 (264) 1,772 / 1,841; 116 of 625
-// (640) 1,624 / 1,669; 18 of 1222 (1,248) 2,283 / 2,080.
+// (640) 1,624 / 1,669; 18 of 1222 (1,248) 2,283 / 2,080.  Against small tiles (fewer than
+// kTallMinTiles) of two members or more an XCD, which even them out, half that depth will
+// do: 32 members of widths 256..1024 on 256 features 563 / 557, 64 of 128..512 on 300 427 /
+// 421; against tall ones 64 of 256..1024 on 256 1,170 / 1,180.
 struct HugeMin {
   int tiles = 0, depth = 0;  // least small tiles and tile-weighted mean depth of a launch (tiles 0: never)
 };
 constexpr HugeMin kHugeFwd{640, 512}, kHugeDx{2048, 768};
 // The output tiles of a launch, or of the launches of all member groups.
 struct LaunchSize {
-  int64_t small = 0, mini = 0, work = 0;  // work: small tiles times depth
+  int64_t small = 0, mini = 0, work = 0, members = 0;  // work: small tiles times depth
   void add(int M, int N, int depth) {
     small += small_tiles(M, N);
     mini += mini_tiles(M, N);
     work += small_tiles(M, N) * depth;
+    ++members;
   }
 };
 // own: the launch; side: it and those of the other groups, which run beside it.
@@ -863,8 +867,10 @@ TileSet launch_tiles(const pack_handle* h, int forced, const LaunchSize& own, co
   const bool beside = h->prec == Prec::BF16 && h->ngroups > 1;
   if (own.small < kMiniMaxTiles && (!beside || side.mini < (one_block ? kMiniSideL1 : kMiniSide))) return TILES_MINI;
   if (h->prec != Prec::BF16 || h->Bp < min_depth) return TILES_SMALL;
-  if (huge.tiles > 0 && own.small >= huge.tiles && own.work >= own.small * huge.depth) return TILES_HUGE;
-  return own.small >= kTallMinTiles ? TILES_TALL : TILES_SMALL;
+  const bool tall = own.small >= kTallMinTiles;
+  const int depth = tall || own.members < 2 * kXcds ? huge.depth : huge.depth / 2;
+  if (huge.tiles > 0 && own.small >= huge.tiles && own.work >= own.small * depth) return TILES_HUGE;
+  return tall ? TILES_TALL : TILES_SMALL;
 }
 
 // Rows of an evaluation chunk: the training batch's padded rows times a power

@@ -119,7 +119,9 @@ def test_mini_weight_gradients_of_several_groups(K, width, B, L, over, dw):
 
 @pytest.mark.parametrize("K,width,B,over,fwd,dx", [
     # huge (5) from 640 small tiles of a mean depth of 512 on, data gradients from 2,048 of 768; else tall (2) from 1,024
-    (40, 512, 2048, dict(), 5, 2), (40, 480, 2048, dict(), 2, 2), (44, 768, 2048, dict(), 5, 5), (44, 736, 2048, dict(), 5, 2),
+    (40, 512, 2048, dict(), 5, 2), (40, 480, 2048, dict(), 2, 2),
+    # (of 256 against small tiles of 16 members or more a launch)
+    (32, 480, 1280, dict(), 5, 1), (30, 480, 1536, dict(), 1, 1), (64, 224, 1280, dict(), 1, 1), (44, 768, 2048, dict(), 5, 5), (44, 736, 2048, dict(), 5, 2),
     (24, 512, 1792, dict(), 5, 1), (22, 512, 1792, dict(), 1, 1),  # 672 and 616 small tiles a group
     (40, 512, 2048, dict(precision="fp32"), 1, 1)])
 def test_huge_tiles_only_for_deep_launches(K, width, B, over, fwd, dx):
