@@ -787,9 +787,9 @@ void add_tiles_sym(Plan& p, Launch& ln, int d, int S, int kdepth) {
   ln.ntiles = (int)p.tiles.size() - ln.tile0;
 }
 
-// Tile set of one forward / data-gradient / weight-gradient launch whose
-// 128 x 128 tiles number n_small: fixed by `forced` (>= 0), else 256 x 128 tiles
-// when there are at least kTallMinTiles small ones (two full rounds of tall
+// Tile set of one forward / data-gradient / weight-gradient launch by its
+// 128 x 128 tiles: fixed by `forced` (>= 0), mini or huge tiles by the rules below,
+// else 256 x 128 tiles when there are at least kTallMinTiles small ones (two full rounds of tall
 // tiles at two workgroups per CU), small tiles otherwise.  Measured (ms per
 // step, all small / all tall / chosen): 64 members of widths 64..2048 at batch
 // 2048 (launches of 700..2800 small tiles) 6.29 / 5.76; 64 of widths
@@ -808,10 +808,10 @@ constexpr int kTallMinTiles = 1024, kTallMinDepthDw = 2048;
 // mini: a prediction of 37 rows by 16 members of widths 128..512 (48 small
 // tiles a layer) 56 / 46 us; an fp32 step of 9 members of widths 33..301 at
 // batch 300 (at most 45) 464 / 265 us.  In bf16 with several groups, whose launches
-// run side by side, all groups' launches of the layer together have fewer than
-// kMiniSide mini tiles (narrow members fill them better than small ones), in packs of
-// one block, whose groups reach them at the same time, kMiniSideL1 (two a CU).
-// (Not the weight gradients of deeper packs at batches of at most kMiniSideRows rows:
+// run side by side, all groups' launches of the layer together must also have fewer
+// than kMiniSide mini tiles (narrow members fill them better than small ones), in
+// packs of one block, whose groups reach them at the same time, than kMiniSideL1
+// (two a CU).  (Not the weight gradients of deeper packs at batches of at most kMiniSideRows rows:
 // they are short, and mini tiles were never slower.)
 // Measured, small / mini weight gradients of two groups (small tiles of both, us a
 // step): 10 members of widths 53..211 at batch 4806 (28, 22, 22) 361 / 261; 17 of 114..456
@@ -819,8 +819,8 @@ constexpr int kTallMinTiles = 1024, kTallMinDepthDw = 2048;
 // 314 / 275; 66 of width 185 at batch 7287 (264, 594 mini ones) 1,239 / 1,118; 26 of 378
 // (234, 936) 736 / 728; 9 of 338..1350 at batch 1831 (330, 391, 391) 441 / 495; 17 of
 // 274..1096 at batch 4960 (102, 341, 268) 839 / 908; one block: 20 of 36..142 at batch 7750
-// (24) 237 / 214, 108 of 83..329 (235, about 780) 178 / 185, 22 of 159..634 (308) 481 / 538; short batches:
-// 56 of 104..415 at batch 916 (420, 384, 384, 384) 455 / 438, 122 of 161 at batch 333 (488)
+// (24) 237 / 214, 108 of 83..329 (235, about 780) 178 / 185, 22 of 159..634 (308) 481 /
+// 538; short batches: 56 of 104..415 at batch 916 (420, 384, 384, 384) 455 / 438, 122 of 161 at batch 333 (488)
 // 270 / 256.
 constexpr int kMiniMaxTiles = 256, kMiniSide = 896, kMiniSideL1 = 512, kMiniSideRows = 1024;
 // Huge tiles for forward (and evaluation) launches from kHugeFwd.tiles small ones
