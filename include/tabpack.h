@@ -153,9 +153,9 @@ int pack_get_hparams(const pack_handle* h, pack_member_hp* out);
 /* Device workspace (bytes) that pack_bind() needs: parameters, gradients,
  * AdamW moments, bf16 weight shadow, activations and launch tables.  The
  * activations are sized for evaluation chunks of up to 8,192 rows (8,192 tiles
- * of 128 x 128 a layer, 256 MiB of gathered input): at most 0.25 GiB a layer in
- * bf16 (0.5 in fp32) more than training alone needs, most of a small pack's
- * workspace. */
+ * of 128 x 128 a layer, 2 GiB of gathered input): at most 0.25 GiB a layer in
+ * bf16 (0.5 in fp32) and the chunk's input rows more than training alone needs,
+ * most of a small pack's workspace. */
 int pack_workspace_size(const pack_handle* h, size_t* bytes);
 
 /* Bind a caller-owned device workspace of at least pack_workspace_size()

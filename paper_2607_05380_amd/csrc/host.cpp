@@ -883,11 +883,12 @@ TileSet launch_tiles(const pack_handle* h, int forced, const LaunchSize& own, co
 // 26.1 / 21.6 ms, 32 of them on 20,000 rows 4.56 / 3.38 ms, 16 members of
 // 128..512 on 37 rows 39.9 / 28.6 us (chunks of 512 rows, of 128).
 // Wide inputs bound the growth too: the gathered rows H_0 are one GEMM operand,
-// which must stay below kOperandBytes, and would dominate the workspace
-// (kEvalInputBytes: 8,192 rows of 8,192 fp32 or 16,384 bf16 features).  Where
-// even a chunk of Bp rows holds a larger operand, a chunk takes the rows below
-// the limit (eval_cap).
-constexpr int64_t kEvalTiles = 8192, kEvalRows = 8192, kEvalInputBytes = (int64_t)256 << 20;
+// which must stay below kOperandBytes (a smaller bound costs requests that then
+// fall into a chunk four times their rows, planned for other tiles: 256 MiB took
+// 1,100 rows of 16,000 fp32 features from 629 to 1,260 us).  Where even a chunk of
+// Bp rows holds a larger operand, a chunk takes the rows below the limit
+// (eval_cap).
+constexpr int64_t kEvalTiles = 8192, kEvalRows = 8192;
 void plan_eval(pack_handle* h) {
   int64_t n = 0, row = h->emb ? 0 : h->Pin;
   for (const Member& m : h->mem) {
@@ -899,7 +900,7 @@ void plan_eval(pack_handle* h) {
   h->eval_shift = 0;
   auto fits = [&](int shift) {
     const int64_t rows = (int64_t)h->Bp << shift;
-    return n << shift <= kEvalTiles && rows <= kEvalRows && rows * in_row <= kEvalInputBytes;
+    return n << shift <= kEvalTiles && rows <= kEvalRows && rows * in_row <= kOperandBytes;
   };
   while (fits(h->eval_shift + 1)) ++h->eval_shift;
   h->eval_levels = 1;

@@ -127,3 +127,11 @@ def test_mini_weight_gradients_of_several_groups(K, width, B, L, over, dw):
 def test_huge_tiles_only_for_deep_launches(K, width, B, over, fwd, dx):
     p = tabpack.debug_plan(configs.workload("regression_onehot", K=K, B=B, L=2, **over), members=members(K, width))
     assert (p["tiles_fwd"], p["tiles_dx"]) == (fwd, dx)
+
+
+@pytest.mark.parametrize("d_in,rows", [(16_000, 8_192), (65_528, 8_192), (65_536, 4_096), (262_144, 1_024)])
+def test_wide_inputs_keep_the_chunks_that_fit(d_in, rows):
+    # a chunk shrinks only where its rows would pass the loaders' limit: smaller
+    # ones serve short requests by other tiles
+    cfg = configs.workload("regression_onehot", K=4, B=256, L=1, d_in=d_in, precision="fp32")
+    assert tabpack.debug_plan(cfg, members=members(4, 128))["eval_rows"][0] == rows
