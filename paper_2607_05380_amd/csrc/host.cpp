@@ -844,11 +844,16 @@ constexpr int kMiniMaxTiles = 256, kMiniSide = 896, kMiniSideL1 = 512, kMiniSide
 // (640) 1,624 / 1,669; 18 of 1222 (1,248) 2,283 / 2,080.  Against small tiles (fewer than
 // kTallMinTiles) of two members or more an XCD, which even them out, half that depth will
 // do: 32 members of widths 256..1024 on 256 features 563 / 557, 64 of 128..512 on 300 427 /
-// 421; against tall ones 64 of 256..1024 on 256 1,170 / 1,180.
+// 421; against tall ones 64 of 256..1024 on 256 1,170 / 1,180.  Evaluation, whose one
+// launch a layer runs alone, gains from them down to a depth of about 192 (us, tall below
+// a depth of 64 / 192 / 512): 100 members of widths 100..200 on 20,000 rows 1,533 / 1,455 /
+// 1,456; 40 of 300..700 on 128 features 1,431 / 1,382 / 1,383; 16 of 150..300 341 / 340 / 355;
+// 8 of 256..512 on 200 333 / 332 / 354; 30 of 100..400 on 2,000 rows 137 / 137 / 148; but 128 of
+// 100..384 on 300 2,763 / 2,762 / 2,501.
 struct HugeMin {
   int tiles = 0, depth = 0;  // least small tiles and tile-weighted mean depth of a launch (tiles 0: never)
 };
-constexpr HugeMin kHugeFwd{640, 512}, kHugeDx{2048, 768};
+constexpr HugeMin kHugeFwd{640, 512}, kHugeDx{2048, 768}, kHugeEval{640, 192};
 // The output tiles of a launch, or of the launches of all member groups.
 struct LaunchSize {
   int64_t small = 0, mini = 0, work = 0, members = 0;  // work: small tiles times depth
@@ -1170,7 +1175,7 @@ Plan build_plan(const pack_handle* h, const Bufs& bf, const std::vector<int> (&g
         for (int k : group[hf])
           if (h->mem[k].depth >= l) z.add(R, h->mem[k].dp, l == 1 ? h->mem[k].p_in : h->mem[k].dp);
       p.tile_set = l == 1 && h->emb ? (sizing ? TILES_SMALL : h->emb_tiles)
-                                    : choose(h->tiles_fwd, z, LaunchSize{}, R >= kBigTile ? kHugeFwd : HugeMin{});
+                                    : choose(h->tiles_fwd, z, LaunchSize{}, R >= kBigTile ? kHugeEval : HugeMin{});
       for (int hf = 0; hf < kGroups; ++hf)
         for (int k : group[hf]) {
           const Member& m = h->mem[k];

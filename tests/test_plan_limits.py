@@ -135,3 +135,10 @@ def test_wide_inputs_keep_the_chunks_that_fit(d_in, rows):
     # ones serve short requests by other tiles
     cfg = configs.workload("regression_onehot", K=4, B=256, L=1, d_in=d_in, precision="fp32")
     assert tabpack.debug_plan(cfg, members=members(4, 128))["eval_rows"][0] == rows
+
+
+@pytest.mark.parametrize("width,tiles", [(128, 2), (160, 2), (192, 5), (512, 5)])
+def test_huge_evaluation_tiles_by_depth(width, tiles):
+    # tall (2) or huge (5) from 1,024 small tiles on: a depth of 192
+    p = tabpack.debug_plan(configs.workload("regression_onehot", K=64, B=256, L=2), members=members(64, width))
+    assert p["eval_tiles"][0] == tiles
